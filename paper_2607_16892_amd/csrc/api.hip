@@ -27,13 +27,14 @@ struct dro_ctx {
     hipStream_t staged_stream = nullptr;
     std::vector<int64_t> staged_off;
     std::vector<int32_t> staged_seg;
+    dro::RowPlan staged_rows{};  // parts of the staged segments; boff points into `stage`
     char err[1024] = {0};
     // host staging of the configuration-space count table (kept alive until
     // the next configuration search on this context has been enqueued)
     std::vector<long long> ways_h;
     std::vector<int32_t> gpus_h;
-    // host copy of the quantile's row table (segments with unequal part counts)
-    std::vector<int64_t> qboff_h;
+    // host copy of the row table (segments with unequal part counts)
+    std::vector<int64_t> boff_h;
 };
 
 // Scratch of dro_cost_eval_noalloc: a fixed array in every device's memory,
@@ -217,37 +218,53 @@ size_t stage_bytes(const dro_problem *p)
     return rup((size_t)(p->S + 1) * 8) + (p->seg_h ? rup((size_t)p->C * 4) : 0);
 }
 
+// The parts every segment's samples are counted in (rows): one count for all
+// segments when they agree, else a row table, built into ctx->boff_h.
+RowPlan plan_rows(dro_ctx *ctx, const dro_problem *p)
+{
+    const int64_t *o = p->offsets_h;
+    const long long len = row_part_len(o, p->S, ctx->num_cu);
+    RowPlan pl{};
+    bool uniform = true;
+    for (int s = 0; s < p->S; ++s) {
+        const long long b = row_parts(o[s + 1] - o[s], len);
+        if (s == 0) pl.B = (int)b;
+        else if (b != pl.B) uniform = false;
+        pl.rows += b;
+    }
+    if (!uniform) {
+        pl.B = 0;
+        std::vector<int64_t> &bo = ctx->boff_h;
+        bo.assign((size_t)p->S + 1, 0);
+        for (int s = 0; s < p->S; ++s) bo[s + 1] = bo[s] + row_parts(o[s + 1] - o[s], len);
+    }
+    return pl;
+}
+
 // The offsets (and segment map) every kernel indexes with: the host copies of
-// the call, uploaded to the device.  Calls on the workspace keep them in the
-// ctx's staging buffer and skip the upload when the host arrays and the stream
-// equal the last ones staged; the no-allocation path stages them into its
-// arena on every call (the static array is shared by every ctx of the device).
-int stage_problem(dro_ctx *ctx, const dro_problem *p, Arena &ar, hipStream_t st, dro_problem *q)
+// the call, uploaded to the device, with the row table of unequal segments
+// behind them.  Calls on the workspace keep them in the ctx's staging buffer
+// and skip the upload when the host arrays and the stream equal the last ones
+// staged.  `q` is the problem with the staged arrays, `rows` its row plan.
+int stage_problem(dro_ctx *ctx, const dro_problem *p, hipStream_t st, dro_problem *q, RowPlan *rows)
 {
     *q = *p;
     const size_t ob = (size_t)(p->S + 1) * 8, sb = p->seg_h ? (size_t)p->C * 4 : 0;
-    char *dst;
-    if (ar.base != (char *)ctx->ws) {
-        dst = ar.take<char>(stage_bytes(p));
-    } else {
-        const bool same =
-            ctx->staged && ctx->staged_stream == st && ctx->staged_off.size() == (size_t)p->S + 1 &&
-            std::equal(p->offsets_h, p->offsets_h + p->S + 1, ctx->staged_off.begin()) &&
-            (p->seg_h ? ctx->staged_seg.size() == (size_t)p->C &&
-                            std::equal(p->seg_h, p->seg_h + p->C, ctx->staged_seg.begin())
-                      : ctx->staged_seg.empty());
-        if (same) {
-            q->offsets = reinterpret_cast<int64_t *>(ctx->stage);
-            if (p->seg_h) q->seg = reinterpret_cast<int32_t *>((char *)ctx->stage + rup(ob));
-            return DRO_OK;
-        }
+    const bool same =
+        ctx->staged && ctx->staged_stream == st && ctx->staged_off.size() == (size_t)p->S + 1 &&
+        std::equal(p->offsets_h, p->offsets_h + p->S + 1, ctx->staged_off.begin()) &&
+        (p->seg_h ? ctx->staged_seg.size() == (size_t)p->C &&
+                        std::equal(p->seg_h, p->seg_h + p->C, ctx->staged_seg.begin())
+                  : ctx->staged_seg.empty());
+    if (!same) {
         ctx->staged = false;
-        if (stage_bytes(p) > ctx->stage_size) {
+        const size_t need = stage_bytes(p) + rup(ob);
+        if (need > ctx->stage_size) {
             HIPCHK(hipDeviceSynchronize());  // earlier work may still read the old copy
             if (ctx->stage) HIPCHK(hipFree(ctx->stage));
             ctx->stage = nullptr;
             ctx->stage_size = 0;
-            const size_t sz = stage_bytes(p) + (1u << 12);
+            const size_t sz = need + (1u << 12);
             if (hipMalloc(&ctx->stage, sz) != hipSuccess) {
                 (void)hipGetLastError();
                 ctx->stage = nullptr;
@@ -255,20 +272,48 @@ int stage_problem(dro_ctx *ctx, const dro_problem *p, Arena &ar, hipStream_t st,
             }
             ctx->stage_size = sz;
         }
-        dst = (char *)ctx->stage;
-    }
-    HIPCHK(hipMemcpyAsync(dst, p->offsets_h, ob, hipMemcpyHostToDevice, st));
-    q->offsets = reinterpret_cast<int64_t *>(dst);
-    if (p->seg_h) {
-        HIPCHK(hipMemcpyAsync(dst + rup(ob), p->seg_h, sb, hipMemcpyHostToDevice, st));
-        q->seg = reinterpret_cast<int32_t *>(dst + rup(ob));
-    }
-    if (dst == (char *)ctx->stage) {
+        // pageable sources: copied out before the calls return
+        char *dst = (char *)ctx->stage;
+        HIPCHK(hipMemcpyAsync(dst, p->offsets_h, ob, hipMemcpyHostToDevice, st));
+        if (p->seg_h)
+            HIPCHK(hipMemcpyAsync(dst + rup(ob), p->seg_h, sb, hipMemcpyHostToDevice, st));
+        RowPlan pl = plan_rows(ctx, p);
+        if (!pl.B) {
+            int64_t *boff = reinterpret_cast<int64_t *>(dst + stage_bytes(p));
+            HIPCHK(hipMemcpyAsync(boff, ctx->boff_h.data(), ob, hipMemcpyHostToDevice, st));
+            pl.boff = boff;
+        }
+        ctx->staged_rows = pl;
         ctx->staged_off.assign(p->offsets_h, p->offsets_h + p->S + 1);
         if (p->seg_h) ctx->staged_seg.assign(p->seg_h, p->seg_h + p->C);
         else ctx->staged_seg.clear();
         ctx->staged_stream = st;
         ctx->staged = true;
+    }
+    q->offsets = reinterpret_cast<int64_t *>(ctx->stage);
+    if (p->seg_h) q->seg = reinterpret_cast<int32_t *>((char *)ctx->stage + rup(ob));
+    *rows = ctx->staged_rows;
+    return DRO_OK;
+}
+
+// The same into the arena, on every call (the no-allocation path: its static
+// array is shared by every ctx of the device); the row table only if `packed`.
+int stage_in_arena(dro_ctx *ctx, const dro_problem *p, Arena &ar, bool packed, hipStream_t st,
+                   dro_problem *q, RowPlan *rows)
+{
+    *q = *p;
+    const size_t ob = (size_t)(p->S + 1) * 8;
+    char *dst = ar.take<char>(stage_bytes(p));
+    HIPCHK(hipMemcpyAsync(dst, p->offsets_h, ob, hipMemcpyHostToDevice, st));
+    q->offsets = reinterpret_cast<int64_t *>(dst);
+    if (p->seg_h) {
+        HIPCHK(hipMemcpyAsync(dst + rup(ob), p->seg_h, (size_t)p->C * 4, hipMemcpyHostToDevice, st));
+        q->seg = reinterpret_cast<int32_t *>(dst + rup(ob));
+    }
+    if (packed && !rows->B) {
+        int64_t *boff = ar.take<int64_t>((size_t)p->S + 1);
+        HIPCHK(hipMemcpyAsync(boff, ctx->boff_h.data(), ob, hipMemcpyHostToDevice, st));
+        rows->boff = boff;
     }
     return DRO_OK;
 }
@@ -333,10 +378,10 @@ int check_dense(dro_ctx *ctx, const dro_problem *p)
 }
 
 // Exact S into `S` ([C][K][M] doubles): the dense per-sample sums, then the
-// exact epilogue over the segments' prefix counts and sums (cnt, sum).  claim:
+// exact epilogue over the segments' prefix entries.  claim:
 // dense_claim_words scratch.
-int run_dense(dro_ctx *ctx, const dro_problem *p, double *S, const uint32_t *cnt,
-              const uint64_t *sum, const DensePlan &pl, uint32_t *claim, hipStream_t st)
+int run_dense(dro_ctx *ctx, const dro_problem *p, double *S, const PrefixEntry *pre,
+              const DensePlan &pl, uint32_t *claim, hipStream_t st)
 {
     unsigned long long *R = reinterpret_cast<unsigned long long *>(S);
     const long long ckm = (long long)p->C * p->K * p->M;
@@ -366,8 +411,7 @@ int run_dense(dro_ctx *ctx, const dro_problem *p, double *S, const uint32_t *cnt
     f.lam = p->lam;
     f.c_p = p->c_p;
     f.c_w = p->c_w;
-    f.cnt = cnt;
-    f.sum = sum;
+    f.pre = pre;
     f.C = p->C;
     f.K = p->K;
     f.M = p->M;
@@ -384,27 +428,48 @@ long long max_segment(const dro_problem *p)
     return max_seg;
 }
 
-struct QuantBufs {
-    uint32_t *hist;  // [S][kHistBins]
-    int B;           // histogram blocks per segment
-};
+// Prefix entries of every segment: counted in packed rows while their scratch
+// stays within kMaxCountRows rows (270 MB), else through a merged histogram,
+// whose scratch does not grow with the samples (rows hold at most 65,535 each,
+// so it takes over beyond 2.7e8 samples, and where the no-allocation array
+// cannot hold the rows).
+constexpr long long kMaxCountRows = 4096;
 
-size_t quantile_bytes(const dro_problem *p) { return rup((size_t)p->S * kHistBins * 4); }
+bool packed_rows(const RowPlan &pl) { return pl.rows <= kMaxCountRows; }
 
-QuantBufs take_quantile(Arena &ar, const dro_problem *p, int num_cu)
+size_t prefix_bytes(const dro_problem *p)
 {
-    QuantBufs q;
-    q.B = hist_parts(p->S, max_segment(p), num_cu);
-    q.hist = ar.take<uint32_t>((size_t)p->S * kHistBins);
-    return q;
+    return (size_t)p->S * kHistBins * sizeof(PrefixEntry);
 }
 
-int run_quantile(dro_ctx *ctx, const dro_problem *p, const QuantBufs &qb, int32_t *q_value,
-                 int64_t *q_rank, hipStream_t st)
+size_t counts_bytes(const dro_problem *p, const RowPlan &pl, bool packed)
 {
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
-    HIPCHK(launch_select(p->offsets, p->seg, p->c_p, p->c_w, qb.hist, p->C, q_value, q_rank, st));
-    return DRO_OK;
+    if (packed)
+        return rup((size_t)pl.rows * kQStride * 4) + 2 * rup((size_t)pl.rows * kQBuckets * 4) +
+               rup(prefix_bytes(p));
+    return rup((size_t)p->S * kHistBins * 4) +
+           rup(prefix_bytes(p) + 8 + (size_t)p->S * kPrefixChunks * 16);
+}
+
+CountBufs take_counts(Arena &ar, const dro_problem *p, const RowPlan &pl, bool packed, int num_cu)
+{
+    CountBufs b{};
+    b.plan = pl;
+    if (packed) {
+        b.fine = ar.take<uint32_t>((size_t)pl.rows * kQStride);
+        b.coarse = ar.take<uint32_t>((size_t)pl.rows * kQBuckets);
+        b.csum = ar.take<uint32_t>((size_t)pl.rows * kQBuckets);
+        b.pre = ar.take<PrefixEntry>((size_t)p->S * kHistBins);
+        return b;
+    }
+    b.plan.B = hist_parts(p->S, max_segment(p), num_cu);
+    b.plan.boff = nullptr;
+    b.hist = ar.take<uint32_t>((size_t)p->S * kHistBins);
+    const size_t pre8 = (prefix_bytes(p) + 7) & ~size_t(7);
+    char *m = ar.take<char>(pre8 + (size_t)p->S * kPrefixChunks * 16);
+    b.pre = reinterpret_cast<PrefixEntry *>(m);
+    b.tot = reinterpret_cast<uint64_t *>(m + pre8);
+    return b;
 }
 
 // E radius rows of C classes are indexed as e C + c in 32 bits.
@@ -418,35 +483,36 @@ int check_rows(dro_ctx *ctx, int E, int C)
 bool finite_pos(float v) { return std::isfinite(v) && v > 0.0f; }
 bool in_limits(float v) { return v >= 0x1p-10f && v <= 0x1p7f; }
 
-// Scratch of one dense evaluation beyond S: the value histogram, the prefix
-// counts and sums, the slice claim counters (and, on the no-allocation path,
-// the staged offsets and segment map).
-size_t cost_eval_scratch_bytes(const dro_problem *p, bool with_stage)
+// Scratch of one dense evaluation beyond S: the counts' scratch and the slice
+// claim counters.
+size_t cost_eval_scratch_bytes(const dro_problem *p, const RowPlan &pl, bool packed)
+{
+    return counts_bytes(p, pl, packed) + rup(dense_claim_words(p->C, p->K, p->M) * 4);
+}
+
+// What dro_cost_eval_noalloc accepts: the staged arrays and 16 bytes per value of
+// a segment (its merged histogram and prefix entries), the chunk totals and the
+// claim counters.
+size_t noalloc_need(const dro_problem *p)
 {
     const size_t bins = (size_t)p->S * kHistBins;
-    return (with_stage ? stage_bytes(p) : 0) + quantile_bytes(p) + rup(bins * 4) +
-           rup(prefix_sum_words(p->S) * 8) + rup(dense_claim_words(p->C, p->K, p->M) * 4);
+    return stage_bytes(p) + rup(bins * 4) + rup(bins * 4) +
+           rup(bins * 8 + (size_t)p->S * kPrefixChunks * 16) +
+           rup(dense_claim_words(p->C, p->K, p->M) * 4);
 }
 
 // The dense evaluation over scratch taken from `ar` (the device must be
-// current): value counts and sample sums of every segment, the exact S into
-// Sbuf, then the minimum over the multipliers.
-int run_cost_eval(dro_ctx *ctx, const dro_problem *p, const Shape &sh, int E, const float *eps,
-                  double *W, int32_t *m_star, double *Sbuf, Arena &ar, hipStream_t st)
+// current; p holds the staged arrays): value counts and sample sums of every
+// segment, the exact S into Sbuf, then the minimum over the multipliers.
+int run_cost_eval(dro_ctx *ctx, const dro_problem *p, const Shape &sh, const RowPlan &rows,
+                  bool packed, int E, const float *eps, double *W, int32_t *m_star, double *Sbuf,
+                  Arena &ar, hipStream_t st)
 {
-    dro_problem q;
-    int rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
-    p = &q;
     const DensePlan pl = plan_dense(p->C, p->K, p->M, sh.max_n, ctx->num_cu, ctx->dense_bpc);
-    const size_t bins = (size_t)p->S * kHistBins;
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
-    uint32_t *cnt = ar.take<uint32_t>(bins);
-    uint64_t *sum = ar.take<uint64_t>(prefix_sum_words(p->S));
+    const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
     uint32_t *claim = ar.take<uint32_t>(dense_claim_words(p->C, p->K, p->M));
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
-    HIPCHK(launch_prefix(qb.hist, p->S, cnt, sum, st));
-    rc = run_dense(ctx, p, Sbuf, cnt, sum, pl, claim, st);
+    HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
+    const int rc = run_dense(ctx, p, Sbuf, cb.pre, pl, claim, st);
     if (rc) return rc;
     HIPCHK(launch_min_over_lambda(Sbuf, p->offsets, p->seg, p->lam, eps, E, p->C, p->K, p->M, W,
                                   m_star, st));
@@ -602,11 +668,15 @@ int dro_cost_eval(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *ep
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
     const size_t ckm = (size_t)p->C * p->K * p->M;
-    rc = ensure_ws(ctx, (S ? 0 : rup(ckm * 8)) + cost_eval_scratch_bytes(p, false), st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    const bool packed = packed_rows(rows);
+    rc = ensure_ws(ctx, (S ? 0 : rup(ckm * 8)) + cost_eval_scratch_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
     double *Sbuf = S ? S : ar.take<double>(ckm);
-    return run_cost_eval(ctx, p, sh, E, eps, W, m_star, Sbuf, ar, st);
+    return run_cost_eval(ctx, &q, sh, rows, packed, E, eps, W, m_star, Sbuf, ar, st);
 }
 
 int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
@@ -621,7 +691,7 @@ int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const f
     if (!ctx->scratch)
         return fail(ctx, DRO_EHIP, "the scratch array's device address is unknown on device %d",
                     ctx->device);
-    const size_t need = cost_eval_scratch_bytes(p, true);
+    const size_t need = noalloc_need(p);
     if (need > (size_t)DRO_NOALLOC_SCRATCH_BYTES)
         return fail(ctx, DRO_ELIMIT,
                     "the problem needs %zu bytes of scratch; the no-allocation array holds %zu",
@@ -629,7 +699,14 @@ int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const f
     if ((rc = check_dense(ctx, p))) return rc;
     ENTER_DEVICE(ctx);
     Arena ar{(char *)ctx->scratch, 0};
-    return run_cost_eval(ctx, p, sh, E, eps, W, m_star, S, ar, (hipStream_t)stream);
+    dro_problem q;
+    RowPlan rows = plan_rows(ctx, p);
+    const bool packed =
+        packed_rows(rows) && stage_bytes(p) + rup(((size_t)p->S + 1) * 8) +
+                                     cost_eval_scratch_bytes(p, rows, true) <=
+                                 (size_t)DRO_NOALLOC_SCRATCH_BYTES;
+    if ((rc = stage_in_arena(ctx, p, ar, packed, (hipStream_t)stream, &q, &rows))) return rc;
+    return run_cost_eval(ctx, &q, sh, rows, packed, E, eps, W, m_star, S, ar, (hipStream_t)stream);
 }
 
 int dro_argmin_reservation(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
@@ -645,12 +722,12 @@ int dro_argmin_reservation(dro_ctx *ctx, const dro_problem *p, int32_t E, const 
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
     const size_t eck = (size_t)E * p->C * p->K;
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
     rc = ensure_ws(ctx, rup(eck * 8) + rup(eck * 4), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
     double *W = ar.take<double>(eck);
     int32_t *m_star = ar.take<int32_t>(eck);
@@ -671,42 +748,20 @@ int class_quantile(dro_ctx *ctx, const dro_problem *p, int32_t *q_value, int64_t
     if (!q_value || !q_rank) return fail(ctx, DRO_EINVAL, "q_value and q_rank must be non-NULL");
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    // parts per segment (one row of counts each); one count for all segments
-    // when they agree, else a row table: segment s owns rows boff[s] .. boff[s+1]
-    const int64_t *o = p->offsets_h;
-    long long B = 0, rows = 0;
-    bool uniform = true;
-    for (int s = 0; s < p->S; ++s) {
-        const long long b = qhist_parts(p->S, o[s + 1] - o[s], ctx->num_cu);
-        if (s == 0) B = b;
-        else if (b != B) uniform = false;
-        rows += b;
-    }
-    if (rows > 0x7fffffffLL)
-        return fail(ctx, DRO_ELIMIT, "%lld quantile rows exceed 2^31 - 1", rows);
-    std::vector<int64_t> &bo = ctx->qboff_h;
-    if (!uniform) {
-        bo.assign((size_t)p->S + 1, 0);
-        for (int s = 0; s < p->S; ++s) bo[s + 1] = bo[s] + qhist_parts(p->S, o[s + 1] - o[s], ctx->num_cu);
-    }
-    const size_t table = uniform ? 0 : rup(((size_t)p->S + 1) * 8);
-    rc = ensure_ws(ctx, rup((size_t)rows * kQStride * 4) + rup((size_t)rows * kQBuckets * 4) + table, st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    if (rows.rows > 0x7fffffffLL)
+        return fail(ctx, DRO_ELIMIT, "%lld quantile rows exceed 2^31 - 1", rows.rows);
+    rc = ensure_ws(ctx, rup((size_t)rows.rows * kQStride * 4) + rup((size_t)rows.rows * kQBuckets * 4),
+                   st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
-    uint32_t *fine = ar.take<uint32_t>((size_t)rows * kQStride);
-    uint32_t *coarse = ar.take<uint32_t>((size_t)rows * kQBuckets);
-    int64_t *boff = nullptr;
-    if (!uniform) {  // pageable source: copied out before the call returns
-        boff = ar.take<int64_t>((size_t)p->S + 1);
-        HIPCHK(hipMemcpyAsync(boff, bo.data(), ((size_t)p->S + 1) * 8, hipMemcpyHostToDevice, st));
-    }
-    HIPCHK(launch_class_quantile(p->offsets, p->seg, p->xi, p->c_p, p->c_w, p->S, p->C,
-                                 uniform ? (int)B : 0, boff, rows, fine, coarse, q_value, q_rank,
-                                 st));
+    uint32_t *fine = ar.take<uint32_t>((size_t)rows.rows * kQStride);
+    uint32_t *coarse = ar.take<uint32_t>((size_t)rows.rows * kQBuckets);
+    HIPCHK(launch_class_quantile(p->offsets, p->seg, p->xi, p->c_p, p->c_w, p->S, p->C, rows, fine,
+                                 coarse, q_value, q_rank, st));
     return DRO_OK;
 }
 
@@ -722,21 +777,19 @@ int dro_exact_table(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *
     if ((rc = check_rows(ctx, E, p->C))) return rc;
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    const size_t bins = (size_t)p->S * kHistBins;
-    rc = ensure_ws(ctx, quantile_bytes(p) + rup(bins * 4) + rup(prefix_sum_words(p->S) * 8), st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    const bool packed = packed_rows(rows);
+    rc = ensure_ws(ctx, counts_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
-    uint32_t *cnt = ar.take<uint32_t>(bins);
-    uint64_t *sum = ar.take<uint64_t>(prefix_sum_words(p->S));
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
+    const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
+    HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
     HIPCHK(launch_exact_table(p->offsets, p->seg, p->L, p->eta, p->lam, p->c_p, p->c_w, eps, k_max,
-                              qb.hist, p->S, E, p->C, p->K, p->M, cnt, sum, W, m_star, k_star,
-                              W_star, m_at_star, st));
+                              cb.pre, E, p->C, p->K, p->M, W, m_star, k_star, W_star, m_at_star,
+                              st));
     return DRO_OK;
 }
 
@@ -751,20 +804,18 @@ int dro_continuous_dual(dro_ctx *ctx, const dro_problem *p, int32_t E, const flo
     if ((rc = check_rows(ctx, E, p->C))) return rc;
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    const size_t bins = (size_t)p->S * kHistBins;
-    rc = ensure_ws(ctx, quantile_bytes(p) + rup(bins * 4) + rup(prefix_sum_words(p->S) * 8), st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    const bool packed = packed_rows(rows);
+    rc = ensure_ws(ctx, counts_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
-    uint32_t *cnt = ar.take<uint32_t>(bins);
-    uint64_t *sum = ar.take<uint64_t>(prefix_sum_words(p->S));
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
-    HIPCHK(launch_continuous_dual(p->offsets, p->seg, p->L, p->eta, p->c_p, p->c_w, eps, qb.hist,
-                                  p->S, E, p->C, p->K, cnt, sum, W, gamma, st));
+    const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
+    HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
+    HIPCHK(launch_continuous_dual(p->offsets, p->seg, p->L, p->eta, p->c_p, p->c_w, eps, cb.pre, E,
+                                  p->C, p->K, W, gamma, st));
     return DRO_OK;
 }
 
@@ -778,16 +829,16 @@ int class_moments(dro_ctx *ctx, const dro_problem *p, int64_t *count, int64_t *s
         return fail(ctx, DRO_EINVAL, "count, sum, sumsq and xmax must be non-NULL");
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    rc = ensure_ws(ctx, quantile_bytes(p), st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    rc = ensure_ws(ctx, rup((size_t)rows.rows * sizeof(RowMoments)), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
-    HIPCHK(launch_moments(p->seg, qb.hist, p->C, count, sum, sumsq, xmax, st));
+    RowMoments *rm = ar.take<RowMoments>(rows.rows);
+    HIPCHK(launch_moments(p->offsets, p->seg, p->xi, p->S, p->C, rows, rm, count, sum, sumsq, xmax,
+                          nullptr, 0, nullptr, st));
     return DRO_OK;
 }
 
@@ -803,20 +854,18 @@ int dro_reservation_cost(dro_ctx *ctx, const dro_problem *p, int32_t R, const in
         return fail(ctx, DRO_ELIMIT, "R*C = %lld reservations exceed 2^31", (long long)R * p->C);
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    const size_t bins = (size_t)p->S * kHistBins;
-    rc = ensure_ws(ctx, quantile_bytes(p) + rup(bins * 4) + rup(prefix_sum_words(p->S) * 8), st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    const bool packed = packed_rows(rows);
+    rc = ensure_ws(ctx, counts_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
-    uint32_t *cnt = ar.take<uint32_t>(bins);
-    uint64_t *sum = ar.take<uint64_t>(prefix_sum_words(p->S));
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
-    HIPCHK(launch_reservation_cost(p->offsets, p->seg, p->c_p, p->c_w, qb.hist, p->S, p->C, R,
-                                   eta_r, cnt, sum, cost, cover, st));
+    const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
+    HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
+    HIPCHK(launch_reservation_cost(p->offsets, p->seg, p->c_p, p->c_w, cb.pre, p->C, R, eta_r, cost,
+                                   cover, st));
     return DRO_OK;
 }
 
@@ -855,15 +904,16 @@ int bcd_init_state(dro_ctx *ctx, const dro_problem *p, int32_t *k0, dro_stream_t
     if (!k0) return fail(ctx, DRO_EINVAL, "k0 must be non-NULL");
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    rc = ensure_ws(ctx, rup((size_t)p->C * 8), st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    rc = ensure_ws(ctx, rup((size_t)rows.rows * sizeof(RowMoments)), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
-    unsigned long long *sums = ar.take<unsigned long long>(p->C);
-    HIPCHK(launch_bcd_init(p->offsets, p->seg, p->xi, p->eta, p->C, p->K, sh.max_n, sums, k0, st));
+    RowMoments *rm = ar.take<RowMoments>(rows.rows);
+    HIPCHK(launch_moments(p->offsets, p->seg, p->xi, p->S, p->C, rows, rm, nullptr, nullptr, nullptr,
+                          nullptr, p->eta, p->K, k0, st));
     return DRO_OK;
 }
 
@@ -884,33 +934,26 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     const int C = p->C;
     const DensePlan pl = plan_dense(C, p->K, p->M, sh.max_n, ctx->num_cu, ctx->dense_bpc);
     const size_t ckm = (size_t)C * p->K * p->M;
-    const size_t bins = (size_t)p->S * kHistBins;
-    const size_t need = rup(ckm * 8) + quantile_bytes(p) + rup(bins * 4) +
-                        rup(prefix_sum_words(p->S) * 8) + rup((size_t)C * p->K * 8) +
-                        rup((size_t)C * 8) + rup((size_t)C * 4) +
-                        rup(dense_claim_words(C, p->K, p->M) * 4);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    const bool packed = packed_rows(rows);
+    const size_t need = rup(ckm * 8) + cost_eval_scratch_bytes(p, rows, packed) +
+                        rup((size_t)C * p->K * 8) + rup((size_t)C * 4);
     rc = ensure_ws(ctx, need, st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
     double *S = ar.take<double>(ckm);
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
-    uint32_t *cnt = ar.take<uint32_t>(bins);
-    uint64_t *sum = ar.take<uint64_t>(prefix_sum_words(p->S));
+    const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
     double *W = ar.take<double>((size_t)C * p->K);
-    int64_t *q_rank = ar.take<int64_t>(C);
     int32_t *kcur = ar.take<int32_t>(C);
     uint32_t *claim = ar.take<uint32_t>(dense_claim_words(C, p->K, p->M));
 
-    rc = run_quantile(ctx, p, qb, out->q_value, q_rank, st);
-    if (rc) return rc;
-    // the quantile's value histogram also gives the prefix counts and sums of
-    // the dense epilogue
-    HIPCHK(launch_prefix(qb.hist, p->S, cnt, sum, st));
-    rc = run_dense(ctx, p, S, cnt, sum, pl, claim, st);
+    // the value counts give the quantile and the dense epilogue's counts and sums
+    HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
+    HIPCHK(launch_prefix_select(p->offsets, p->seg, p->c_p, p->c_w, cb.pre, C, out->q_value, st));
+    rc = run_dense(ctx, p, S, cb.pre, pl, claim, st);
     if (rc) return rc;
     HIPCHK(launch_min_over_lambda(S, p->offsets, p->seg, p->lam, eps, 1, C, p->K, p->M, W, nullptr,
                                   st));
@@ -1072,18 +1115,18 @@ int bcd_service_times(dro_ctx *ctx, const dro_problem *p, const dro_service *svc
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
     const int C = p->C;
-    rc = ensure_ws(ctx, quantile_bytes(p) + 4 * rup((size_t)C * 8), st);
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    rc = ensure_ws(ctx, rup((size_t)rows.rows * sizeof(RowMoments)) + 4 * rup((size_t)C * 8), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
+    RowMoments *rm = ar.take<RowMoments>(rows.rows);
     int64_t *cnt = ar.take<int64_t>(C), *sum = ar.take<int64_t>(C), *ssq = ar.take<int64_t>(C);
     int32_t *xmax = ar.take<int32_t>(C);
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
-    HIPCHK(launch_moments(p->seg, qb.hist, C, cnt, sum, ssq, xmax, st));
+    HIPCHK(launch_moments(p->offsets, p->seg, p->xi, p->S, C, rows, rm, cnt, sum, ssq, xmax, nullptr,
+                          0, nullptr, st));
     HIPCHK(launch_service_times(svc_args(svc, C), cnt, sum, ssq, T, ET2, st));
     return DRO_OK;
 }
@@ -1202,24 +1245,23 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
     const long long nz = count_configs(ctx, svc, st);
     if (nz < 0) return fail(ctx, DRO_EHIP, "stream synchronisation failed");
     if (nz > kMaxConfigs) return fail(ctx, DRO_ELIMIT, "%lld configurations exceed 2^32", nz);
-    const size_t bins = (size_t)p->S * kHistBins;
-    const size_t need = quantile_bytes(p) + rup(bins * 4) +
-                        rup(prefix_sum_words(p->S) * 8) + rup((size_t)C * K * 8) + rup((size_t)C * K * 4) +
+    dro_problem q;
+    RowPlan rows;
+    if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
+    const bool packed = packed_rows(rows);
+    const size_t need = counts_bytes(p, rows, packed) + rup((size_t)rows.rows * sizeof(RowMoments)) +
+                        rup((size_t)C * K * 8) + rup((size_t)C * K * 4) +
                         4 * rup((size_t)C * 8) + rup(lp1_tableau_doubles(C, G) * 8) +
                         rup((size_t)m * 4) + 4 * rup((size_t)CG * 8) + 2 * rup((size_t)CG) +
-                        7 * rup((size_t)G * 8) + 6 * rup((size_t)C * 8) +
+                        7 * rup((size_t)G * 8) + 5 * rup((size_t)C * 8) +
                         config_bytes(C, G, J, nz) + rup(64);
     rc = ensure_ws(ctx, need, st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    dro_problem q;
-    rc = stage_problem(ctx, p, ar, st, &q);
-    if (rc) return rc;
     p = &q;
     const SvcArgs s = svc_args(svc, C);
-    const QuantBufs qb = take_quantile(ar, p, ctx->num_cu);
-    uint32_t *pcnt = ar.take<uint32_t>(bins);
-    uint64_t *psum = ar.take<uint64_t>(prefix_sum_words(p->S));
+    const CountBufs vb = take_counts(ar, p, rows, packed, ctx->num_cu);
+    RowMoments *rm = ar.take<RowMoments>(rows.rows);
     double *W = ar.take<double>((size_t)C * K);
     int32_t *mstar = ar.take<int32_t>((size_t)C * K);
     int64_t *cnt = ar.take<int64_t>(C), *sum = ar.take<int64_t>(C), *ssq = ar.take<int64_t>(C);
@@ -1233,20 +1275,18 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
     double *Wq_blk = ar.take<double>(G);
     double *Wc = ar.take<double>(C);
     int32_t *eta_c = ar.take<int32_t>(C), *k_new = ar.take<int32_t>(C);
-    unsigned long long *sums = ar.take<unsigned long long>(C);
     int32_t *ctl = ar.take<int32_t>(8);  // converge flag, lp pivots, lp status
     const ConfigBufs cb = take_config(ar, C, G, J, nz);
     rc = upload_configs(ctx, cb, G, J, st);
     if (rc) return rc;
 
     // the exact worst-case table of the radius row, the moments, the service times, r0
-    HIPCHK(launch_histogram(p->offsets, p->xi, p->S, qb.B, qb.hist, st));
+    HIPCHK(launch_counts(p->offsets, p->xi, p->S, vb, st));
     HIPCHK(launch_exact_table(p->offsets, p->seg, p->L, p->eta, p->lam, p->c_p, p->c_w, eps, nullptr,
-                              qb.hist, p->S, 1, C, K, p->M, pcnt, psum, W, mstar, nullptr, nullptr,
-                              nullptr, st));
-    HIPCHK(launch_moments(p->seg, qb.hist, C, cnt, sum, ssq, xmax, st));
+                              vb.pre, 1, C, K, p->M, W, mstar, nullptr, nullptr, nullptr, st));
+    HIPCHK(launch_moments(p->offsets, p->seg, p->xi, p->S, C, rows, rm, cnt, sum, ssq, xmax, p->eta,
+                          K, k, st));
     HIPCHK(launch_service_times(s, cnt, sum, ssq, T, ET2, st));
-    HIPCHK(launch_bcd_init(p->offsets, p->seg, p->xi, p->eta, C, K, sh.max_n, sums, k, st));
     HIPCHK(launch_fill_u32(reinterpret_cast<uint32_t *>(pi), 2LL * CG, 0u, st));
     HIPCHK(launch_zero_u8(delta, CG, st));
 

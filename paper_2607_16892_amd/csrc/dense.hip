@@ -408,12 +408,12 @@ hipError_t launch_zero_u64_u32(unsigned long long *p, long long n, uint32_t *q, 
     return hipGetLastError();
 }
 
-// #{x <= v} of a segment from its prefix counts (cn[v], v in [0, 2^15]).
-__device__ __forceinline__ long long count_le(const uint32_t *cn, long long v, long long N)
+// #{x <= v} of a segment from its prefix entries (v in [0, 2^15]).
+__device__ __forceinline__ long long count_le(const PrefixEntry *pre, long long v, long long N)
 {
     if (v < 0) return 0;
     if (v >= kHistBins - 1) return N;
-    return (long long)cn[v];
+    return (long long)pre[v].cnt;
 }
 
 // S[c,k,m] from the per-sample sums sum |x - t_c| of the dense kernel (in R,
@@ -427,8 +427,8 @@ __device__ __forceinline__ void dense_finish_one(const DenseFinishArgs &a, long 
     const int m = (int)(i % a.M);
     const int s = seg_of(a.seg, c);
     const long long N = a.offsets[s + 1] - a.offsets[s];
-    const uint32_t *cn = a.cnt + (long long)s * kHistBins;
-    const __int128 sx = (__int128)a.sum[(long long)s * kHistBins + kHistBins - 1];
+    const PrefixEntry *cn = a.pre + (long long)s * kHistBins;
+    const __int128 sx = (__int128)cn[kHistBins - 1].sum();
     const float cpf = a.c_p[c], cwf = a.c_w[c];
     const bool upper = cwf <= cpf;
     const int L = a.L[c];

@@ -59,8 +59,22 @@ constexpr long long kMaxGridBlocks = 1LL << 20;
 hipError_t launch_zero_u64_u32(unsigned long long *p, long long n, uint32_t *q, long long nq,
                                hipStream_t st);
 
-// S from the dense kernel's sums and the segments' prefix counts and sums
-// (cnt, sum: [S][kHistBins], from launch_prefix), written over R as doubles.
+// ---- value counts ------------------------------------------------------------
+constexpr int kHistBins = 32769;  // values 0 .. 2^15
+// Prefix count #{x <= v} and sum of those samples of one segment: one entry per
+// value v, read with one 12-byte load.
+struct PrefixEntry {
+    uint32_t cnt, sum_lo, sum_hi;
+    __host__ __device__ static PrefixEntry of(uint32_t c, uint64_t s)
+    {
+        return PrefixEntry{c, (uint32_t)s, (uint32_t)(s >> 32)};
+    }
+    __host__ __device__ uint64_t sum() const { return (uint64_t)sum_lo | ((uint64_t)sum_hi << 32); }
+};
+
+// ---- dense epilogue ------------------------------------------------------------
+// S from the dense kernel's sums and the segments' prefix entries
+// (pre: [S][kHistBins], from launch_counts), written over R as doubles.
 struct DenseFinishArgs {
     const int64_t *offsets;
     const int32_t *seg;
@@ -69,8 +83,7 @@ struct DenseFinishArgs {
     const float *lam;
     const float *c_p;
     const float *c_w;
-    const uint32_t *cnt;
-    const uint64_t *sum;
+    const PrefixEntry *pre;
     int C, K, M;
     unsigned long long *R;
 };
@@ -80,58 +93,65 @@ hipError_t launch_min_over_lambda(const double *S, const int64_t *offsets, const
                                   const float *lam, const float *eps, int E, int C, int K, int M,
                                   double *W, int32_t *m_star, hipStream_t st);
 
-// ---- quantile ----------------------------------------------------------------
-constexpr int kHistBins = 32769;   // values 0 .. 2^15
-hipError_t launch_fill_u32(uint32_t *p, long long n, uint32_t v, hipStream_t st);
-// allows the histogram and quantile kernels their 128 KB of dynamic LDS (once per device)
-hipError_t hist_prepare();
-// blocks per segment for the histogram pass
-int hist_parts(int S, long long max_seg, int num_cu);
-// hist: [S][kHistBins], B blocks per segment (zeroed first when B > 1).
-hipError_t launch_histogram(const int64_t *offsets, const int32_t *xi, int S, int B,
-                            uint32_t *hist, hipStream_t st);
-hipError_t launch_select(const int64_t *offsets, const int32_t *seg, const float *c_p,
-                         const float *c_w, const uint32_t *hist, int C, int32_t *q_value,
-                         int64_t *q_rank, hipStream_t st);
-
-// ---- class_quantile (per-block packed histograms, then a select per class) ----
+// ---- rows: the parts the samples are counted in ---------------------------------
 constexpr int kQTop = 32768;              // largest sample value, 2^15
 constexpr int kQWords = kQTop / 2 + 1;    // packed 16-bit counts of the values 0 .. 2^15
 constexpr int kQStride = kQWords + 3;     // words per stored row and LDS copy (16-byte multiple)
 constexpr int kQBuckets = 256;            // coarse buckets of 128 values (the last also holds 2^15)
-constexpr long long kQMaxPart = 65535;    // samples per block, so every 16-bit count fits
-// blocks (parts) of a segment of n samples: about one block per compute unit
-// over all S segments, each holding at most kQMaxPart samples
-long long qhist_parts(int S, long long n, int num_cu);
-// fine: [S][B][kQStride] u32, coarse: [S][B][kQBuckets] u32 (scratch, fully written)
-// Parts: B per segment when boff is null (rows = S B), else boff[s] .. boff[s+1]
-// are segment s's rows (device int64 [S+1], rows = boff[S]).
+constexpr long long kQMaxPart = 65535;    // samples per row, so every 16-bit count fits
+// Every segment is cut into parts of about one length, one row each: B rows per
+// segment when boff is null (rows = S B), else boff[s] .. boff[s+1] are segment
+// s's rows (device int64 [S+1], rows = boff[S]).
+struct RowPlan {
+    long long rows;
+    int B;
+    const int64_t *boff;
+};
+// samples per part: about one part per compute unit over all segments (host offsets)
+long long row_part_len(const int64_t *offsets_h, int S, int num_cu);
+inline long long row_parts(long long n, long long len) { return n <= len ? 1 : (n + len - 1) / len; }
+
+hipError_t launch_fill_u32(uint32_t *p, long long n, uint32_t v, hipStream_t st);
+// allows the histogram and quantile kernels their 128 KB of dynamic LDS (once per device)
+hipError_t hist_prepare();
+
+// ---- class_quantile (per-block packed histograms, then a select per class) ----
+// fine: [rows][kQStride] u32, coarse: [rows][kQBuckets] u32 (scratch, fully written)
 hipError_t launch_class_quantile(const int64_t *offsets, const int32_t *seg, const int32_t *xi,
-                                 const float *c_p, const float *c_w, int S, int C, int B,
-                                 const int64_t *boff, long long rows, uint32_t *fine,
-                                 uint32_t *coarse, int32_t *q_value, int64_t *q_rank,
-                                 hipStream_t st);
+                                 const float *c_p, const float *c_w, int S, int C, const RowPlan &pl,
+                                 uint32_t *fine, uint32_t *coarse, int32_t *q_value,
+                                 int64_t *q_rank, hipStream_t st);
+
+// ---- prefix counts and sums of every segment -----------------------------------
+// From packed rows (fine, coarse and csum, the sums per coarse bucket: [rows]
+// each) or, where their scratch does not fit, from a merged histogram (hist
+// non-null: [S][kHistBins], plan.B blocks per segment; tot: the chunk totals).
+constexpr int kPrefixChunk = 4096;  // bins per chunk of the merged histogram's prefix pass
+constexpr int kPrefixChunks = (kHistBins + kPrefixChunk - 1) / kPrefixChunk;
+struct CountBufs {
+    RowPlan plan;
+    uint32_t *fine, *coarse, *csum;
+    uint32_t *hist;
+    uint64_t *tot;     // [S][kPrefixChunks][2]
+    PrefixEntry *pre;  // [S][kHistBins]
+};
+// blocks per segment of the merged histogram
+int hist_parts(int S, long long max_seg, int num_cu);
+hipError_t launch_counts(const int64_t *offsets, const int32_t *xi, int S, const CountBufs &b,
+                         hipStream_t st);
+// the critical-fractile quantile of every class from the prefix entries
+hipError_t launch_prefix_select(const int64_t *offsets, const int32_t *seg, const float *c_p,
+                                const float *c_w, const PrefixEntry *pre, int C, int32_t *q_value,
+                                hipStream_t st);
 
 // ---- exact table (value counts and prefix sums) -------------------------------
-// The prefix pass works in chunks of 4096 bins.  A sum array holds the S x
-// kHistBins prefix sums followed by S x kPrefixChunks (count, sum) chunk totals
-// that the pass uses as scratch: prefix_sum_words(S) u64 in all.
-constexpr int kPrefixChunk = 4096;
-constexpr int kPrefixChunks = (kHistBins + kPrefixChunk - 1) / kPrefixChunk;
-inline size_t prefix_sum_words(int S)
-{
-    return (size_t)S * kHistBins + (size_t)S * kPrefixChunks * 2;
-}
-// cnt[s][v] = #{x <= v}, sum[s][v] = sum of the samples <= v of segment s, from
-// its value histogram.
-hipError_t launch_prefix(const uint32_t *hist, int S, uint32_t *cnt, uint64_t *sum, hipStream_t st);
-// cnt: [S][kHistBins] u32, sum: prefix_sum_words(S) u64 scratch; k_star == null skips the argmin.
+// k_star == null skips the argmin.
 hipError_t launch_exact_table(const int64_t *offsets, const int32_t *seg, const int32_t *L,
                               const int32_t *eta, const float *lam, const float *c_p,
                               const float *c_w, const float *eps, const int32_t *k_max,
-                              const uint32_t *hist, int S, int E, int C, int K, int M,
-                              uint32_t *cnt, uint64_t *sum, double *W, int32_t *m_star,
-                              int32_t *k_star, double *W_star, int32_t *m_at_star, hipStream_t st);
+                              const PrefixEntry *pre, int E, int C, int K, int M, double *W,
+                              int32_t *m_star, int32_t *k_star, double *W_star, int32_t *m_at_star,
+                              hipStream_t st);
 // Per (e, c): the lowest k <= k_max[c] (k_max may be null: K - 1) with the
 // smallest W[e,c,k], W there, and m_star there (m_at_star may be null).
 hipError_t launch_table_argmin(const double *W, const int32_t *m_star, const int32_t *k_max,
@@ -141,17 +161,26 @@ hipError_t launch_table_argmin(const double *W, const int32_t *m_star, const int
 // continuous-multiplier dual over the same prefix counts (gamma: the smallest minimiser)
 hipError_t launch_continuous_dual(const int64_t *offsets, const int32_t *seg, const int32_t *L,
                                   const int32_t *eta, const float *c_p, const float *c_w,
-                                  const float *eps, const uint32_t *hist, int S, int E, int C,
-                                  int K, uint32_t *cnt, uint64_t *sum, double *W, double *gamma,
-                                  hipStream_t st);
+                                  const float *eps, const PrefixEntry *pre, int E, int C, int K,
+                                  double *W, double *gamma, hipStream_t st);
 
 // ---- reservation cost and class moments ----------------------------------------
-hipError_t launch_moments(const int32_t *seg, const uint32_t *hist, int C, int64_t *count,
-                          int64_t *sum, int64_t *sumsq, int32_t *xmax, hipStream_t st);
+struct RowMoments {
+    long long raw, sum;     // sum of the samples as they are, and clamped to 0 .. 2^15
+    unsigned long long sq;  // sum of squares and largest of the clamped samples
+    long long mx;
+};
+// rows: [plan.rows] scratch.  count .. xmax (may all be null) and, with eta, the
+// initial state of Alg. 1, r0 = L_in + E[xi]: k0[c] = the largest k with
+// eta[k] N <= the sum of the samples.
+hipError_t launch_moments(const int64_t *offsets, const int32_t *seg, const int32_t *xi, int S,
+                          int C, const RowPlan &pl, RowMoments *rows, int64_t *count, int64_t *sum,
+                          int64_t *sumsq, int32_t *xmax, const int32_t *eta, int K, int32_t *k0,
+                          hipStream_t st);
 hipError_t launch_reservation_cost(const int64_t *offsets, const int32_t *seg, const float *c_p,
-                                   const float *c_w, const uint32_t *hist, int S, int C, int R,
-                                   const int32_t *eta_r, uint32_t *cnt, uint64_t *sum,
-                                   double *cost, int64_t *cover, hipStream_t st);
+                                   const float *c_w, const PrefixEntry *pre, int C, int R,
+                                   const int32_t *eta_r, double *cost, int64_t *cover,
+                                   hipStream_t st);
 
 // ---- baseline reservations (policy comparison) ---------------------------------
 constexpr int kMaxBaselineKs = 8;
@@ -164,10 +193,6 @@ hipError_t launch_baselines(int C, const int64_t *count, const int64_t *sum, con
                             int32_t *mean_r, int32_t *lp_r, int32_t *block_r, hipStream_t st);
 
 // ---- block step ----------------------------------------------------------------
-// sums: [C] scratch
-hipError_t launch_bcd_init(const int64_t *offsets, const int32_t *seg, const int32_t *xi,
-                           const int32_t *eta, int C, int K, long long max_n,
-                           unsigned long long *sums, int32_t *k0, hipStream_t st);
 // The block step's Gauss-Seidel sweep over the exact W [C][K] (one radius row),
 // kcur [C] the state entering it (updated in place).
 hipError_t launch_bcd_sweep(const double *W, const int32_t *eta, int C, int K, int G,

@@ -20,6 +20,50 @@ namespace dro {
 
 __device__ __forceinline__ int seg_of_x(const int32_t *seg, int c) { return seg ? seg[c] : c; }
 
+// Wave-wide sums and scans with DPP moves: one VALU instruction a step, where a
+// shuffle is a trip through the LDS unit (the 96 shuffles a wave of a prefix
+// pass that used them took 9 of its 15 us).
+template <int kCtrl, int kRows = 0xf> __device__ __forceinline__ uint32_t dpp0(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRows, 0xf, true);
+}
+template <int kCtrl, int kRows = 0xf> __device__ __forceinline__ uint64_t dpp0(uint64_t x)
+{
+    return (uint64_t)dpp0<kCtrl, kRows>((uint32_t)x) |
+           ((uint64_t)dpp0<kCtrl, kRows>((uint32_t)(x >> 32)) << 32);
+}
+// inclusive scan over each row of 16 lanes (lane 15 of a row holds its total)
+template <class T> __device__ __forceinline__ T scan_row16(T x)
+{
+    x += dpp0<0x111>(x);  // row_shr:1
+    x += dpp0<0x112>(x);
+    x += dpp0<0x114>(x);
+    x += dpp0<0x118>(x);
+    return x;
+}
+// inclusive scan over each half of 32 lanes (lanes 31 and 63 hold the totals)
+template <class T> __device__ __forceinline__ T scan_half32(T x)
+{
+    x = scan_row16(x);
+    x += dpp0<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    return x;
+}
+// inclusive scan over the wave (lane 63 holds the total)
+template <class T> __device__ __forceinline__ T scan_wave(T x)
+{
+    x = scan_half32(x);
+    x += dpp0<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int l)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t x, int l)
+{
+    return (uint64_t)lane_value((uint32_t)x, l) | ((uint64_t)lane_value((uint32_t)(x >> 32), l) << 32);
+}
+
 #define HIPRET(expr)                                 \
     do {                                             \
         const hipError_t e_ = (expr);                \
@@ -27,25 +71,25 @@ __device__ __forceinline__ int seg_of_x(const int32_t *seg, int c) { return seg 
     } while (0)
 
 // Exact S of one (class, grid point, multiplier), in units of 2^-33, from the
-// prefix counts cn[v] = #{x <= v} and sums sm[v] = sum{x : x <= v} of the
+// prefix counts cnt(v) = #{x <= v} and sums sum(v) = sum{x : x <= v} of the
 // class's segment (N samples).  For 0 <= x, eta <= L the three candidates of
 // Step 4 reduce to the larger of two lines, B - a1 x and C - a2 (L - x) with
 // B = c_w eta, C = c_p (L - eta), a1 = min(g, c_w), a2 = min(g, c_p); the
 // first is the larger up to t = floor((B - C + a2 L) / (a1 + a2)), so
 //   S = B cnt(t) - a1 sum(t) + (C - a2 L)(N - cnt(t)) + a2 (sum_all - sum(t)),
 // every term an exact integer (the sum is non-negative, as phi is).
-__device__ __forceinline__ unsigned __int128 exact_S_prefix(const uint32_t *cn, const uint64_t *sm,
-                                                           int64_t N, int64_t L, int64_t eta,
-                                                           int64_t CP, int64_t CW, int64_t G)
+__device__ __forceinline__ unsigned __int128 exact_S_prefix(const PrefixEntry *pre, int64_t N,
+                                                           int64_t L, int64_t eta, int64_t CP,
+                                                           int64_t CW, int64_t G)
 {
     const int64_t B = CW * eta, Cc = CP * (L - eta);
     const int64_t A1 = G < CW ? G : CW, A2 = G < CP ? G : CP;
     const int64_t tmax = L < kHistBins - 1 ? L : kHistBins - 1;
     int64_t tt = floor_div(B - Cc + A2 * L, A1 + A2);
     tt = tt < -1 ? -1 : (tt > tmax ? tmax : tt);
-    const __int128 ct = tt >= 0 ? (__int128)cn[tt] : 0;
-    const __int128 st = tt >= 0 ? (__int128)sm[tt] : 0;
-    const __int128 sum_all = (__int128)sm[kHistBins - 1];
+    const __int128 ct = tt >= 0 ? (__int128)pre[tt].cnt : 0;
+    const __int128 st = tt >= 0 ? (__int128)pre[tt].sum() : 0;
+    const __int128 sum_all = (__int128)pre[kHistBins - 1].sum();
     const __int128 S = (__int128)B * ct - (__int128)A1 * st + (__int128)(Cc - A2 * L) * ((__int128)N - ct) +
                        (__int128)A2 * (sum_all - st);
     return (unsigned __int128)S;
@@ -177,41 +221,56 @@ __device__ int64_t exact_rank(float cp, float cw, int64_t N);
 // rows boff[s] .. boff[s + 1] - 1 of a table built by the host, in which the
 // block finds its segment by bisection.  No global atomics: the select reads
 // the segment's rows of the bucket it needs.
+//
+// kSums: also the sum of the values of each coarse bucket (below 2^31: 65,535
+// samples of at most 2^15), which the prefix pass starts its chunks from.
 constexpr int kQThreads = 1024;
 typedef uint32_t u32x4_nt __attribute__((ext_vector_type(4)));
 
+// The samples [lo, hi) of row r.
+struct RowPart {
+    long long lo, hi;
+};
+
+__device__ __forceinline__ RowPart row_part(const int64_t *offsets, int S, int B,
+                                            const int64_t *boff, long long r)
+{
+    int s;
+    long long b, Bs;
+    if (boff) {  // the segment whose rows hold r: boff[s] <= r < boff[s + 1]
+        int a = 0, z = S;
+        while (z - a > 1) {
+            const int mid = (a + z) >> 1;
+            if (boff[mid] <= r) a = mid;
+            else z = mid;
+        }
+        s = a;
+        b = r - boff[s];
+        Bs = boff[s + 1] - boff[s];
+    } else {
+        s = (int)(r / B);
+        b = r % B;
+        Bs = B;
+    }
+    const long long n0 = offsets[s], N = offsets[s + 1] - n0;
+    return RowPart{n0 + (N * b) / Bs, n0 + (N * (b + 1)) / Bs};
+}
+
+template <bool kSums>
 __global__ __launch_bounds__(kQThreads) void qhist_kernel(const int64_t *offsets, const int32_t *xi,
                                                           int S, int B, const int64_t *boff,
                                                           long long rows, uint32_t *fine,
-                                                          uint32_t *coarse)
+                                                          uint32_t *coarse, uint32_t *csum)
 {
     extern __shared__ uint32_t h[];  // 2 x kQStride words
     const int t = threadIdx.x;
     for (long long r = blockIdx.x; r < rows; r += gridDim.x) {
-        int s;
-        long long b, Bs;
-        if (boff) {  // the segment whose rows hold r: boff[s] <= r < boff[s + 1]
-            int a = 0, z = S;
-            while (z - a > 1) {
-                const int mid = (a + z) >> 1;
-                if (boff[mid] <= r) a = mid;
-                else z = mid;
-            }
-            s = a;
-            b = r - boff[s];
-            Bs = boff[s + 1] - boff[s];
-        } else {
-            s = (int)(r / B);
-            b = r % B;
-            Bs = B;
-        }
-        const long long n0 = offsets[s], N = offsets[s + 1] - n0;
-        const long long lo = n0 + (N * b) / Bs, hi = n0 + (N * (b + 1)) / Bs;
+        const RowPart rp = row_part(offsets, S, B, boff, r);
         uint32_t *hc = h + (t & 1) * kQStride;
         uint4 *h4 = reinterpret_cast<uint4 *>(h);
         const uint4 *g4 = reinterpret_cast<const uint4 *>(h + kQStride);
         for_each_sample<kQThreads>(
-            xi, lo, hi,
+            xi, rp.lo, rp.hi,
             [&](int v) {
                 v = v < 0 ? 0 : (v > kQTop ? kQTop : v);
                 // bit 14 of v selects the half (v = 2^15 has it clear)
@@ -238,12 +297,30 @@ __global__ __launch_bounds__(kQThreads) void qhist_kernel(const int64_t *offsets
             const uint4 c = make_uint4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
             __builtin_nontemporal_store(u32x4_nt{c.x, c.y, c.z, c.w}, reinterpret_cast<u32x4_nt *>(out + q));
             uint32_t p = (c.x + c.y) + (c.z + c.w);
-            for (int d = 1; d < 32; d <<= 1) p += __shfl_xor(p, d, 64);
-            if ((t & 31) == 0) {
-                const int bk = q >> 5;
-                co[bk] = p & 0xffffu;
+            const int bk = q >> 5;
+            // sums of the values less the bucket's first one (below 2^23)
+            uint32_t vl = 0, vh = 0;
+            if (kSums) {
+                const uint32_t o = 4u * (q & 31), pl = p & 0xffffu, ph = p >> 16;
+                vl = o * pl + (c.y & 0xffffu) + 2u * (c.z & 0xffffu) + 3u * (c.w & 0xffffu);
+                vh = o * ph + (c.y >> 16) + 2u * (c.z >> 16) + 3u * (c.w >> 16);
+            }
+            p = scan_half32(p);
+            if (kSums) {
+                vl = scan_half32(vl);
+                vh = scan_half32(vh);
+            }
+            if ((t & 31) == 31) {
                 // the last bucket also holds the value 2^15
-                co[128 + bk] = (p >> 16) + (bk == 127 ? (h[kQTop / 2] + h[kQStride + kQTop / 2]) & 0xffffu : 0u);
+                const uint32_t top =
+                    bk == 127 ? (h[kQTop / 2] + h[kQStride + kQTop / 2]) & 0xffffu : 0u;
+                co[bk] = p & 0xffffu;
+                co[128 + bk] = (p >> 16) + top;
+                if (kSums) {
+                    uint32_t *cv = csum + r * kQBuckets;
+                    cv[bk] = vl + 128u * bk * (p & 0xffffu);
+                    cv[128 + bk] = vh + (kQTop / 2 + 128u * bk) * (p >> 16) + (uint32_t)kQTop * top;
+                }
             }
         }
         if (t == 0) {  // the group of the value 2^15 and the padding words
@@ -391,7 +468,6 @@ __global__ __launch_bounds__(kQThreads) void qselect_kernel(const int64_t *offse
     }
 }
 
-hipError_t select_prepare();
 hipError_t qhist_prepare();
 
 hipError_t hist_prepare()
@@ -400,8 +476,27 @@ hipError_t hist_prepare()
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                              (int)(kHistBins * sizeof(uint32_t)));
     if (e != hipSuccess) return e;
-    const hipError_t e2 = select_prepare();
-    return e2 != hipSuccess ? e2 : qhist_prepare();
+    return qhist_prepare();
+}
+
+long long row_part_len(const int64_t *offsets_h, int S, int num_cu)
+{
+    // The shortest parts whose rows still fit one resident block per compute
+    // unit (their LDS counts allow one; a few more rows than units would take a
+    // second pass over the chip), at least 16,384 samples, below which a row's
+    // fixed cost (clearing and storing its counts) passes its reading time, and
+    // at most what 16-bit counts hold.
+    const long long slots = (long long)num_cu * ((S + num_cu - 1) / num_cu);
+    long long lo = 16384, hi = kQMaxPart;
+    while (lo < hi) {
+        const long long mid = (lo + hi) / 2;
+        long long rows = 0;
+        for (int s = 0; s < S && rows <= slots; ++s)
+            rows += row_parts(offsets_h[s + 1] - offsets_h[s], mid);
+        if (rows <= slots) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo;
 }
 
 int hist_parts(int S, long long max_seg, int num_cu)
@@ -437,185 +532,70 @@ __device__ int64_t exact_rank(float cp, float cw, int64_t N)
     return j;
 }
 
-// Block per class: prefix counts over the segment histogram; the j-th
-// smallest sample is the first value whose cumulative count reaches j.
-constexpr int kSelThreads = 1024;
+// One wave per class: the j-th smallest sample is the first value whose prefix
+// count reaches j, found in three 64-way steps (513 values a lane, then 9, then
+// one).
+constexpr int kSelWaves = 4;  // classes per block
 
-__device__ void select_class(const int64_t *offsets, const int32_t *seg, const float *c_p,
-                             const float *c_w, const uint32_t *hist, int c, uint32_t *hl,
-                             int32_t *q_value, int64_t *q_rank)
+__global__ __launch_bounds__(64 * kSelWaves) void prefix_select_kernel(
+    const int64_t *offsets, const int32_t *seg, const float *c_p, const float *c_w,
+    const PrefixEntry *pre, int C, int32_t *q_value)
 {
-    __shared__ uint64_t sc[kSelThreads / 64];
-    const int t = threadIdx.x;
-    const int s = seg_of_x(seg, c);
-    const int64_t N = offsets[s + 1] - offsets[s];
-    const uint32_t *h = hist + (long long)s * kHistBins;
-    // thread t owns the bins [t * per, (t + 1) * per); per is odd, so a wave's
-    // LDS reads fall in distinct banks
-    constexpr int per = (kHistBins + kSelThreads - 1) / kSelThreads;
-    {   // coalesced loads, all in flight before the first LDS store
-        uint32_t r[per];
-#pragma unroll
-        for (int i = 0; i < per; ++i) {
-            const int v = t + i * kSelThreads;
-            r[i] = v < kHistBins ? h[v] : 0u;
+    const int lane = threadIdx.x & 63;
+    // classes in a loop of whole waves (no block barrier)
+    for (long long c = (long long)blockIdx.x * kSelWaves + (threadIdx.x >> 6); c < C;
+         c += (long long)gridDim.x * kSelWaves) {
+        const int s = seg_of_x(seg, (int)c);
+        const int64_t j = exact_rank(c_p[c], c_w[c], offsets[s + 1] - offsets[s]);
+        const PrefixEntry *pc = pre + (long long)s * kHistBins;
+        int v0 = 0;  // the answer is in [v0, v0 + 64 step)
+        for (int step = 513; step >= 1; step = step == 513 ? 9 : (step == 9 ? 1 : 0)) {
+            const int v = min(v0 + (lane + 1) * step - 1, kHistBins - 1);
+            const unsigned long long reach = __ballot((int64_t)pc[v].cnt >= j);
+            // the last lane's value is 2^15 or past the answer, so some lane reaches j <= N
+            v0 += (reach ? __ffsll(reach) - 1 : 63) * step;
         }
-#pragma unroll
-        for (int i = 0; i < per; ++i) {
-            const int v = t + i * kSelThreads;
-            if (v < kHistBins) hl[v] = r[i];
-        }
-    }
-    const int64_t j = exact_rank(c_p[c], c_w[c], N);
-    __syncthreads();
-    const int b0 = t * per, b1 = min(kHistBins, b0 + per);
-    uint64_t part = 0;
-    for (int v = b0; v < b1; ++v) part += hl[v];
-    // inclusive scan of the thread totals: within each wave by shuffles, then
-    // over the wave totals
-    const int lane = t & 63, wave = t >> 6;
-    uint64_t incl = part;
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint64_t o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
-    if (lane == 63) sc[wave] = incl;
-    __syncthreads();
-    if (t == 0)
-        for (int w = 1; w < kSelThreads / 64; ++w) sc[w] += sc[w - 1];
-    __syncthreads();
-    if (wave > 0) incl += sc[wave - 1];
-    const uint64_t before = incl - part;
-    if ((int64_t)before < j && j <= (int64_t)incl) {
-        uint64_t cum = before;
-        for (int v = b0; v < b1; ++v) {
-            cum += hl[v];
-            if ((int64_t)cum >= j) {
-                q_value[c] = v;
-                break;
-            }
-        }
-    }
-    if (t == 0) q_rank[c] = j;
-}
-
-// classes in a block-uniform loop; the barrier lets the next class reuse the LDS
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const int64_t *offsets,
-                                                             const int32_t *seg, const float *c_p,
-                                                             const float *c_w, const uint32_t *hist,
-                                                             int C, int32_t *q_value, int64_t *q_rank)
-{
-    extern __shared__ uint32_t hl[];  // the segment's histogram, kHistBins words
-    for (int c = blockIdx.x; c < C; c += gridDim.x) {
-        select_class(offsets, seg, c_p, c_w, hist, c, hl, q_value, q_rank);
-        __syncthreads();
+        if (lane == 0) q_value[c] = min(v0, kHistBins - 1);
     }
 }
 
-hipError_t select_prepare()
+hipError_t launch_prefix_select(const int64_t *offsets, const int32_t *seg, const float *c_p,
+                                const float *c_w, const PrefixEntry *pre, int C, int32_t *q_value,
+                                hipStream_t st)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(select_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)(kHistBins * sizeof(uint32_t)));
-}
-
-hipError_t launch_select(const int64_t *offsets, const int32_t *seg, const float *c_p,
-                         const float *c_w, const uint32_t *hist, int C, int32_t *q_value,
-                         int64_t *q_rank, hipStream_t st)
-{
-    hipLaunchKernelGGL(select_kernel, dim3((unsigned)std::min((long long)C, kMaxGridBlocks)),
-                       dim3(kSelThreads), kHistBins * sizeof(uint32_t), st, offsets, seg, c_p, c_w,
-                       hist, C, q_value, q_rank);
+    const long long blocks = std::min(((long long)C + kSelWaves - 1) / kSelWaves, kMaxGridBlocks);
+    hipLaunchKernelGGL(prefix_select_kernel, dim3((unsigned)blocks), dim3(64 * kSelWaves), 0, st,
+                       offsets, seg, c_p, c_w, pre, C, q_value);
     return hipGetLastError();
 }
 
 hipError_t qhist_prepare()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(qhist_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)(2 * kQStride * sizeof(uint32_t)));
-}
-
-long long qhist_parts(int S, long long n, int num_cu)
-{
-    const long long need = (n + kQMaxPart - 1) / kQMaxPart;
-    return std::max((long long)hist_parts(S, n, num_cu), std::max(1LL, need));
+    const int bytes = (int)(2 * kQStride * sizeof(uint32_t));
+    HIPRET(hipFuncSetAttribute(reinterpret_cast<const void *>(qhist_kernel<false>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(qhist_kernel<true>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 hipError_t launch_class_quantile(const int64_t *offsets, const int32_t *seg, const int32_t *xi,
-                                 const float *c_p, const float *c_w, int S, int C, int B,
-                                 const int64_t *boff, long long rows, uint32_t *fine,
-                                 uint32_t *coarse, int32_t *q_value, int64_t *q_rank,
-                                 hipStream_t st)
+                                 const float *c_p, const float *c_w, int S, int C, const RowPlan &pl,
+                                 uint32_t *fine, uint32_t *coarse, int32_t *q_value,
+                                 int64_t *q_rank, hipStream_t st)
 {
-    hipLaunchKernelGGL(qhist_kernel, dim3((unsigned)std::min(rows, kMaxGridBlocks)), dim3(kQThreads),
-                       2 * kQStride * sizeof(uint32_t), st, offsets, xi, S, B, boff, rows, fine,
-                       coarse);
+    hipLaunchKernelGGL(qhist_kernel<false>, dim3((unsigned)std::min(pl.rows, kMaxGridBlocks)),
+                       dim3(kQThreads), 2 * kQStride * sizeof(uint32_t), st, offsets, xi, S, pl.B,
+                       pl.boff, pl.rows, fine, coarse, (uint32_t *)nullptr);
     HIPRET(hipGetLastError());
     hipLaunchKernelGGL(qselect_kernel, dim3((unsigned)std::min((long long)C, kMaxGridBlocks)),
-                       dim3(kQThreads), 0, st, offsets, seg, c_p, c_w, fine, coarse, B, boff, C,
-                       q_value, q_rank);
+                       dim3(kQThreads), 0, st, offsets, seg, c_p, c_w, fine, coarse, pl.B, pl.boff,
+                       C, q_value, q_rank);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------ block step ----
 // Grid indices arriving from the caller (k_prev) are clamped into [0, K).
 __device__ __forceinline__ int clampk(int k, int K) { return k < 0 ? 0 : (k >= K ? K - 1 : k); }
-
-// Alg. 1 initialisation r0 = L_in + E[xi]: per class, the exact integer sum of
-// the samples (block partial sums added atomically; integer addition makes the
-// result independent of the order), then the largest k with eta[k] N <= sum.
-__global__ __launch_bounds__(256) void class_sum_kernel(const int64_t *offsets, const int32_t *seg,
-                                                        const int32_t *xi, long long chunk,
-                                                        unsigned long long *sums)
-{
-    const int c = blockIdx.x, t = threadIdx.x;
-    const int s = seg_of_x(seg, c);
-    const long long n0 = offsets[s] + (long long)blockIdx.y * chunk;
-    const long long n1 = min(offsets[s + 1], n0 + chunk);
-    long long sum = 0;
-    for (long long n = n0 + t; n < n1; n += 256) sum += xi[n];
-    __shared__ long long sh[256];
-    sh[t] = sum;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) sh[t] += sh[t + w];
-        __syncthreads();
-    }
-    if (t == 0 && sh[0] != 0) atomicAdd(&sums[c], (unsigned long long)sh[0]);
-}
-
-__global__ void bcd_init_select_kernel(const int64_t *offsets, const int32_t *seg, const int32_t *eta,
-                                       int C, int K, const unsigned long long *sums, int32_t *k0)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    const int s = seg_of_x(seg, c);
-    const long long N = offsets[s + 1] - offsets[s];
-    const long long tot = (long long)sums[c];
-    int lo = 0, hi = K - 1;  // eta ascending: largest k with eta[k] * N <= tot (0 if none)
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if ((long long)eta[mid] * N <= tot) lo = mid;
-        else hi = mid - 1;
-    }
-    k0[c] = lo;
-}
-
-hipError_t launch_bcd_init(const int64_t *offsets, const int32_t *seg, const int32_t *xi,
-                           const int32_t *eta, int C, int K, long long max_n,
-                           unsigned long long *sums, int32_t *k0, hipStream_t st)
-{
-    const long long chunk = 1 << 16;
-    const long long nch = std::max(1LL, (max_n + chunk - 1) / chunk);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((2 * C + 255) / 256), dim3(256), 0, st,
-                       reinterpret_cast<uint32_t *>(sums), (long long)2 * C, 0u);
-    hipLaunchKernelGGL(class_sum_kernel, dim3(C, (unsigned)nch), dim3(256), 0, st, offsets, seg, xi,
-                       chunk, sums);
-    hipLaunchKernelGGL(bcd_init_select_kernel, dim3((C + 255) / 256), dim3(256), 0, st, offsets, seg,
-                       eta, C, K, (const unsigned long long *)sums, k0);
-    return hipGetLastError();
-}
 
 // Capacity bound of class c (the memory-capacity constraint of Sec. 3.4), then the largest admissible k.
 // The Gauss-Seidel sweep of the block step, one workgroup: for c = 0..C-1 in
@@ -824,8 +804,8 @@ __global__ __launch_bounds__(kPrefixThreads) void chunk_total_kernel(const uint3
 }
 
 __global__ __launch_bounds__(kPrefixThreads) void prefix_kernel(const uint32_t *hist,
-                                                                const uint64_t *tot, uint32_t *cnt,
-                                                                uint64_t *sum)
+                                                                const uint64_t *tot,
+                                                                PrefixEntry *pre)
 {
     __shared__ uint32_t hc[kPrefixChunk + kPrefixChunk / 32];
     __shared__ uint64_t rc[kPrefixThreads / 64], rs[kPrefixThreads / 64];
@@ -872,30 +852,167 @@ __global__ __launch_bounds__(kPrefixThreads) void prefix_kernel(const uint32_t *
         is += rs[w];
     }
     uint64_t c = base_c + ic - lc, x = base_s + is - ls;
-    uint32_t *gc = cnt + (long long)s * kHistBins + v0;
-    uint64_t *gs = sum + (long long)s * kHistBins + v0;
+    PrefixEntry *gp = pre + (long long)s * kHistBins + v0;
     for (int i = 0; i < kPrefixPer; ++i) {
         const int j = a + i;
         if (j < n) {
             const uint64_t hv = hc[pad32(j)];
             c += hv;
             x += hv * (uint64_t)(v0 + j);
-            gc[j] = (uint32_t)c;
-            gs[j] = x;
+            gp[j] = PrefixEntry::of((uint32_t)c, x);
         }
     }
 }
 
-hipError_t launch_prefix(const uint32_t *hist, int S, uint32_t *cnt, uint64_t *sum, hipStream_t st)
+// Prefix counts and sums straight from the per-block packed rows of
+// qhist_kernel<true>, in one pass and without a merged histogram.  Block
+// (segment s, chunk ch of 32): the 512 words ch * 512 .. of a row hold the
+// values 512 ch .. 512 ch + 511 in their low halves and the same plus 2^14 in
+// their high halves, so the block owns two runs of 512 values.  Wave g takes
+// the segment's rows g, g + 16, ...: four 16-byte loads a lane and row, the
+// chunk's counts and the row's coarse counts and sums (a run starts on a bucket,
+// so the totals before it are sums of whole buckets).  The waves' counts meet in
+// LDS; then thread t scans value t of the low run (t < 512) or t - 512 of the
+// high run and stores its entry, consecutive threads consecutive entries.  The
+// sums are scanned relative to the wave's first value: 63 * 2^26 fits 32 bits.
+// Bound by latency (a block's loads are one round trip for up to 16 rows).  On
+// 16 x 1e6 samples the rows and this pass take 14.0 + 9.2 us; the zero fill,
+// the merged histogram (2e6 global atomics), the chunk totals and the chunk
+// scans they replaced took 4.9 + 22.1 + 6.3 + 12.3 us.
+constexpr int kPreThreads = 1024;
+constexpr int kPreWaves = kPreThreads / 64;
+constexpr int kPreWords = kPreThreads / 2;         // packed words per chunk
+constexpr int kPreChunks = kQTop / 2 / kPreWords;  // 32 per segment
+
+__global__ __launch_bounds__(kPreThreads) void prefix_rows_kernel(const uint32_t *fine,
+                                                                  const uint32_t *coarse,
+                                                                  const uint32_t *csum,
+                                                                  const int64_t *offsets, int S,
+                                                                  int B0, const int64_t *boff,
+                                                                  PrefixEntry *pre)
 {
-    // chunk totals first (after the prefix sums in the same array), then each
-    // chunk's scan starts from the totals of the chunks before it
+    __shared__ __attribute__((aligned(16))) uint32_t part[kPreWaves][2 * kPreWords];
+    __shared__ uint32_t base_c[2][16], tot_c[16];  // before the low and the high run, by wave
+    __shared__ uint64_t base_s[2][16], tot_s[16];
+    static_assert(kPreWaves == 16 && kQBuckets == 4 * 64, "a row of 16 lanes per wave table");
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (long long u = blockIdx.x; u < (long long)S * kPreChunks; u += gridDim.x) {
+        const int s = (int)(u / kPreChunks), ch = (int)(u % kPreChunks);
+        const long long row0 = boff ? boff[s] : (long long)s * B0;
+        const int B = boff ? (int)(boff[s + 1] - row0) : B0;
+        const int parts = min(B, kPreWaves);
+        if (wave < parts) {
+            uint32_t lo[8] = {0, 0, 0, 0, 0, 0, 0, 0}, hi[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            uint32_t bc[4] = {0, 0, 0, 0};
+            uint64_t bs[4] = {0, 0, 0, 0};
+            auto add = [&](const uint4 &w, int o) {
+                lo[o] += w.x & 0xffffu;
+                lo[o + 1] += w.y & 0xffffu;
+                lo[o + 2] += w.z & 0xffffu;
+                lo[o + 3] += w.w & 0xffffu;
+                hi[o] += w.x >> 16;
+                hi[o + 1] += w.y >> 16;
+                hi[o + 2] += w.z >> 16;
+                hi[o + 3] += w.w >> 16;
+            };
+#pragma unroll 2
+            for (int r = wave; r < B; r += kPreWaves) {
+                const uint4 *f = reinterpret_cast<const uint4 *>(fine + (row0 + r) * kQStride) +
+                                 ch * (kPreWords / 4) + lane;
+                const long long cr = (row0 + r) * (kQBuckets / 4) + lane;
+                const uint4 a = f[0], b = f[64];
+                const uint4 c = reinterpret_cast<const uint4 *>(coarse)[cr];
+                const uint4 v = reinterpret_cast<const uint4 *>(csum)[cr];
+                add(a, 0);
+                add(b, 4);
+                bc[0] += c.x;
+                bc[1] += c.y;
+                bc[2] += c.z;
+                bc[3] += c.w;
+                bs[0] += v.x;
+                bs[1] += v.y;
+                bs[2] += v.z;
+                bs[3] += v.w;
+            }
+            uint4 *pw = reinterpret_cast<uint4 *>(part[wave]);
+            pw[lane] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            pw[64 + lane] = make_uint4(lo[4], lo[5], lo[6], lo[7]);
+            pw[kPreWords / 4 + lane] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            pw[kPreWords / 4 + 64 + lane] = make_uint4(hi[4], hi[5], hi[6], hi[7]);
+            // lane's buckets 4 lane .. 4 lane + 3; a run starts at a multiple of 4
+            // buckets: the low one after lane ch, the high one after lane 32 + ch
+            const uint32_t c4 = (bc[0] + bc[1]) + (bc[2] + bc[3]);
+            const uint64_t s4 = (bs[0] + bs[1]) + (bs[2] + bs[3]);
+            static_assert(kPreWords == 4 * 128, "four buckets per run");
+            // (the lanes are read outside the branch: every lane is active there)
+            const uint32_t cs = scan_wave(c4);
+            const uint64_t ss = scan_wave(s4);
+            const uint32_t c_hi = lane_value(cs, 31 + ch), c_lo = lane_value(cs, max(ch, 1) - 1);
+            const uint64_t s_hi = lane_value(ss, 31 + ch), s_lo = lane_value(ss, max(ch, 1) - 1);
+            if (lane == 0) {
+                base_c[0][wave] = ch ? c_lo : 0u;
+                base_s[0][wave] = ch ? s_lo : 0ull;
+                base_c[1][wave] = c_hi;
+                base_s[1][wave] = s_hi;
+            }
+        }
+        __syncthreads();
+        uint32_t c = 0;
+        for (int g = 0; g < parts; ++g) c += part[g][t];
+        const uint32_t cs = scan_wave(c), rs = scan_wave(c * (uint32_t)lane);
+        const int run = wave >> 3;
+        const int v = ch * kPreWords + (t & (kPreWords - 1)) + run * (kQTop / 2);
+        if (lane == 63) {
+            tot_c[wave] = cs;
+            tot_s[wave] = (uint64_t)cs * (uint32_t)(v - 63) + rs;
+        }
+        __syncthreads();
+        // before this wave: the totals before its run and those of the run's waves before it
+        uint32_t bc = 0;
+        uint64_t bs = 0;
+        if (lane < parts) {
+            bc = base_c[run][lane];
+            bs = base_s[run][lane];
+        }
+        if (lane < (wave & 7)) {
+            bc += tot_c[run * 8 + lane];
+            bs += tot_s[run * 8 + lane];
+        }
+        bc = lane_value(scan_row16(bc), 15) + cs;
+        bs = lane_value(scan_row16(bs), 15) + (uint64_t)cs * (uint32_t)(v - lane) + rs;
+        PrefixEntry *o = pre + (long long)s * kHistBins;
+        o[v] = PrefixEntry::of(bc, bs);
+        if (v == kQTop - 1) {  // the value 2^15 (one thread of the last chunk)
+            const uint64_t N = (uint64_t)(offsets[s + 1] - offsets[s]);
+            o[kQTop] = PrefixEntry::of((uint32_t)N, bs + (N - bc) * (uint64_t)kQTop);
+        }
+        __syncthreads();  // the next chunk reuses the LDS
+    }
+}
+
+hipError_t launch_counts(const int64_t *offsets, const int32_t *xi, int S, const CountBufs &b,
+                         hipStream_t st)
+{
+    if (!b.hist) {
+        hipLaunchKernelGGL(qhist_kernel<true>, dim3((unsigned)std::min(b.plan.rows, kMaxGridBlocks)),
+                           dim3(kQThreads), 2 * kQStride * sizeof(uint32_t), st, offsets, xi, S, b.plan.B,
+                           b.plan.boff, b.plan.rows, b.fine, b.coarse, b.csum);
+        HIPRET(hipGetLastError());
+        const long long units = (long long)S * kPreChunks;
+        hipLaunchKernelGGL(prefix_rows_kernel, dim3((unsigned)std::min(units, kMaxGridBlocks)),
+                           dim3(kPreThreads), 0, st, (const uint32_t *)b.fine,
+                           (const uint32_t *)b.coarse, (const uint32_t *)b.csum, offsets, S, b.plan.B,
+                           b.plan.boff, b.pre);
+        return hipGetLastError();
+    }
+    HIPRET(launch_histogram(offsets, xi, S, b.plan.B, b.hist, st));
+    // chunk totals first, then each chunk's scan starts from the totals of the
+    // chunks before it
     const long long blocks = (long long)S * kPrefixChunks;
-    uint64_t *tot = sum + (long long)S * kHistBins;
     hipLaunchKernelGGL(chunk_total_kernel, dim3((unsigned)blocks), dim3(kPrefixThreads), 0, st,
-                       hist, tot);
-    hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)blocks), dim3(kPrefixThreads), 0, st, hist,
-                       (const uint64_t *)tot, cnt, sum);
+                       (const uint32_t *)b.hist, b.tot);
+    hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)blocks), dim3(kPrefixThreads), 0, st,
+                       (const uint32_t *)b.hist, (const uint64_t *)b.tot, b.pre);
     return hipGetLastError();
 }
 
@@ -914,8 +1031,8 @@ constexpr int kTableChunk = 256;  // multipliers staged per wave at a time
 
 __global__ __launch_bounds__(64 * kTableWaves) void exact_table_kernel(
     const int64_t *offsets, const int32_t *seg, const int32_t *L_, const int32_t *eta_,
-    const float *lam, const float *c_p, const float *c_w, const float *eps, const uint32_t *cnt,
-    const uint64_t *sum, int E, int C, int K, int M, double *W, int32_t *m_star)
+    const float *lam, const float *c_p, const float *c_w, const float *eps,
+    const PrefixEntry *pre, int E, int C, int K, int M, double *W, int32_t *m_star)
 {
     __shared__ double2 stq[kTableWaves][kTableChunk];  // (q_m, lambda_m)
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -926,8 +1043,7 @@ __global__ __launch_bounds__(64 * kTableWaves) void exact_table_kernel(
         const int s = seg_of_x(seg, c);
         const int64_t N = offsets[s + 1] - offsets[s];
         const int64_t L = L_[c], eta = eta_[k];
-        const uint32_t *cn = cnt + (long long)s * kHistBins;
-        const uint64_t *sm = sum + (long long)s * kHistBins;
+        const PrefixEntry *pc = pre + (long long)s * kHistBins;
         const int64_t CP = fix33(c_p[c]), CW = fix33(c_w[c]);
         const double Nd = (double)N;
         int lg = 0;  // log2 of the groups
@@ -946,7 +1062,7 @@ __global__ __launch_bounds__(64 * kTableWaves) void exact_table_kernel(
                     __builtin_amdgcn_wave_barrier();  // the last chunk's reads come first
                     for (int i = lane; i < mc; i += 64) {
                         const float lm = lam[m0 + i];
-                        const unsigned __int128 u = exact_S_prefix(cn, sm, N, L, eta, CP, CW, fix33(lm));
+                        const unsigned __int128 u = exact_S_prefix(pc, N, L, eta, CP, CW, fix33(lm));
                         q[i] = make_double2(__ddiv_rn(fix128_to_double((uint64_t)u, (uint64_t)(u >> 64)), Nd),
                                             (double)lm);
                     }
@@ -1048,16 +1164,15 @@ hipError_t launch_table_argmin(const double *W, const int32_t *m_star, const int
 hipError_t launch_exact_table(const int64_t *offsets, const int32_t *seg, const int32_t *L,
                               const int32_t *eta, const float *lam, const float *c_p,
                               const float *c_w, const float *eps, const int32_t *k_max,
-                              const uint32_t *hist, int S, int E, int C, int K, int M,
-                              uint32_t *cnt, uint64_t *sum, double *W, int32_t *m_star,
-                              int32_t *k_star, double *W_star, int32_t *m_at_star, hipStream_t st)
+                              const PrefixEntry *pre, int E, int C, int K, int M, double *W,
+                              int32_t *m_star, int32_t *k_star, double *W_star, int32_t *m_at_star,
+                              hipStream_t st)
 {
-    HIPRET(launch_prefix(hist, S, cnt, sum, st));
     const long long rows = (long long)C * K;
     const long long blocks = std::min((rows + kTableWaves - 1) / kTableWaves, kMaxGridBlocks);
     hipLaunchKernelGGL(exact_table_kernel, dim3((unsigned)blocks),
                        dim3(64 * kTableWaves), 0, st, offsets, seg, L, eta, lam, c_p, c_w, eps,
-                       (const uint32_t *)cnt, (const uint64_t *)sum, E, C, K, M, W, m_star);
+                       pre, E, C, K, M, W, m_star);
     if (k_star) HIPRET(launch_table_argmin(W, m_star, k_max, E, C, K, k_star, W_star, m_at_star, st));
     return hipGetLastError();
 }
@@ -1134,8 +1249,7 @@ hipError_t launch_baselines(int C, const int64_t *count, const int64_t *sum, con
 // with J'(g+) >= 0, i.e. the smallest minimiser; J is evaluated there in fp64.
 
 struct SegStats {
-    const uint32_t *cnt;
-    const uint64_t *sum;
+    const PrefixEntry *pre;
     double N, SX;
     int tmax;
 };
@@ -1144,8 +1258,9 @@ __device__ __forceinline__ void side_stats(const SegStats &g, long long t, doubl
 {
     if (t < 0) { n = 0.0; s = 0.0; return; }
     if (t > g.tmax) t = g.tmax;
-    n = (double)g.cnt[t];
-    s = (double)g.sum[t];
+    const PrefixEntry e = g.pre[t];
+    n = (double)e.cnt;
+    s = (double)e.sum();
 }
 
 // value J(g) and right derivative J'(g+) for one (eta, L, costs, eps)
@@ -1184,8 +1299,8 @@ __device__ void dual_at(const SegStats &st, double B, double C, double L, double
 
 __global__ __launch_bounds__(256) void continuous_dual_kernel(
     const int64_t *offsets, const int32_t *seg, const int32_t *L_, const int32_t *eta_,
-    const float *c_p, const float *c_w, const float *eps, const uint32_t *cnt, const uint64_t *sum,
-    int E, int C, int K, double *W, double *gamma)
+    const float *c_p, const float *c_w, const float *eps, const PrefixEntry *pre, int E, int C,
+    int K, double *W, double *gamma)
 {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < (long long)E * C * K;
          i += (long long)gridDim.x * blockDim.x) {
@@ -1193,10 +1308,9 @@ __global__ __launch_bounds__(256) void continuous_dual_kernel(
         const int ec = (int)(i / K), c = ec % C, e = ec / C;
         const int s = seg_of_x(seg, c);
         SegStats st;
-        st.cnt = cnt + (long long)s * kHistBins;
-        st.sum = sum + (long long)s * kHistBins;
+        st.pre = pre + (long long)s * kHistBins;
         st.N = (double)(offsets[s + 1] - offsets[s]);
-        st.SX = (double)st.sum[kHistBins - 1];
+        st.SX = (double)st.pre[kHistBins - 1].sum();
         const int Li = L_[c];
         st.tmax = Li < kHistBins - 1 ? Li : kHistBins - 1;
         const double L = (double)Li, eta = (double)eta_[k];
@@ -1224,16 +1338,13 @@ __global__ __launch_bounds__(256) void continuous_dual_kernel(
 
 hipError_t launch_continuous_dual(const int64_t *offsets, const int32_t *seg, const int32_t *L,
                                   const int32_t *eta, const float *c_p, const float *c_w,
-                                  const float *eps, const uint32_t *hist, int S, int E, int C,
-                                  int K, uint32_t *cnt, uint64_t *sum, double *W, double *gamma,
-                                  hipStream_t st)
+                                  const float *eps, const PrefixEntry *pre, int E, int C, int K,
+                                  double *W, double *gamma, hipStream_t st)
 {
-    HIPRET(launch_prefix(hist, S, cnt, sum, st));
     const long long n = (long long)E * C * K;
     hipLaunchKernelGGL(continuous_dual_kernel, dim3((unsigned)std::min((n + 255) / 256, kMaxGridBlocks)),
                        dim3(256), 0, st,
-                       offsets, seg, L, eta, c_p, c_w, eps, (const uint32_t *)cnt,
-                       (const uint64_t *)sum, E, C, K, W, gamma);
+                       offsets, seg, L, eta, c_p, c_w, eps, pre, E, C, K, W, gamma);
     return hipGetLastError();
 }
 
@@ -1244,67 +1355,121 @@ namespace dro {
 // ===================================================== reservation cost ====
 // The stochastic cost of Sec. 3.3, Q(eta, x) = c_p (x - eta)^+ + c_w (eta - x)^+,
 // averaged over a class's samples for any given reservations, and the class
-// moments from which mean- and spread-based reservations are formed.  Both
-// read the value histogram: with cnt(v) = #{x <= v} and sum(v) the sum of
-// those samples, for an integer eta
+// moments from which mean- and spread-based reservations are formed.  With
+// cnt(v) = #{x <= v} and sum(v) the sum of those samples, for an integer eta
 //   sum_n Q(eta, x_n) = c_p ((SX - sum(eta)) - eta (N - cnt(eta)))
 //                     + c_w (eta cnt(eta) - sum(eta)),
 // evaluated in 128-bit integers in units of 2^-33: exact for every eta.
 
-// One block per class: count, sum, sum of squares and largest sample.
-__global__ __launch_bounds__(1024) void moments_kernel(const int32_t *seg, const uint32_t *hist,
-                                                       int64_t *count, int64_t *sum,
-                                                       int64_t *sumsq, int32_t *xmax)
+// Block for row r (segment s, part b, as the quantile's rows): the sum of its
+// samples, the same sum, the sum of squares and the largest with every sample
+// clamped to the histogram's values 0 .. 2^15 (equal for validated samples).
+constexpr int kMomThreads = 1024;
+
+__global__ __launch_bounds__(kMomThreads) void row_moments_kernel(const int64_t *offsets,
+                                                                  const int32_t *xi, int S, int B,
+                                                                  const int64_t *boff,
+                                                                  long long rows, RowMoments *out)
 {
-    const int c = blockIdx.x, t = threadIdx.x;
-    const uint32_t *h = hist + (long long)seg_of_x(seg, c) * kHistBins;
-    unsigned long long n = 0, a = 0, b = 0;
-    int mx = -1;
-    for (int v = t; v < kHistBins; v += 1024) {
-        const unsigned long long k = h[v];
-        n += k;
-        a += k * (unsigned long long)v;
-        b += k * (unsigned long long)v * (unsigned long long)v;
-        if (k) mx = v;  // ascending within a thread
-    }
-    __shared__ unsigned long long sn[1024], sa[1024], sb[1024];
-    __shared__ int sm[1024];
-    sn[t] = n;
-    sa[t] = a;
-    sb[t] = b;
-    sm[t] = mx;
-    __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
-        if (t < w) {
-            sn[t] += sn[t + w];
-            sa[t] += sa[t + w];
-            sb[t] += sb[t + w];
-            sm[t] = max(sm[t], sm[t + w]);
+    __shared__ RowMoments red[kMomThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (long long r = blockIdx.x; r < rows; r += gridDim.x) {
+        const RowPart rp = row_part(offsets, S, B, boff, r);
+        RowMoments m{0, 0, 0, 0};
+        for_each_sample<kMomThreads>(
+            xi, rp.lo, rp.hi,
+            [&](int x) {
+                m.raw += x;
+                const int v = x < 0 ? 0 : (x > kHistBins - 1 ? kHistBins - 1 : x);
+                m.sum += v;
+                m.sq += (unsigned long long)((uint32_t)v * (uint32_t)v);
+                m.mx = v > m.mx ? v : m.mx;
+            },
+            [] {});
+        for (int d = 32; d >= 1; d >>= 1) {
+            m.raw += __shfl_xor(m.raw, d, 64);
+            m.sum += __shfl_xor(m.sum, d, 64);
+            m.sq += __shfl_xor(m.sq, d, 64);
+            const long long o = __shfl_xor(m.mx, d, 64);
+            m.mx = o > m.mx ? o : m.mx;
         }
+        if (lane == 0) red[wave] = m;
         __syncthreads();
+        if (t == 0) {
+            for (int w = 1; w < kMomThreads / 64; ++w) {
+                m.raw += red[w].raw;
+                m.sum += red[w].sum;
+                m.sq += red[w].sq;
+                m.mx = red[w].mx > m.mx ? red[w].mx : m.mx;
+            }
+            out[r] = m;
+        }
+        __syncthreads();  // the next row reuses red
     }
-    if (t == 0) {
-        count[c] = (int64_t)sn[0];
-        sum[c] = (int64_t)sa[0];
-        sumsq[c] = (int64_t)sb[0];
-        xmax[c] = sm[0] < 0 ? 0 : sm[0];
+}
+
+// One wave per class: the rows of its segment combined.  count .. xmax are
+// written when count is given; k0, the largest k with eta[k] N <= the sum of
+// the samples (0 if none), when eta is.
+constexpr int kMomWaves = 4;  // classes per block
+
+__global__ __launch_bounds__(64 * kMomWaves) void class_moments_kernel(
+    const int64_t *offsets, const int32_t *seg, const RowMoments *rows, int B0,
+    const int64_t *boff, int C, int64_t *count, int64_t *sum, int64_t *sumsq, int32_t *xmax,
+    const int32_t *eta, int K, int32_t *k0)
+{
+    const int lane = threadIdx.x & 63;
+    const int c = blockIdx.x * kMomWaves + (threadIdx.x >> 6);
+    if (c >= C) return;  // whole waves
+    const int s = seg_of_x(seg, c);
+    const long long row0 = boff ? boff[s] : (long long)s * B0;
+    const int B = boff ? (int)(boff[s + 1] - row0) : B0;
+    RowMoments m{0, 0, 0, 0};
+    for (int r = lane; r < B; r += 64) {
+        const RowMoments x = rows[row0 + r];
+        m.raw += x.raw;
+        m.sum += x.sum;
+        m.sq += x.sq;
+        m.mx = x.mx > m.mx ? x.mx : m.mx;
+    }
+    for (int d = 32; d >= 1; d >>= 1) {
+        m.raw += __shfl_xor(m.raw, d, 64);
+        m.sum += __shfl_xor(m.sum, d, 64);
+        m.sq += __shfl_xor(m.sq, d, 64);
+        const long long o = __shfl_xor(m.mx, d, 64);
+        m.mx = o > m.mx ? o : m.mx;
+    }
+    if (lane != 0) return;
+    const long long N = offsets[s + 1] - offsets[s];
+    if (count) {
+        count[c] = N;
+        sum[c] = m.sum;
+        sumsq[c] = (int64_t)m.sq;
+        xmax[c] = (int32_t)m.mx;
+    }
+    if (eta) {
+        int lo = 0, hi = K - 1;  // eta ascending
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) / 2;
+            if ((long long)eta[mid] * N <= m.raw) lo = mid;
+            else hi = mid - 1;
+        }
+        k0[c] = lo;
     }
 }
 
 // Thread per (row r, class c): cost = RN(RN(S) / N) and cover = cnt(eta).
 __global__ __launch_bounds__(256) void reservation_cost_kernel(
     const int64_t *offsets, const int32_t *seg, const float *c_p, const float *c_w,
-    const uint32_t *cnt, const uint64_t *sum, int C, long long RC, const int32_t *eta_r,
-    double *cost, int64_t *cover)
+    const PrefixEntry *pre, int C, long long RC, const int32_t *eta_r, double *cost, int64_t *cover)
 {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= RC) return;
     const int c = (int)(i % C);
     const int s = seg_of_x(seg, c);
     const int64_t N = offsets[s + 1] - offsets[s];
-    const uint32_t *cn = cnt + (long long)s * kHistBins;
-    const uint64_t *sm = sum + (long long)s * kHistBins;
-    const __int128 SX = (__int128)sm[kHistBins - 1];
+    const PrefixEntry *pc = pre + (long long)s * kHistBins;
+    const __int128 SX = (__int128)pc[kHistBins - 1].sum();
     const int64_t eta = eta_r[i];
     int64_t nle;
     __int128 sle;
@@ -1315,8 +1480,9 @@ __global__ __launch_bounds__(256) void reservation_cost_kernel(
         nle = N;
         sle = SX;
     } else {
-        nle = (int64_t)cn[eta];
-        sle = (__int128)sm[eta];
+        const PrefixEntry e = pc[eta];
+        nle = (int64_t)e.cnt;
+        sle = (__int128)e.sum();
     }
     const __int128 CP = fix33(c_p[c]), CW = fix33(c_w[c]);
     const __int128 S = CP * ((SX - sle) - (__int128)eta * (__int128)(N - nle)) +
@@ -1326,24 +1492,28 @@ __global__ __launch_bounds__(256) void reservation_cost_kernel(
     cover[i] = nle;
 }
 
-hipError_t launch_moments(const int32_t *seg, const uint32_t *hist, int C, int64_t *count,
-                          int64_t *sum, int64_t *sumsq, int32_t *xmax, hipStream_t st)
+hipError_t launch_moments(const int64_t *offsets, const int32_t *seg, const int32_t *xi, int S,
+                          int C, const RowPlan &pl, RowMoments *rows, int64_t *count, int64_t *sum,
+                          int64_t *sumsq, int32_t *xmax, const int32_t *eta, int K, int32_t *k0,
+                          hipStream_t st)
 {
-    hipLaunchKernelGGL(moments_kernel, dim3(C), dim3(1024), 0, st, seg, hist, count, sum, sumsq,
-                       xmax);
+    hipLaunchKernelGGL(row_moments_kernel, dim3((unsigned)std::min(pl.rows, kMaxGridBlocks)),
+                       dim3(kMomThreads), 0, st, offsets, xi, S, pl.B, pl.boff, pl.rows, rows);
+    HIPRET(hipGetLastError());
+    hipLaunchKernelGGL(class_moments_kernel, dim3((unsigned)((C + kMomWaves - 1) / kMomWaves)),
+                       dim3(64 * kMomWaves), 0, st, offsets, seg, (const RowMoments *)rows, pl.B,
+                       pl.boff, C, count, sum, sumsq, xmax, eta, K, k0);
     return hipGetLastError();
 }
 
 hipError_t launch_reservation_cost(const int64_t *offsets, const int32_t *seg, const float *c_p,
-                                   const float *c_w, const uint32_t *hist, int S, int C, int R,
-                                   const int32_t *eta_r, uint32_t *cnt, uint64_t *sum,
-                                   double *cost, int64_t *cover, hipStream_t st)
+                                   const float *c_w, const PrefixEntry *pre, int C, int R,
+                                   const int32_t *eta_r, double *cost, int64_t *cover,
+                                   hipStream_t st)
 {
-    HIPRET(launch_prefix(hist, S, cnt, sum, st));
     const long long n = (long long)R * C;
     hipLaunchKernelGGL(reservation_cost_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       st, offsets, seg, c_p, c_w, (const uint32_t *)cnt, (const uint64_t *)sum,
-                       C, n, eta_r, cost, cover);
+                       st, offsets, seg, c_p, c_w, pre, C, n, eta_r, cost, cover);
     return hipGetLastError();
 }
 
