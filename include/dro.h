@@ -185,8 +185,8 @@ int class_quantile(dro_ctx *ctx, const dro_problem *p, int32_t *q_value, int64_t
 /* Exact table by value grouping and prefix sums.  For 0 <= x, eta <= L the three
  * candidates of Step 4 reduce to the larger of two lines in x, so with the
  * per-segment counts and sums of the sample values every S[c,k,m] is a closed
- * form in 128-bit integers: O(N + L) per segment plus O(1) per (c,k,m), instead
- * of O(N) per (c,k,m).  This is the production alternative to the dense
+ * form in 128-bit integers, and the dual is convex in the multiplier: O(N + L)
+ * per segment plus O(log M) per (e,c,k), instead of O(N) per (c,k,m).  This is the production alternative to the dense
  * evaluation when only the results are needed (it does not evaluate every
  * per-sample term, so it is not the dense throughput measurement):
  *   W[e,c,k], m_star[e,c,k] = exact-spec values (the expression of

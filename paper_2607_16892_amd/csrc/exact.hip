@@ -70,29 +70,49 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t x, int l)
         if (e_ != hipSuccess) return e_;             \
     } while (0)
 
-// Exact S of one (class, grid point, multiplier), in units of 2^-33, from the
-// prefix counts cnt(v) = #{x <= v} and sums sum(v) = sum{x : x <= v} of the
-// class's segment (N samples).  For 0 <= x, eta <= L the three candidates of
-// Step 4 reduce to the larger of two lines, B - a1 x and C - a2 (L - x) with
-// B = c_w eta, C = c_p (L - eta), a1 = min(g, c_w), a2 = min(g, c_p); the
-// first is the larger up to t = floor((B - C + a2 L) / (a1 + a2)), so
-//   S = B cnt(t) - a1 sum(t) + (C - a2 L)(N - cnt(t)) + a2 (sum_all - sum(t)),
-// every term an exact integer (the sum is non-negative, as phi is).
-__device__ __forceinline__ unsigned __int128 exact_S_prefix(const PrefixEntry *pre, int64_t N,
-                                                           int64_t L, int64_t eta, int64_t CP,
-                                                           int64_t CW, int64_t G)
+// One (class, grid point) of the exact table.  For 0 <= x, eta <= L the three
+// candidates of Step 4 reduce to the larger of two lines, B - a1 x and
+// C - a2 (L - x) with B = c_w eta, C = c_p (L - eta), a1 = min(g, c_w),
+// a2 = min(g, c_p); the first is the larger up to t = floor((B - C + a2 L) /
+// (a1 + a2)).  All integers in units of 2^-33.
+struct TableRow {
+    const PrefixEntry *pre;  // of the class's segment
+    int64_t B, C, CP, CW;
+    uint64_t SX;             // sum of the samples
+    uint32_t N;
+    int L, tmax;
+};
+
+__device__ __forceinline__ PrefixEntry row_split(const TableRow &r, int64_t A1, int64_t A2)
 {
-    const int64_t B = CW * eta, Cc = CP * (L - eta);
-    const int64_t A1 = G < CW ? G : CW, A2 = G < CP ? G : CP;
-    const int64_t tmax = L < kHistBins - 1 ? L : kHistBins - 1;
-    int64_t tt = floor_div(B - Cc + A2 * L, A1 + A2);
-    tt = tt < -1 ? -1 : (tt > tmax ? tmax : tt);
-    const __int128 ct = tt >= 0 ? (__int128)pre[tt].cnt : 0;
-    const __int128 st = tt >= 0 ? (__int128)pre[tt].sum() : 0;
-    const __int128 sum_all = (__int128)pre[kHistBins - 1].sum();
-    const __int128 S = (__int128)B * ct - (__int128)A1 * st + (__int128)(Cc - A2 * L) * ((__int128)N - ct) +
-                       (__int128)A2 * (sum_all - st);
-    return (unsigned __int128)S;
+    const int t = floor_div_clamped(r.B - r.C + A2 * r.L, A1 + A2, -1, r.tmax);
+    const PrefixEntry e = r.pre[max(t, 0)];
+    return t >= 0 ? e : PrefixEntry::of(0u, 0ull);
+}
+
+// S at multiplier G: with cnt and sum over the samples <= t,
+//   S = B cnt - a1 sum + (C - a2 L)(N - cnt) + a2 (sum_all - sum),
+// every term an exact integer (the sum is non-negative, as phi is).
+__device__ __forceinline__ double row_S(const TableRow &r, int64_t G)
+{
+    const int64_t A1 = G < r.CW ? G : r.CW, A2 = G < r.CP ? G : r.CP;
+    const PrefixEntry e = row_split(r, A1, A2);
+    const __int128 S = mul_i64_u31(r.B, e.cnt) + mul_i64_u31(r.C - A2 * r.L, r.N - e.cnt) +
+                       mul_u43((uint64_t)A2, r.SX) - mul_u43((uint64_t)(A1 + A2), e.sum());
+    return fix128_to_double((uint64_t)S, (uint64_t)((unsigned __int128)S >> 64));
+}
+
+// N times a subgradient of gamma -> gamma eps + S(gamma) / N at multiplier G:
+// eN = RN(eps N) less the slopes of the active lines, an exact integer below
+// 2^42 (a sample where the lines meet may take either line's slope).
+__device__ __forceinline__ double row_slope(const TableRow &r, int64_t G, double eN)
+{
+    const int64_t A1 = G < r.CW ? G : r.CW, A2 = G < r.CP ? G : r.CP;
+    const PrefixEntry e = row_split(r, A1, A2);
+    const int64_t below = G < r.CW ? (int64_t)e.sum() : 0;
+    const int64_t above =
+        G < r.CP ? (int64_t)(r.N - e.cnt) * r.L - (int64_t)(r.SX - e.sum()) : 0;
+    return eN - (double)(below + above);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, long long n, uint32_t v)
@@ -1016,88 +1036,139 @@ hipError_t launch_counts(const int64_t *offsets, const int32_t *xi, int S, const
     return hipGetLastError();
 }
 
-// One wave per (c, k) row, as the minimum over the multipliers of the dense
-// path: the wave computes each multiplier's exact S from the segment's prefix
-// counts and sums once and stages q_m = RN(S / N) with lambda_m in LDS, a
-// chunk of multipliers at a time; then its 64 lanes split into g groups of
-// 64/g, g the power of two covering E (at most 64), group j taking radius
-// e0 + j and its lanes the multipliers m = part, part + 64/g, ... of the
-// chunk.  Each lane keeps the smallest J of its multipliers (the lowest m among
-// equal values, as it visits them in ascending order), and log2(64/g) shuffle
-// steps take the group's smallest J, ties to the lowest m (W, m_star): the
-// same values and the same lowest m as a scan over m.
-constexpr int kTableWaves = 4;    // waves (rows) per block
-constexpr int kTableChunk = 256;  // multipliers staged per wave at a time
+// One thread per (e, c, k): W = min over m of J_m = RN(RN(lam_m eps) +
+// RN(RN(S_m) / N)) and the lowest m attaining it, without evaluating every m.
+// J without its roundings, j(gamma) = gamma eps + S(gamma) / N, is convex (Step 4
+// is a supremum of lines in gamma), so a binary search on the sign of its
+// subgradient at the grid's multipliers finds the first m = b where it is not
+// negative; the smallest j on the grid is at b or at a = b - 1.  J_a and J_b are
+// evaluated exactly.  Any other m is ruled out by convexity: left of a, j is at
+// least j_a + |slope_a| (lam_a - lam_(a-1)), right of b at least j_b + slope_b
+// (lam_(b+1) - lam_b); three roundings move J by less than 4 * 2^-53 of j, so a
+// rise above 2^-44 of J settles it (and the slope itself must exceed its own
+// rounding, 2^-50 eps N).  At eps = 0 the slope right of b is exactly zero and S
+// the same integer, so J ties and b is the lower index.  Where the rise is too
+// small the neighbours are evaluated, one after the other, until it is not: the
+// same W and the same lowest m as a scan over all m.
+// About 9 subgradients and 2 values of S instead of M = 256 values: 16 x 2048
+// grid points of 1e6 samples 83 -> 10 us, 128 classes x 1024 points x 16 radii
+// 248 -> 83 us (M = 128).  Few rows are bound by the search's chain of dependent
+// instructions and loads, many by the integer arithmetic (three subgradients in
+// flight per step, on quarters of the range, took 12.7 us for the 10.2).
+// The multipliers are staged in LDS; a grid that is not ascending (outside the
+// contract) is scanned.
+constexpr int kTableThreads = 128;
+constexpr int kTableLam = 2048;  // multipliers staged per block
 
-__global__ __launch_bounds__(64 * kTableWaves) void exact_table_kernel(
+__global__ __launch_bounds__(kTableThreads) void exact_table_kernel(
     const int64_t *offsets, const int32_t *seg, const int32_t *L_, const int32_t *eta_,
     const float *lam, const float *c_p, const float *c_w, const float *eps,
-    const PrefixEntry *pre, int E, int C, int K, int M, double *W, int32_t *m_star)
+    const PrefixEntry *pre, long long rows, int C, int K, int M, double *W, int32_t *m_star)
 {
-    __shared__ double2 stq[kTableWaves][kTableChunk];  // (q_m, lambda_m)
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // rows in a grid-stride loop of whole waves (no block barrier below)
-    for (long long ck = (long long)blockIdx.x * kTableWaves + wv; ck < (long long)C * K;
-         ck += (long long)gridDim.x * kTableWaves) {
-        const int c = (int)(ck / K), k = (int)(ck % K);
+    __shared__ float s_lam[kTableLam];
+    bool up = true;
+    for (int m = threadIdx.x; m < M; m += kTableThreads) {
+        const float l = lam[m];
+        if (m < kTableLam) s_lam[m] = l;
+        if (m > 0 && !(l > lam[m - 1])) up = false;
+    }
+    const bool ascending = __syncthreads_and(up);
+    auto lam_at = [&](int m) { return m < kTableLam ? s_lam[m] : lam[m]; };
+    for (long long i = (long long)blockIdx.x * kTableThreads + threadIdx.x; i < rows;
+         i += (long long)gridDim.x * kTableThreads) {
+        const int k = (int)(i % K);
+        const long long ec = i / K;
+        const int c = (int)(ec % C);
         const int s = seg_of_x(seg, c);
-        const int64_t N = offsets[s + 1] - offsets[s];
-        const int64_t L = L_[c], eta = eta_[k];
-        const PrefixEntry *pc = pre + (long long)s * kHistBins;
-        const int64_t CP = fix33(c_p[c]), CW = fix33(c_w[c]);
-        const double Nd = (double)N;
-        int lg = 0;  // log2 of the groups
-        while (lg < 6 && (1 << lg) < E) ++lg;
-        const int lp = 6 - lg;  // log2 of the lanes per group
-        const int part = lane & ((1 << lp) - 1), grp = lane >> lp;
-        double2 *q = stq[wv];
-        for (int e0 = 0; e0 < E; e0 += 1 << lg) {
-            const int e = e0 + grp;
-            const double ev = e < E ? (double)eps[(long long)e * C + c] : 0.0;
-            double best = __builtin_inf();
-            int bm = M;  // no multiplier yet: loses every comparison below
-            for (int m0 = 0; m0 < M; m0 += kTableChunk) {
-                const int mc = min(kTableChunk, M - m0);
-                if (e0 == 0 || M > kTableChunk) {  // else the one chunk is still staged
-                    __builtin_amdgcn_wave_barrier();  // the last chunk's reads come first
-                    for (int i = lane; i < mc; i += 64) {
-                        const float lm = lam[m0 + i];
-                        const unsigned __int128 u = exact_S_prefix(pc, N, L, eta, CP, CW, fix33(lm));
-                        q[i] = make_double2(__ddiv_rn(fix128_to_double((uint64_t)u, (uint64_t)(u >> 64)), Nd),
-                                            (double)lm);
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                }
-                for (int i = part; i < mc; i += 1 << lp) {
-                    const double2 v = q[i];
-                    const double J = __dadd_rn(__dmul_rn(v.y, ev), v.x);
-                    if (J < best) {
-                        best = J;
-                        bm = m0 + i;
-                    }
-                }
-            }
-            for (int d = (1 << lp) >> 1; d >= 1; d >>= 1) {
-                const double ob = __shfl_xor(best, d, 64);
-                const int om = __shfl_xor(bm, d, 64);
-                if (ob < best || (ob == best && om < bm)) {
-                    best = ob;
-                    bm = om;
+        TableRow r;
+        r.pre = pre + (long long)s * kHistBins;
+        r.SX = r.pre[kHistBins - 1].sum();
+        r.N = (uint32_t)(offsets[s + 1] - offsets[s]);
+        r.L = L_[c];
+        r.tmax = min(r.L, kHistBins - 1);
+        r.CP = fix33(c_p[c]);
+        r.CW = fix33(c_w[c]);
+        const int64_t eta = eta_[k];
+        r.B = r.CW * eta;
+        r.C = r.CP * (r.L - eta);
+        const double ev = (double)eps[ec], Nd = (double)r.N, eN = __dmul_rn(ev, Nd);
+        auto slope = [&](int m) { return row_slope(r, fix33(lam_at(m)), eN); };
+        auto value = [&](int m) {
+            const float l = lam_at(m);
+            return __dadd_rn(__dmul_rn((double)l, ev), __ddiv_rn(row_S(r, fix33(l)), Nd));
+        };
+        // m and all beyond it are settled: the rise over the gap to the next
+        // multiplier, of slope h at a point of value J
+        auto clear = [&](double h, double J, int m0) {
+            const double gap = (double)lam_at(m0 + 1) - (double)lam_at(m0);
+            return h * gap > Nd * fabs(J) * 0x1p-44 && h > fabs(eN) * 0x1p-50;
+        };
+        double best = __builtin_inf();
+        int bm = M;
+        if (ascending) {
+            int a = -1, b = M;  // the slope is negative at a, not at b
+            double ha = 0.0, hb = 0.0;
+            while (b - a > 1) {
+                const int mid = (a + b) >> 1;
+                const double h = slope(mid);
+                if (h < 0.0) {
+                    a = mid;
+                    ha = h;
+                } else {
+                    b = mid;
+                    hb = h;
                 }
             }
-            if (part == 0 && e < E) {
-                const long long o = ((long long)e * C + c) * K + k;
-                W[o] = best;
-                m_star[o] = bm;
+            double Ja = 0.0, Jb = 0.0;
+            if (b < M) {
+                best = Jb = value(b);
+                bm = b;
+            }
+            if (a >= 0) {
+                Ja = value(a);
+                if (Ja <= best) {
+                    best = Ja;
+                    bm = a;
+                }
+            }
+            while (a > 0 && !clear(-ha, Ja, a - 1)) {
+                --a;
+                ha = slope(a);
+                Ja = value(a);
+                if (Ja <= best) {
+                    best = Ja;
+                    bm = a;
+                }
+            }
+            while (b < M - 1 && ev != 0.0 && !clear(hb, Jb, b)) {
+                ++b;
+                hb = slope(b);
+                Jb = value(b);
+                if (Jb < best) {
+                    best = Jb;
+                    bm = b;
+                }
+            }
+        } else {
+            for (int m = 0; m < M; ++m) {
+                const double J = value(m);
+                if (J < best) {
+                    best = J;
+                    bm = m;
+                }
             }
         }
+        W[i] = best;
+        m_star[i] = bm;
     }
 }
 
 // Block per (e, c): lowest k <= kmax with the smallest W, and the values there
-// (the exact optimum over a W table whose entries are exact-spec values).
+// (the exact optimum over a W table whose entries are exact-spec values).  Bound
+// by latency: each thread loads four values at a time, then shuffles within the
+// waves and one pass over their results.
+constexpr int kArgThreads = 256;
+
 __device__ void table_argmin_row(const double *W, const int32_t *m_star, const int32_t *k_max,
                                 int C, int K, int ec, int32_t *k_star, double *W_star,
                                 int32_t *m_at_star)
@@ -1111,39 +1182,50 @@ __device__ void table_argmin_row(const double *W, const int32_t *m_star, const i
     const double *w = W + (long long)ec * K;
     double bw = __builtin_inf();
     int bk = 0x7fffffff;
-    for (int k = t; k <= kmax; k += 256)
-        if (w[k] < bw) {
-            bw = w[k];
-            bk = k;
-        }
-    __shared__ double sw[256];
-    __shared__ int sk[256];
-    sw[t] = bw;
-    sk[t] = bk;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (t < s) {
-            const double w2 = sw[t + s];
-            const int k2 = sk[t + s];
-            if (w2 < sw[t] || (w2 == sw[t] && k2 < sk[t])) {
-                sw[t] = w2;
-                sk[t] = k2;
+    for (int k0 = t; k0 <= kmax; k0 += 4 * kArgThreads) {
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = w[min(k0 + q * kArgThreads, kmax)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = k0 + q * kArgThreads;
+            if (k <= kmax && v[q] < bw) {
+                bw = v[q];
+                bk = k;
             }
         }
-        __syncthreads();
     }
+    for (int d = 32; d >= 1; d >>= 1) {
+        const double w2 = __shfl_xor(bw, d, 64);
+        const int k2 = __shfl_xor(bk, d, 64);
+        if (w2 < bw || (w2 == bw && k2 < bk)) {
+            bw = w2;
+            bk = k2;
+        }
+    }
+    __shared__ double sw[kArgThreads / 64];
+    __shared__ int sk[kArgThreads / 64];
+    if ((t & 63) == 0) {
+        sw[t >> 6] = bw;
+        sk[t >> 6] = bk;
+    }
+    __syncthreads();
     if (t == 0) {
-        k_star[ec] = sk[0];
-        W_star[ec] = sw[0];
-        if (m_at_star) m_at_star[ec] = m_star[(long long)ec * K + sk[0]];
+        for (int i = 1; i < kArgThreads / 64; ++i)
+            if (sw[i] < bw || (sw[i] == bw && sk[i] < bk)) {
+                bw = sw[i];
+                bk = sk[i];
+            }
+        k_star[ec] = bk;
+        W_star[ec] = bw;
+        if (m_at_star) m_at_star[ec] = m_star[(long long)ec * K + bk];
     }
 }
 
 // rows (e, c) in a block-uniform loop; the barrier lets the next row reuse the LDS
-__global__ __launch_bounds__(256) void table_argmin_kernel(const double *W, const int32_t *m_star,
-                                                           const int32_t *k_max, int C, int K,
-                                                           int rows, int32_t *k_star, double *W_star,
-                                                           int32_t *m_at_star)
+__global__ __launch_bounds__(kArgThreads) void table_argmin_kernel(
+    const double *W, const int32_t *m_star, const int32_t *k_max, int C, int K, int rows,
+    int32_t *k_star, double *W_star, int32_t *m_at_star)
 {
     for (int ec = blockIdx.x; ec < rows; ec += gridDim.x) {
         table_argmin_row(W, m_star, k_max, C, K, ec, k_star, W_star, m_at_star);
@@ -1156,8 +1238,8 @@ hipError_t launch_table_argmin(const double *W, const int32_t *m_star, const int
                                int32_t *m_at_star, hipStream_t st)
 {
     const long long rows = (long long)E * C;  // below 2^31: checked by the entry points
-    hipLaunchKernelGGL(table_argmin_kernel, dim3((unsigned)std::min(rows, kMaxGridBlocks)), dim3(256),
-                       0, st, W, m_star, k_max, C, K, (int)rows, k_star, W_star, m_at_star);
+    hipLaunchKernelGGL(table_argmin_kernel, dim3((unsigned)std::min(rows, kMaxGridBlocks)),
+                       dim3(kArgThreads), 0, st, W, m_star, k_max, C, K, (int)rows, k_star, W_star, m_at_star);
     return hipGetLastError();
 }
 
@@ -1168,11 +1250,11 @@ hipError_t launch_exact_table(const int64_t *offsets, const int32_t *seg, const 
                               int32_t *m_star, int32_t *k_star, double *W_star, int32_t *m_at_star,
                               hipStream_t st)
 {
-    const long long rows = (long long)C * K;
-    const long long blocks = std::min((rows + kTableWaves - 1) / kTableWaves, kMaxGridBlocks);
-    hipLaunchKernelGGL(exact_table_kernel, dim3((unsigned)blocks),
-                       dim3(64 * kTableWaves), 0, st, offsets, seg, L, eta, lam, c_p, c_w, eps,
-                       pre, E, C, K, M, W, m_star);
+    const long long rows = (long long)E * C * K;
+    const long long blocks = std::min((rows + kTableThreads - 1) / kTableThreads, kMaxGridBlocks);
+    hipLaunchKernelGGL(exact_table_kernel, dim3((unsigned)blocks), dim3(kTableThreads), 0, st, offsets, seg, L,
+                       eta, lam, c_p, c_w, eps, pre, rows, C, K, M, W, m_star);
+    HIPRET(hipGetLastError());
     if (k_star) HIPRET(launch_table_argmin(W, m_star, k_max, E, C, K, k_star, W_star, m_at_star, st));
     return hipGetLastError();
 }

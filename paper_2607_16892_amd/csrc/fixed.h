@@ -31,25 +31,50 @@ __device__ __forceinline__ int64_t floor_div(int64_t a, int64_t b)
     return q;
 }
 
-// Correctly rounded double of the unsigned 128-bit value (hi, lo) times 2^-33.
-__device__ inline double fix128_to_double(uint64_t lo, uint64_t hi)
+// floor(a / b) clamped to [lo, hi] for b > 0 and -2 <= lo <= hi < 2^16: the
+// quotient by the reciprocal instruction (about 2^-26 relative, so within one of
+// the floor after the clamp) corrected once with the exact remainder.
+__device__ __forceinline__ int floor_div_clamped(int64_t a, int64_t b, int lo, int hi)
 {
-    int nb;
-    if (hi) nb = 128 - __clzll((long long)hi);
-    else if (lo) nb = 64 - __clzll((long long)lo);
-    else return 0.0;
-    if (nb <= 53) return ldexp((double)(long long)lo, -33);
-    const int sh = nb - 53;
-    const unsigned __int128 v = ((unsigned __int128)hi << 64) | (unsigned __int128)lo;
-    uint64_t mant = (uint64_t)(v >> sh);
-    const unsigned __int128 rem = v & ((((unsigned __int128)1) << sh) - 1);
-    const unsigned __int128 half = ((unsigned __int128)1) << (sh - 1);
-    if (rem > half || (rem == half && (mant & 1u))) mant += 1;
-    return ldexp((double)(long long)mant, sh - 33);
+    const double q = (double)a * __builtin_amdgcn_rcp((double)b);
+    int t = (int)floor(fmin(fmax(q, (double)lo), (double)hi));
+    const int64_t r = a - b * t;
+    t += r < 0 ? -1 : (r >= b ? 1 : 0);
+    return t < lo ? lo : (t > hi ? hi : t);
+}
+
+// a * b for a of 64 bits and b < 2^31, and for a, b < 2^43, exactly: two and
+// four 32-bit multiply-adds where the general 128-bit product takes ten.
+__device__ __forceinline__ __int128 mul_i64_u31(int64_t a, uint32_t b)
+{
+    const uint64_t l = (uint64_t)(uint32_t)a * b;
+    const int64_t h = (int64_t)(int32_t)(a >> 32) * (int64_t)(int32_t)b;
+    return (__int128)(((unsigned __int128)(__int128)h << 32) + l);
+}
+
+__device__ __forceinline__ __int128 mul_u43(uint64_t a, uint64_t b)
+{
+    const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b,
+                   bh = (uint32_t)(b >> 32);
+    const uint64_t mid = (uint64_t)ah * bl + (uint64_t)al * bh;  // below 2^44
+    return (__int128)(((unsigned __int128)((uint64_t)(ah * bh)) << 64) +
+                      ((unsigned __int128)mid << 32) + (uint64_t)al * bl);
+}
+
+// Correctly rounded double of the unsigned 128-bit value (hi, lo) times 2^-33.
+// The top 64 bits below the leading zeros, with a bit for the rest in the last
+// place, round to 53 bits as the whole value does.
+__device__ __forceinline__ double fix128_to_double(uint64_t lo, uint64_t hi)
+{
+    const int s = hi ? __clzll((long long)hi) : 0;
+    const unsigned __int128 v = (((unsigned __int128)hi << 64) | lo) << s;
+    const uint64_t rest = (uint64_t)v;
+    const uint64_t top = hi ? (uint64_t)(v >> 64) | (rest ? 1u : 0u) : lo;
+    return ldexp((double)top, hi ? 64 - s - 33 : -33);
 }
 
 // Correctly rounded double of a signed 128-bit value times 2^-33.
-__device__ inline double sfix128_to_double(__int128 v)
+__device__ __forceinline__ double sfix128_to_double(__int128 v)
 {
     const bool neg = v < 0;
     const unsigned __int128 u = neg ? (unsigned __int128)(-v) : (unsigned __int128)v;
