@@ -54,11 +54,11 @@ PAPER_FLOPS_PER_EVAL = 7                 # 2 multiply-adds (4), a 3-way max (2),
 # stripped, identified by the hash prefix) and are reported as null for any
 # other code or workload.
 DENSE_COUNTERS = {
-    "dense_code_sha256_16": "2d58a6d03fe9d642",
+    "dense_code_sha256_16": "a02407c483815aeb",
     "workload": "mixture-16x1M",
     "valu_instr_per_eval": 0.50312,    # SQ_INSTS_VALU x 64 / evaluations
-    "clock_ghz": 2.371,                # GRBM_GUI_ACTIVE / 8 XCDs / duration
-    "hbm_bytes_per_launch": 222985011,  # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated)
+    "clock_ghz": 2.383,                # GRBM_GUI_ACTIVE / 8 XCDs / duration
+    "hbm_bytes_per_launch": 222573824,  # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated)
     "source": "profiles/dense_kernel_mixture-16x1M_counters.md",
 }
 
@@ -82,9 +82,8 @@ def dense_code_hash() -> str:
     consts = [ln for ln in hdr[:i].splitlines() if "constexpr" in ln]
     api = code("api.hip")
     plan_consts = [ln for ln in api.splitlines()
-                   if any(f"constexpr long long {k} " in ln for k in ("kDirectSampleTiles", "kSlicesPerBlock",
-                                                                      "kMaxSliceN", "kBalanceSliceN",
-                                                                      "kMinSliceN", "kMaxDirectSlices"))]
+                   if any(f"constexpr long long {k} " in ln for k in ("kSlicesPerBlock", "kMaxSliceN",
+                                                                      "kBalanceSliceN", "kMinSliceN"))]
     i = api.index("DensePlan plan_dense(")
     plan = api[i:api.index("return pl;", i)]
     dense = code("dense.hip")

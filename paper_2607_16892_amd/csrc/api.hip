@@ -11,6 +11,9 @@
 
 #include "dro_internal.h"
 
+// Sizes of the classes' segments and how many classes have each.
+using SizeCounts = std::vector<std::pair<long long, long long>>;
+
 struct dro_ctx {
     int device = 0;
     int num_cu = 256;
@@ -28,6 +31,10 @@ struct dro_ctx {
     std::vector<int64_t> staged_off;
     std::vector<int32_t> staged_seg;
     dro::RowPlan staged_rows{};  // parts of the staged segments; boff points into `stage`
+    SizeCounts staged_sizes;     // the staged classes' segment sizes
+    // the dense plan last made for the staged problem, and its grid (K = 0: none)
+    int plan_K = 0, plan_M = 0;
+    dro::DensePlan plan{};
     char err[1024] = {0};
     // host staging of the configuration-space count table (kept alive until
     // the next configuration search on this context has been enqueued)
@@ -184,9 +191,8 @@ int check_problem(dro_ctx *ctx, const dro_problem *p, Shape *sh)
     return DRO_OK;
 }
 
-// Tiles of kTM pairs per lane; each tile's samples are split into P slices.
-// A problem with at least kDirectSampleTiles (tile, sample) terms per resident
-// block runs the persistent grid that claims slices (see dense.hip).  There P
+// Large problems run the persistent grid that claims slices (see dense.hip):
+// tiles of kTM pairs per lane, each tile's samples split into P slices.  P
 // is the largest of three needs: slices of at most kMaxSliceN samples, so that
 // the last ones are short; about kSlicesPerBlock slices per resident block, so
 // that the issue priorities keep the blocks of a compute unit in step and the
@@ -196,22 +202,35 @@ int check_problem(dro_ctx *ctx, const dro_problem *p, Shape *sh)
 // 1024 resident blocks): P = 16 (62,500-sample slices) ran 0.3 % faster than
 // the launch of 20,480 short blocks it replaced, P = 31 0.2 % slower and
 // P = 8 2.5 % slower.
-// A smaller problem (of at most 2^22 blocks) runs one block per slice instead
-// (direct mode): a run's set-up (its thresholds, claims, the search for work)
-// is then not small beside its work.  P is the smallest whose grid fills its
-// last wave of resident blocks to at least 97 %, else the best-filled P
-// (P <= 64, slices of at least kMinSliceN samples): on 4 x 1e5 samples
-// (K = 512, M = 128) one full wave of blocks (P = 32) ran 3 % faster than two
-// (P = 64) and 22 % faster than four.
+// Others run one block per slice instead (dense_slices_kernel): a run's set-up
+// (its thresholds, claims, the search for work) is then not small beside its
+// work.  plan_slices picks its tile shape and slice length, plan_dense between
+// the two.
 // The kernels index with the host-validated offsets and segment map: both are
 // copied into the workspace at the start of every call, so device data that
 // disagrees with the host copies can never steer a kernel outside xi.
-constexpr long long kDirectSampleTiles = 65536;
 constexpr long long kSlicesPerBlock = 16;
 constexpr long long kMaxSliceN = 65536;
 constexpr long long kBalanceSliceN = 512;
 constexpr long long kMinSliceN = 64;
-constexpr long long kMaxDirectSlices = 64;
+
+// The distinct sizes of the classes' segments and how many classes have each.
+SizeCounts class_sizes(const dro_problem *p)
+{
+    SizeCounts v(p->S);
+    for (int s = 0; s < p->S; ++s) v[s] = {p->offsets_h[s + 1] - p->offsets_h[s], p->seg_h ? 0 : 1};
+    if (p->seg_h)
+        for (int c = 0; c < p->C; ++c) ++v[p->seg_h[c]].second;
+    std::sort(v.begin(), v.end());
+    size_t n = 0;
+    for (size_t i = 0; i < v.size(); ++i) {
+        if (!v[i].second) continue;
+        if (n && v[n - 1].first == v[i].first) v[n - 1].second += v[i].second;
+        else v[n++] = v[i];
+    }
+    v.resize(n);
+    return v;
+}
 
 size_t stage_bytes(const dro_problem *p)
 {
@@ -284,6 +303,8 @@ int stage_problem(dro_ctx *ctx, const dro_problem *p, hipStream_t st, dro_proble
             pl.boff = boff;
         }
         ctx->staged_rows = pl;
+        ctx->staged_sizes = class_sizes(p);
+        ctx->plan_K = 0;
         ctx->staged_off.assign(p->offsets_h, p->offsets_h + p->S + 1);
         if (p->seg_h) ctx->staged_seg.assign(p->seg_h, p->seg_h + p->C);
         else ctx->staged_seg.clear();
@@ -318,37 +339,88 @@ int stage_in_arena(dro_ctx *ctx, const dro_problem *p, Arena &ar, bool packed, h
     return DRO_OK;
 }
 
-DensePlan plan_dense(int C, int K, int M, long long max_n, int num_cu, int bpc)
+// Tile shape and slice length of dense_slices_kernel by a model of its time in
+// cycles of a compute unit: w passes of the chip's resident blocks (one of 1,024
+// threads per compute unit), each as long as a slice's v_sad_u16 (4 waves a SIMD,
+// 4 cycles each; kLoop more per step of sixteen samples for its loads, claims and
+// branch) and a block's set-up, which grows with its pairs (the first samples,
+// thresholds, LDS sums, flush: 31 us for 8,192 pairs from slices of 12,500 and
+// 14,286 samples, 5 us for 512).  For every shape and w the shortest slices whose
+// blocks fit w passes; a sum split over slices also pays the zero fill of the
+// table.
+constexpr int kMaxDirectSlice = 65536;
+constexpr double kLoop = 8.0, kBlockCycles = 12000.0, kPairCycles = 7.0, kZeroCycles = 6000.0;
+
+double plan_slices(const SizeCounts &sizes, int K, int M, int num_cu, DensePlan *best)
 {
+    const long long KM = (long long)K * M;
+    double total = 0.0, best_cost = -1.0;
+    for (const auto &z : sizes) total += (double)z.first * z.second;
+    for (int sh = 0; sh < kSliceShapes; ++sh) {
+        const int TM = kSliceTM[sh], GL = kSliceGL[sh], NG = 1024 / GL;
+        const long long tiles = (KM + (long long)TM * GL - 1) / ((long long)TM * GL);
+        const double per_sample = (8 * TM + kLoop) / NG;
+        const double per_block = kBlockCycles + kPairCycles * TM * GL;
+        double least = 0.0;  // blocks of the longest slices
+        for (const auto &z : sizes)
+            least += (double)tiles * slices_of(z.first, kMaxDirectSlice) * z.second;
+        if (least > (1LL << 22)) continue;
+        const int w0 = std::max(1, (int)std::ceil(least / num_cu));
+        for (int i = 0; i < 12; ++i) {
+            const int w = i < 8 ? w0 + i : w0 + 7 + 4 * (i - 7);
+            const double room = (double)w * num_cu;
+            double len = std::max(16.0, std::ceil(total * tiles / room));
+            double blocks = 0.0, longest = 0.0;
+            bool one = true, fits = false;
+            for (int it = 0; it < 6 && !fits && len <= kMaxDirectSlice; ++it) {
+                blocks = longest = 0.0;
+                one = true;
+                for (const auto &z : sizes) {
+                    const double n = std::ceil((double)z.first / len);
+                    blocks += n * z.second;
+                    longest = std::max(longest, (double)z.first / n);
+                    one = one && n <= 1.0;
+                }
+                blocks *= tiles;
+                fits = blocks <= room;
+                if (!fits) len = std::ceil(len * std::max(1.02, blocks / room));
+            }
+            if (!fits) continue;
+            const double cost = w * (longest * per_sample + per_block) + (one ? 0.0 : kZeroCycles);
+            if (best_cost < 0.0 || cost < best_cost) {
+                best_cost = cost;
+                *best = DensePlan{};
+                best->tiles = (int)tiles;
+                best->direct = 1;
+                best->shape = sh;
+                best->len = (int)len;
+                best->stored = one;
+                best->blocks = (long long)blocks;
+            }
+        }
+    }
+    if (best_cost >= 0.0 && sizes.size() == 1) best->P = slices_of(sizes[0].first, best->len);
+    return best_cost;  // below 0: too many blocks
+}
+
+DensePlan plan_dense(const SizeCounts &sizes, int C, int K, int M, int num_cu, int bpc)
+{
+    const long long max_n = sizes.back().first;
     DensePlan pl{};
-    const int need_m = (M + kTM - 1) / kTM;
-    pl.lanes_m = 1;
-    while (pl.lanes_m < need_m && pl.lanes_m < kThreads) pl.lanes_m *= 2;
-    pl.lanes_k = kThreads / pl.lanes_m;
-    pl.tiles_k = (K + pl.lanes_k - 1) / pl.lanes_k;
-    pl.tiles_m = (M + kTM * pl.lanes_m - 1) / (kTM * pl.lanes_m);
-    pl.tiles = pl.tiles_k * pl.tiles_m;
+    pl.tiles = (int)(((long long)K * M + kThreads * kTM - 1) / (kThreads * kTM));
     const long long T = (long long)C * pl.tiles;
     const long long slots = (long long)num_cu * std::max(bpc, 1);
-    if (T * max_n < kDirectSampleTiles * slots && T * kMaxDirectSlices <= (1LL << 22)) {
-        const long long maxP = std::max(1LL, std::min(kMaxDirectSlices, max_n / kMinSliceN));
-        long long fillP = 1;
-        double best = -1.0;
-        for (long long P = 1; P <= maxP; ++P) {
-            const long long n = T * P;
-            const long long waves = (n + slots - 1) / slots;
-            const double fill = (double)n / (double)(waves * slots);
-            if (fill > best + 1e-9) {
-                best = fill;
-                fillP = P;
-            }
-            if (fill >= 0.97) break;
-        }
-        pl.P = (int)fillP;
-        pl.direct = 1;
-        pl.blocks = T * pl.P;
-        return pl;
-    }
+    // The claimed slices run at 1.2 % above the v_sad_u16 rate of their padded
+    // tiles (16 x 1e6 samples: 108.6 ms), and lose 100 us where the last slices
+    // end and some 17 us per tile and compute unit in the runs' set-up (16 x 2e5 samples, K = 1000, M = 200:
+    // 8.72 ms, one block per slice 9.03; 8 x 4e5, K = 1024, M = 128: 5.75 and 5.53).
+    double total = 0.0;
+    for (const auto &z : sizes) total += (double)z.first * z.second;
+    const double claimed = total * pl.tiles * (kThreads * kTM) / (128.0 * num_cu) * 1.012 + 2.5e5 +
+                           4e4 * (double)T / num_cu;
+    DensePlan direct;
+    const double cost = plan_slices(sizes, K, M, num_cu, &direct);
+    if (cost >= 0.0 && cost <= claimed) return direct;
     const long long by_size = (max_n + kMaxSliceN - 1) / kMaxSliceN;
     const long long by_balance = std::min((kSlicesPerBlock * slots + T - 1) / T, max_n / kBalanceSliceN);
     const long long by_fill = std::min((slots + T - 1) / T, max_n / kMinSliceN);
@@ -360,11 +432,21 @@ DensePlan plan_dense(int C, int K, int M, long long max_n, int num_cu, int bpc)
     return pl;
 }
 
+// The plan of the staged problem, kept until another grid or other segments come.
+const DensePlan &staged_plan(dro_ctx *ctx, const dro_problem *p)
+{
+    if (ctx->plan_K != p->K || ctx->plan_M != p->M) {
+        ctx->plan = plan_dense(ctx->staged_sizes, p->C, p->K, p->M, ctx->num_cu, ctx->dense_bpc);
+        ctx->plan_K = p->K;
+        ctx->plan_M = p->M;
+    }
+    return ctx->plan;
+}
+
 // Claim counters of a dense launch: one per tile and the total.
 size_t dense_claim_words(int C, int K, int M)
 {
-    const DensePlan pl = plan_dense(C, K, M, 1, 1, 1);
-    return (size_t)C * pl.tiles + 1;
+    return (size_t)C * (((size_t)K * M + kThreads * kTM - 1) / (kThreads * kTM)) + 1;
 }
 
 // Host check of the dense entry points, before anything is enqueued: the
@@ -386,7 +468,7 @@ int run_dense(dro_ctx *ctx, const dro_problem *p, double *S, const PrefixEntry *
     unsigned long long *R = reinterpret_cast<unsigned long long *>(S);
     const long long ckm = (long long)p->C * p->K * p->M;
     const long long T = (long long)p->C * pl.tiles;  // T P < 2^31: check_dense and plan_dense
-    HIPCHK(launch_zero_u64_u32(R, ckm, claim, T + 1, st));
+    if (!pl.stored) HIPCHK(launch_zero_u64_u32(R, ckm, claim, pl.direct ? 0 : T + 1, st));
     DenseArgs a{};
     a.offsets = p->offsets;
     a.seg = p->seg;
@@ -504,11 +586,10 @@ size_t noalloc_need(const dro_problem *p)
 // The dense evaluation over scratch taken from `ar` (the device must be
 // current; p holds the staged arrays): value counts and sample sums of every
 // segment, the exact S into Sbuf, then the minimum over the multipliers.
-int run_cost_eval(dro_ctx *ctx, const dro_problem *p, const Shape &sh, const RowPlan &rows,
+int run_cost_eval(dro_ctx *ctx, const dro_problem *p, const DensePlan &pl, const RowPlan &rows,
                   bool packed, int E, const float *eps, double *W, int32_t *m_star, double *Sbuf,
                   Arena &ar, hipStream_t st)
 {
-    const DensePlan pl = plan_dense(p->C, p->K, p->M, sh.max_n, ctx->num_cu, ctx->dense_bpc);
     const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
     uint32_t *claim = ar.take<uint32_t>(dense_claim_words(p->C, p->K, p->M));
     HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
@@ -676,7 +757,7 @@ int dro_cost_eval(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *ep
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
     double *Sbuf = S ? S : ar.take<double>(ckm);
-    return run_cost_eval(ctx, &q, sh, rows, packed, E, eps, W, m_star, Sbuf, ar, st);
+    return run_cost_eval(ctx, &q, staged_plan(ctx, &q), rows, packed, E, eps, W, m_star, Sbuf, ar, st);
 }
 
 int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
@@ -706,7 +787,9 @@ int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const f
                                      cost_eval_scratch_bytes(p, rows, true) <=
                                  (size_t)DRO_NOALLOC_SCRATCH_BYTES;
     if ((rc = stage_in_arena(ctx, p, ar, packed, (hipStream_t)stream, &q, &rows))) return rc;
-    return run_cost_eval(ctx, &q, sh, rows, packed, E, eps, W, m_star, S, ar, (hipStream_t)stream);
+    const DensePlan pl =
+        plan_dense(class_sizes(p), p->C, p->K, p->M, ctx->num_cu, ctx->dense_bpc);
+    return run_cost_eval(ctx, &q, pl, rows, packed, E, eps, W, m_star, S, ar, (hipStream_t)stream);
 }
 
 int dro_argmin_reservation(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
@@ -932,7 +1015,6 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
     const int C = p->C;
-    const DensePlan pl = plan_dense(C, p->K, p->M, sh.max_n, ctx->num_cu, ctx->dense_bpc);
     const size_t ckm = (size_t)C * p->K * p->M;
     dro_problem q;
     RowPlan rows;
@@ -953,7 +1035,7 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     // the value counts give the quantile and the dense epilogue's counts and sums
     HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
     HIPCHK(launch_prefix_select(p->offsets, p->seg, p->c_p, p->c_w, cb.pre, C, out->q_value, st));
-    rc = run_dense(ctx, p, S, cb.pre, pl, claim, st);
+    rc = run_dense(ctx, p, S, cb.pre, staged_plan(ctx, p), claim, st);
     if (rc) return rc;
     HIPCHK(launch_min_over_lambda(S, p->offsets, p->seg, p->lam, eps, 1, C, p->K, p->M, W, nullptr,
                                   st));

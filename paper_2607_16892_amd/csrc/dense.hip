@@ -30,7 +30,7 @@
 // (k, m) pair in one single-rate VALU instruction.  Samples are staged in LDS
 // as 16-bit x + 1 (x <= 2^15, t clamped to [-1, L] or [0, L + 1], so both
 // fit), read back as wave-wide broadcasts of sixteen samples, and every lane
-// keeps kTM thresholds and 32-bit sums of one grid point.  Every
+// keeps the thresholds and 32-bit sums of kTM pairs.  Every
 // kHalfSadSteps instructions the bit 2^31 of each sum moves into a 16-bit
 // carry in LDS, so a sum spans any number of samples without a flush.
 //
@@ -51,31 +51,43 @@
 
 #include "dro_internal.h"
 #include "fixed.h"
+#include "wave.h"
 
 namespace dro {
 
 __device__ __forceinline__ int seg_of(const int32_t *seg, int c) { return seg ? seg[c] : c; }
 
-// Integer threshold t of a pair and its clamp to the range a 16-bit sample
-// code can meet: [-1, L] when c_w <= c_p (relu(x - t)), [0, L + 1] otherwise
-// (relu(t - x)).  Outside those ranges the sums are linear in the samples and
-// the epilogue adds the difference.
-struct Kink {
-    int64_t t;
-    int tc;
+// Integer threshold of a pair, clamped to the range a 16-bit sample code can
+// meet: [-1, L] when c_w <= c_p (relu(x - t)), [0, L + 1] otherwise
+// (relu(t - x)).  Beyond it the sums are linear in the samples, and the epilogue's
+// formula holds with the clamped t as it stands.
+__device__ __forceinline__ int pair_kink(const PairLinesFix &q, bool upper, int L)
+{
+    return upper ? floor_div_clamped(q.Nu, q.De, -1, L) : -floor_div_clamped(-q.Nu, q.De, -L - 1, 0);
+}
+
+// What the thresholds of one class need.
+struct ClassLines {
+    int64_t CP, CW;
+    int L;
+    bool upper;
 };
 
-__device__ __forceinline__ Kink pair_kink(const PairLinesFix &q, bool upper, int L)
+__device__ __forceinline__ ClassLines class_lines(const DenseArgs &a, int c)
 {
-    Kink k;
-    if (upper) {
-        k.t = floor_div(q.Nu, q.De);
-        k.tc = (int)(k.t < -1 ? -1 : (k.t > L ? L : k.t));
-    } else {
-        k.t = -floor_div(-q.Nu, q.De);
-        k.tc = (int)(k.t < 0 ? 0 : (k.t > L + 1 ? L + 1 : k.t));
-    }
-    return k;
+    const float cpf = a.c_p[c], cwf = a.c_w[c];
+    return ClassLines{fix33(cpf), fix33(cwf), a.L[c], cwf <= cpf};
+}
+
+// Threshold code t + 1 of pair p of a class (pairs in table order, p = k M + m;
+// pairs past the table take its last one, their sums are never stored).
+__device__ __forceinline__ uint16_t pair_code(const DenseArgs &a, const ClassLines &cl, uint32_t p)
+{
+    const uint32_t M = (uint32_t)a.M;
+    p = min(p, (uint32_t)a.K * M - 1u);
+    const uint32_t k = p / M, m = p - k * M;
+    const PairLinesFix q = pair_lines_fix(cl.CP, cl.CW, fix33(a.lam[m]), a.eta[k], cl.L);
+    return (uint16_t)(pair_kink(q, cl.upper, cl.L) + 1);
 }
 
 // First sample (relative to the segment start) of slice p of P: even offsets,
@@ -116,8 +128,6 @@ __global__ __launch_bounds__(kThreads) void dense_kernel(DenseArgs a)
     const int own_end = own(b + 1);
 
     const int t = threadIdx.x;
-    const int lm = t % pl.lanes_m, lk = t / pl.lanes_m;
-    const int BM = kTM * pl.lanes_m;
 
     uint32_t thr[kTM];  // (t + 1) in both 16-bit halves
     uint32_t acc[kTM];
@@ -126,7 +136,7 @@ __global__ __launch_bounds__(kThreads) void dense_kernel(DenseArgs a)
         acc[j] = 0u;
         carry[j * kThreads + t] = 0;
     }
-    int c = 0, k = 0, m0 = 0;
+    int c = 0, p0 = 0;  // the run's class and this lane's first pair
     // Sample codes 0 pad the end of a slice to whole groups of sixteen; each
     // adds t + 1 to a sum, which the flush takes off again.
     int pads = 0, steps = 0;
@@ -145,20 +155,19 @@ __global__ __launch_bounds__(kThreads) void dense_kernel(DenseArgs a)
         steps = 0;
     };
     auto flush = [&]() {
-        int ke = k, me = m0, ce = c, te = t;
-        asm volatile("" : "+v"(ke), "+v"(me), "+v"(ce), "+v"(te));
-        unsigned long long *row = a.R + ((long long)ce * a.K + ke) * a.M;
+        int pe = p0, ce = c, te = t;
+        asm volatile("" : "+v"(pe), "+v"(ce), "+v"(te));
+        const uint32_t KM = (uint32_t)a.K * (uint32_t)a.M;  // below 2^31
+        unsigned long long *row = a.R + (long long)ce * KM;
         uint16_t *cp = carry + te;
-        if (ke < a.K) {
 #pragma unroll
-            for (int j = 0; j < kTM; ++j) {
-                const int m = me + j * pl.lanes_m;
-                uint32_t a32 = acc[j];
-                asm volatile("" : "+v"(a32));  // keeps the sums 32-bit through the sample loop
-                const unsigned long long tot = ((unsigned long long)cp[j * kThreads] << 31) + a32 -
-                                               (unsigned long long)pads * (thr[j] & 0xffffu);
-                if (m < a.M) atomicAdd(row + m, tot);
-            }
+        for (int j = 0; j < kTM; ++j) {
+            const uint32_t p = (uint32_t)pe + j * kThreads;
+            uint32_t a32 = acc[j];
+            asm volatile("" : "+v"(a32));  // keeps the sums 32-bit through the sample loop
+            const unsigned long long tot = ((unsigned long long)cp[j * kThreads] << 31) + a32 -
+                                           (unsigned long long)pads * (thr[j] & 0xffffu);
+            if (p < KM) atomicAdd(row + p, tot);
         }
 #pragma unroll
         for (int j = 0; j < kTM; ++j) {
@@ -168,27 +177,16 @@ __global__ __launch_bounds__(kThreads) void dense_kernel(DenseArgs a)
         pads = 0;
         steps = 0;
     };
-    // the thresholds of tile tau (lanes past K or M take the last valid pair;
-    // their sums are never stored)
+    // the thresholds of tile tau: pair j * kThreads + t of its kThreads * kTM
     auto start_run = [&](int tau) {
         c = tau / pl.tiles;
-        const int tile = tau % pl.tiles;
-        const int tm = tile % pl.tiles_m, tk = tile / pl.tiles_m;
-        k = tk * pl.lanes_k + lk;
-        m0 = tm * BM + lm;
-        const float cpf = a.c_p[c], cwf = a.c_w[c];
-        const bool upper = cwf <= cpf;
-        const int64_t CP = fix33(cpf), CW = fix33(cwf);
-        const int L = a.L[c];
-        const int eta = a.eta[min(k, a.K - 1)];
+        p0 = (int)((uint32_t)(tau % pl.tiles) * (kThreads * kTM) + t);
+        const ClassLines cl = class_lines(a, c);
         // (four at a time: their multiplier loads overlap, and the 64-bit
         // arithmetic of four pairs fits beside the live sums)
 #pragma unroll 4
-        for (int j = 0; j < kTM; ++j) {
-            const int m = min(m0 + j * pl.lanes_m, a.M - 1);
-            const PairLinesFix q = pair_lines_fix(CP, CW, fix33(a.lam[m]), eta, L);
-            xs[j * kThreads + t] = (uint16_t)(pair_kink(q, upper, L).tc + 1);
-        }
+        for (int j = 0; j < kTM; ++j)
+            xs[j * kThreads + t] = pair_code(a, cl, (uint32_t)p0 + j * kThreads);
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < kTM; ++j) thr[j] = (uint32_t)xs[j * kThreads + t] * 0x10001u;
@@ -326,19 +324,6 @@ __global__ __launch_bounds__(kThreads) void dense_kernel(DenseArgs a)
         return s_claim;
     };
 
-    if (pl.direct) {
-        // Small problems: the grid has a block per slice (slices of a tile on
-        // consecutive logical blocks) and the hardware hands blocks to compute
-        // units as they free up; no claims.
-        const int tau = b / pl.P, p = b % pl.P;
-        start_run(tau);
-        const int sg = seg_of(a.seg, c);
-        const long long n_beg = a.offsets[sg], N = a.offsets[sg + 1] - n_beg;
-        run_slice(n_beg + slice_start(N, p, pl.P), n_beg + slice_start(N, p + 1, pl.P));
-        flush();
-        return;
-    }
-
     // Runs: pick a tile and claim a slice of it; take its thresholds; evaluate
     // its slices while claims on it succeed; add the sums to the table.
     bool any_xcd = xt0 == 0 && xt1 == T;  // search every tile (this XCD's are drained)
@@ -374,6 +359,184 @@ __global__ __launch_bounds__(kThreads) void dense_kernel(DenseArgs a)
     }
 }
 
+// Smaller problems: one block per (class, tile, slice of its samples).  Bound
+// by the same v_sad_u16, but a block's fixed cost (thresholds, first samples, the
+// sums' way to the table) is no longer small beside its samples, so it is spread
+// over 1,024 threads: NG = 1024 / GL groups of GL lanes hold the same tile of
+// TM * GL pairs.  Each threshold is then computed once per block (not once per 256
+// lanes) and the groups' sums meet in LDS, so the table gets one 64-bit atomic
+// per pair and block, a plain store where one block holds all of a class's
+// samples.  The waves that hold the same 64 TM pairs claim steps of sixteen
+// staged samples from a counter in LDS: with fixed shares the oldest wave of a
+// SIMD runs ahead and the last one ends alone, waiting for its reads (8 x 4e5
+// samples: 5.68 ms with fixed shares and 4,096 samples a buffer, 5.60 claimed,
+// 5.50 with 16,384 a buffer, whose barriers are fewer).
+// The tile shape (TM, GL) fits the grid: its pairs are taken in table order, so
+// only the last tile of a class is padded.  Slices have one length over all
+// classes, so segments of unequal size keep every block equally long.  A slice
+// holds at most 65,536 samples: with its padding its sums stay below 2^32, so
+// there are no carries.
+// dense part of dro_cost_eval before and after, in blocks of 256 threads with
+// 32 multipliers a lane before: 4 x 1e5 samples, K = 512, M = 128: 429 -> 375 us
+// (344 at this launch's clock of 2.33 GHz; 4.5 % more VALU instructions than
+// sads, 99.6 % issue, the rest before the first and after the last wave); six
+// segments from 1.2e5 to 7.9e3 samples, K = 333, M = 50: 289 -> 102 us; 1,000
+// samples, K = 64, M = 32: 21 -> 5.3 us.
+constexpr int kSliceThreads = 1024;
+
+template <int TM, int GL>
+__global__ __launch_bounds__(kSliceThreads) void dense_slices_kernel(DenseArgs a)
+{
+    constexpr int NG = kSliceThreads / GL, kPairs = TM * GL;
+    constexpr int kT = 16384, kPer = kT / kSliceThreads;  // samples per staging buffer, per thread
+    __shared__ __attribute__((aligned(16))) uint16_t xs[2][kT];
+    __shared__ uint16_t code[kPairs];
+    __shared__ uint32_t sums[kPairs];
+    constexpr int kParts = GL / 64, kChunk = 64 / TM;
+    __shared__ uint32_t next[2][kParts];  // next unclaimed step of a buffer, by part of the tile
+    const DensePlan pl = a.plan;
+    const int t = threadIdx.x, lane = t & 63, gl = t % GL;
+    const int part = __builtin_amdgcn_readfirstlane(gl / 64);  // the wave's part of the tile
+    // the logical block order gives each XCD one contiguous run of blocks
+    const int nb = (int)gridDim.x, xcd = (int)(blockIdx.x % kXcds);
+    const int b = xcd * (nb / kXcds) + min(xcd, nb % kXcds) + (int)(blockIdx.x / kXcds);
+    // block b: class c, then slice p of its P, then tile
+    int c = 0, P = pl.P, u = b;
+    if (P) {
+        c = b / (P * pl.tiles);
+        u = b % (P * pl.tiles);
+    } else {
+        for (;; c += 64) {  // 64 classes at a time: the one whose blocks hold b
+            int n = 0;
+            if (c + lane < a.C) {
+                const int sg = seg_of(a.seg, c + lane);
+                n = pl.tiles * slices_of(a.offsets[sg + 1] - a.offsets[sg], pl.len);
+            }
+            const int incl = (int)scan_wave((uint32_t)n);
+            const unsigned long long in = __ballot(u < incl);
+            if (in || c + 64 >= a.C) {
+                const int l = in ? __ffsll(in) - 1 : 0;
+                c += l;
+                u -= __builtin_amdgcn_readlane(incl - n, l);
+                P = __builtin_amdgcn_readlane(n, l) / pl.tiles;
+                break;
+            }
+            u -= __builtin_amdgcn_readlane(incl, 63);
+        }
+    }
+    const int p = u / pl.tiles, tile = u % pl.tiles;
+    const int sg = seg_of(a.seg, c);
+    // slice p of P nearly equal ones (N <= 2^26)
+    const long long n_beg = a.offsets[sg];
+    const uint32_t N = (uint32_t)(a.offsets[sg + 1] - n_beg);
+    const uint32_t each = N / (uint32_t)P, more = N % (uint32_t)P;
+    const int len = (int)(each + ((uint32_t)p < more ? 1u : 0u));
+    const int32_t *tp = a.xi + n_beg + (uint32_t)p * each + min((uint32_t)p, more);
+
+    int32_t pf[kPer];
+    auto fetch = [&](int base) {
+#pragma unroll
+        for (int r = 0; r < kPer; ++r)
+            if (base + r * kSliceThreads < len)
+                pf[r] = tp[min(base + r * kSliceThreads + t, len - 1)];
+    };
+    auto put = [&](int base) {  // codes 0 past the slice's end
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            const int i = t + r * kSliceThreads;
+            if (base + r * kSliceThreads < len)
+                xs[(base / kT) & 1][i] = (uint16_t)(base + i < len ? pf[r] + 1 : 0);
+        }
+    };
+    if (len > 0) fetch(0);
+    const ClassLines cl = class_lines(a, c);
+#pragma unroll  // the multiplier and grid loads of all a thread's pairs in flight
+    for (int r = 0; r < (kPairs + kSliceThreads - 1) / kSliceThreads; ++r) {
+        const int q = t + r * kSliceThreads;
+        if (q < kPairs) {
+            code[q] = pair_code(a, cl, (uint32_t)tile * kPairs + q);
+            sums[q] = 0u;
+        }
+    }
+    if (len > 0) put(0);
+    if (t < kParts) next[0][t] = 0u;
+    __syncthreads();
+    uint32_t thr[TM], acc[TM];
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+        thr[j] = (uint32_t)code[j * GL + gl] * 0x10001u;
+        acc[j] = 0u;
+    }
+    const int nbuf = (len + kT - 1) / kT;
+    for (int i = 0; i < nbuf; ++i) {
+        const int n16 = (min(kT, len - i * kT) + 15) / 16;
+        if (i + 1 < nbuf) fetch((i + 1) * kT);
+        const uint4 *x4 = reinterpret_cast<const uint4 *>(xs[i & 1]);
+        // the next step's samples are read while this step's are evaluated, in
+        // two register sets
+        uint4 v0, z0, v1, z1;
+        auto read = [&](int w, uint4 &v, uint4 &z) {
+            const int q = min(w, n16 - 1);
+            v = x4[2 * q];
+            z = x4[2 * q + 1];
+        };
+        auto eval = [&](const uint4 &v, const uint4 &z) {
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(v.x, thr[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(v.y, thr[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(v.z, thr[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(v.w, thr[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(z.x, thr[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(z.y, thr[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(z.z, thr[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[j] = __builtin_amdgcn_sad_u16(z.w, thr[j], acc[j]);
+        };
+        const int ch = max(1, min(kChunk, n16 / (8 * NG)));
+        auto claim = [&]() {  // (a register, read when the next chunk starts)
+            int w = 0;
+            if (lane == 0) w = (int)atomicAdd(&next[i & 1][part], (uint32_t)ch);
+            return w;
+        };
+        if (t < kParts) next[(i + 1) & 1][t] = 0u;
+        int w = __builtin_amdgcn_readfirstlane(claim());
+        while (w < n16) {
+            const int after = claim();
+            const int w1 = min(w + ch, n16);
+            read(w, v0, z0);
+            for (; w < w1; w += 2) {
+                read(w + 1, v1, z1);
+                eval(v0, z0);
+                if (w + 1 >= w1) break;
+                read(w + 2, v0, z0);
+                eval(v1, z1);
+            }
+            w = __builtin_amdgcn_readfirstlane(after);
+        }
+        if (i + 1 < nbuf) put((i + 1) * kT);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < TM; ++j) atomicAdd(&sums[j * GL + gl], acc[j]);
+    __syncthreads();
+    // codes 0 pad the last buffer to sixteens; each added t + 1
+    const uint32_t pads = (uint32_t)((16 - (len & 15)) & 15);
+    const int KM = a.K * a.M, q0 = tile * kPairs;  // below 2^31
+    unsigned long long *row = a.R + (long long)c * KM + q0;
+    const int nq = min(kPairs, KM - q0);
+    for (int q = t; q < nq; q += kSliceThreads) {
+        const unsigned long long tot = sums[q] - pads * (uint32_t)code[q];
+        if (P == 1) row[q] = tot;
+        else atomicAdd(row + q, tot);
+    }
+}
+
 int dense_blocks_per_cu()
 {
     int n = 0;
@@ -382,9 +545,19 @@ int dense_blocks_per_cu()
     return n;
 }
 
+// the tile shapes of dense_slices_kernel, by DensePlan::shape
+using SlicesKernel = void (*)(DenseArgs);
+static const SlicesKernel kSlicesKernels[kSliceShapes] = {
+    dense_slices_kernel<32, 256>, dense_slices_kernel<32, 128>, dense_slices_kernel<32, 64>,
+    dense_slices_kernel<16, 64>, dense_slices_kernel<8, 64>};
+
 hipError_t launch_dense(const DenseArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(dense_kernel, dim3((unsigned)a.plan.blocks), dim3(kThreads), 0, st, a);
+    if (a.plan.direct)
+        hipLaunchKernelGGL(kSlicesKernels[a.plan.shape], dim3((unsigned)a.plan.blocks),
+                           dim3(kSliceThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL(dense_kernel, dim3((unsigned)a.plan.blocks), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
 
@@ -426,30 +599,26 @@ __device__ __forceinline__ void dense_finish_one(const DenseFinishArgs &a, long 
     const int k = (int)((i / a.M) % a.K);
     const int m = (int)(i % a.M);
     const int s = seg_of(a.seg, c);
-    const long long N = a.offsets[s + 1] - a.offsets[s];
+    const int64_t N = a.offsets[s + 1] - a.offsets[s];
     const PrefixEntry *cn = a.pre + (long long)s * kHistBins;
-    const __int128 sx = (__int128)cn[kHistBins - 1].sum();
+    const int64_t sx = (int64_t)cn[kHistBins - 1].sum();
     const float cpf = a.c_p[c], cwf = a.c_w[c];
     const bool upper = cwf <= cpf;
     const int L = a.L[c];
     const PairLinesFix q = pair_lines_fix(fix33(cpf), fix33(cwf), fix33(a.lam[m]), a.eta[k], L);
-    const Kink kk = pair_kink(q, upper, L);
-    const __int128 sad = (__int128)a.R[i];
-    const __int128 n = N, tc = kk.tc, tt = kk.t;
+    const int64_t t = pair_kink(q, upper, L);
+    const int64_t sad = (int64_t)a.R[i];
     __int128 S;
     if (upper) {
-        // sum relu(x - t) with the clamp undone for t < -1 (every sample above t)
-        const __int128 Rt = (sx - n * tc + sad) / 2 + n * (tc > tt ? tc - tt : 0);
-        const __int128 r = (__int128)q.Nu - (__int128)q.De * tt;
-        const __int128 above = n - count_le(cn, kk.t, N);
-        S = n * q.B - (__int128)q.A1 * sx + (__int128)q.De * Rt - r * above;
+        const uint64_t Rt = (uint64_t)(sx - N * t + sad) / 2;
+        const uint32_t above = (uint32_t)(N - count_le(cn, t, N));
+        S = mul_i64_u31(q.B, (uint32_t)N) - mul_u43((uint64_t)q.A1, (uint64_t)sx) +
+            mul_u43((uint64_t)q.De, Rt) - mul_i64_u31(q.Nu - q.De * t, above);
     } else {
-        // sum relu(t - x) with the clamp undone for t > L + 1 (every sample below t)
-        const __int128 Rt = (n * tc - sx + sad) / 2 + n * (tt > tc ? tt - tc : 0);
-        const __int128 r = (__int128)q.De * tt - (__int128)q.Nu;
-        const __int128 below = count_le(cn, kk.t - 1, N);
-        S = n * ((__int128)q.Cc - (__int128)q.A2 * L) + (__int128)q.A2 * sx + (__int128)q.De * Rt -
-            r * below;
+        const uint64_t Rt = (uint64_t)(N * t - sx + sad) / 2;
+        const uint32_t below = (uint32_t)count_le(cn, t - 1, N);
+        S = mul_i64_u31(q.Cc - q.A2 * L, (uint32_t)N) + mul_u43((uint64_t)q.A2, (uint64_t)sx) +
+            mul_u43((uint64_t)q.De, Rt) - mul_i64_u31(q.De * t - q.Nu, below);
     }
     reinterpret_cast<double *>(a.R)[i] = sfix128_to_double(S);
 }

@@ -10,9 +10,9 @@
 namespace dro {
 
 // ---- dense evaluation -------------------------------------------------------
-// Every lane owns one grid point and kTM multipliers; a 256-lane block covers a
-// tile of lanes_k x (kTM * lanes_m) pairs of one class.  The samples of each
-// tile are split into P slices.  A persistent grid of blocks claims slices
+// A 256-lane block covers a tile of 256 kTM (grid point, multiplier) pairs of one
+// class, kTM per lane, taken in table order.  The samples of each tile are split
+// into P slices.  A persistent grid of blocks claims slices
 // (its own tiles first, then other tiles' unclaimed slices) and keeps a
 // tile's sums in registers over consecutive slices of that tile.
 constexpr int kThreads = 256;
@@ -22,15 +22,26 @@ constexpr int kHalfSadSteps = 32766;  // v_sad_u16 steps between carries: a sum 
                                       // takes 32766 more steps of at most 2 * 32770 below 2^32
 constexpr int kXcds = 8;              // accelerator complex dies of one MI355X (one L2 each)
 
+// tile shapes of the one-block-per-slice kernel: pairs per lane, lanes per group
+constexpr int kSliceShapes = 5;
+constexpr int kSliceTM[kSliceShapes] = {32, 32, 32, 16, 8};
+constexpr int kSliceGL[kSliceShapes] = {256, 128, 64, 64, 64};
+
 struct DensePlan {
-    int lanes_m, lanes_k;  // lane grid inside a block
-    int tiles_k, tiles_m;  // block tiles per class
-    int tiles;             // tiles_k * tiles_m
-    int P;                 // sample slices per tile
-    int direct;            // 1: one block per slice, no claims (small problems)
-    long long blocks;      // direct: C * tiles * P; else the persistent grid,
-                           // min(resident blocks, C * tiles * P)
+    int tiles;         // tiles of the K * M pairs of a class, in table order
+    int P;             // sample slices per tile (direct: 0 = by each class's size and len)
+    int direct;        // 1: one block per slice, no claims (smaller problems)
+    int shape;         // direct: the tile shape
+    int len;           // direct: samples per slice, at most
+    bool stored;       // direct: every class has one slice, so the sums are stored, not added
+    long long blocks;  // direct: a block per slice; else the persistent grid,
+                       // min(resident blocks, C * tiles * P)
 };
+// slices of n samples
+__host__ __device__ inline int slices_of(long long n, int len)
+{
+    return n <= len ? 1 : (int)((n + len - 1) / len);
+}
 
 struct DenseArgs {
     const int64_t *offsets;
@@ -44,6 +55,7 @@ struct DenseArgs {
     int C, K, M;
     DensePlan plan;
     unsigned long long *R;  // [C][K][M] sums of |x - t| over the class's samples, zeroed first
+                            // unless plan.stored
     uint32_t *claim;        // [C * tiles + 1] slice counters per tile, then the total; zeroed first
 };
 

@@ -31,7 +31,7 @@ __device__ __forceinline__ int64_t floor_div(int64_t a, int64_t b)
     return q;
 }
 
-// floor(a / b) clamped to [lo, hi] for b > 0 and -2 <= lo <= hi < 2^16: the
+// floor(a / b) clamped to [lo, hi] for b > 0 and -2^16 < lo <= hi < 2^16: the
 // quotient by the reciprocal instruction (about 2^-26 relative, so within one of
 // the floor after the clamp) corrected once with the exact remainder.
 __device__ __forceinline__ int floor_div_clamped(int64_t a, int64_t b, int lo, int hi)

@@ -1,0 +1,66 @@
+"""The one-block-per-slice schedule of the dense evaluation at its edges, S bit
+for bit against the oracle: tables of one pair, of one pair less and more than a
+tile of each shape (512 to 8,192 pairs), class sizes around the staging buffer
+(16,384 samples) and the sixteens of a step, more unequal classes than one wave
+looks through at once (64), a class of one sample beside long ones, and sums of
+one slice (stored) as well as of several (added).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from workloads.configs import Workload, _csr, _f32, eta_grid, lam_grid
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx(dev):
+    import paper_2607_16892_amd as dro
+    c = dro.Context(dev.index or 0)
+    yield c
+    c.close()
+
+
+def _check(ctx, dev, sizes, K, M, L=32768, seg=None):
+    import torch
+    import paper_2607_16892_amd as dro
+    rng = np.random.default_rng(K * M + len(sizes))
+    parts = [np.clip(np.rint(rng.lognormal(6.0, 2.0, n)), 0, L).astype(np.int32) for n in sizes]
+    off, xi = _csr(parts)
+    C = len(sizes) if seg is None else len(seg)
+    choice = [(8.0, 1.0), (1.0, 1.0), (2.0 ** 7, 2.0 ** -10), (0.5, 3.0)]
+    w = Workload("slices", C, off, None if seg is None else np.asarray(seg, np.int32), xi,
+                 np.full(C, L, np.int32), eta_grid(K, L), lam_grid(M),
+                 _f32([choice[c % 4][0] for c in range(C)]),
+                 _f32([choice[c % 4][1] for c in range(C)]), 1, _f32(rng.uniform(0, 50, C)))
+    print(f"[gpu] slices: {C} classes, K={K} M={M}, {off[-1]} samples", flush=True)
+    prob = dro.Problem.from_workload(w, dev)
+    r = dro.dro_cost_eval(ctx, prob, torch.from_numpy(w.eps).to(dev))
+    torch.cuda.synchronize()
+    S = oracle.S_exact(w)
+    assert np.array_equal(r["S"].cpu().numpy().view(np.uint64),
+                          S.to_double().reshape(C, K, M).view(np.uint64))
+    W, m = oracle.W_table(w, S)
+    assert np.array_equal(r["W"].cpu().numpy().view(np.uint64), W.view(np.uint64))
+    assert np.array_equal(r["m_star"].cpu().numpy(), m)
+
+
+@pytest.mark.parametrize("K,M", [(1, 1), (1, 511), (64, 8), (27, 19), (32, 32), (25, 41),
+                                 (2047, 1), (64, 64), (17, 241), (4095, 2), (64, 128), (2731, 3)])
+def test_tables_around_the_tiles(ctx, dev, K, M):
+    _check(ctx, dev, (700, 1, 33), K, M)
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 16_383, 16_384, 16_385, 40_000, 150_001])
+def test_class_sizes_around_the_buffers(ctx, dev, n):
+    _check(ctx, dev, (n,), 33, 31)
+    _check(ctx, dev, (n, 5), 40, 52)
+
+
+def test_more_unequal_classes_than_a_wave_holds(ctx, dev):
+    rng = np.random.default_rng(3)
+    sizes = [int(v) for v in rng.integers(1, 3000, 131)]
+    sizes[64] = 60_000
+    _check(ctx, dev, sizes, 7, 11)
+    _check(ctx, dev, sizes[60:70], 20, 30, seg=[c % 10 for c in range(70)])
