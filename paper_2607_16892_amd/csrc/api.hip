@@ -459,11 +459,19 @@ int check_dense(dro_ctx *ctx, const dro_problem *p)
     return DRO_OK;
 }
 
-// Exact S into `S` ([C][K][M] doubles): the dense per-sample sums, then the
-// exact epilogue over the segments' prefix entries.  claim:
-// dense_claim_words scratch.
-int run_dense(dro_ctx *ctx, const dro_problem *p, double *S, const PrefixEntry *pre,
-              const DensePlan &pl, uint32_t *claim, hipStream_t st)
+RowMinArgs row_args(const dro_problem *p, int E, const float *eps, double *S,
+                    const PrefixEntry *pre, double *W, int32_t *m_star)
+{
+    return RowMinArgs{p->offsets, p->seg, p->L, p->eta, p->lam, p->c_p, p->c_w, eps,
+                      pre,        E,      p->C, p->K,   p->M,   S,      W,      m_star};
+}
+
+// Exact S into `S` ([C][K][M] doubles) and the minimum over the multipliers: the
+// dense per-sample sums, then the exact epilogue over the segments' prefix
+// entries.  claim: dense_claim_words scratch.
+int run_dense(dro_ctx *ctx, const dro_problem *p, int E, const float *eps, double *S,
+              const PrefixEntry *pre, const DensePlan &pl, uint32_t *claim, double *W,
+              int32_t *m_star, hipStream_t st)
 {
     unsigned long long *R = reinterpret_cast<unsigned long long *>(S);
     const long long ckm = (long long)p->C * p->K * p->M;
@@ -485,20 +493,7 @@ int run_dense(dro_ctx *ctx, const dro_problem *p, double *S, const PrefixEntry *
     a.R = R;
     a.claim = claim;
     HIPCHK(launch_dense(a, st));
-    DenseFinishArgs f{};
-    f.offsets = p->offsets;
-    f.seg = p->seg;
-    f.L = p->L;
-    f.eta = p->eta;
-    f.lam = p->lam;
-    f.c_p = p->c_p;
-    f.c_w = p->c_w;
-    f.pre = pre;
-    f.C = p->C;
-    f.K = p->K;
-    f.M = p->M;
-    f.R = R;
-    HIPCHK(launch_dense_finish(f, st));
+    HIPCHK(launch_row_min(row_args(p, E, eps, S, pre, W, m_star), true, ctx->num_cu, st));
     return DRO_OK;
 }
 
@@ -593,11 +588,7 @@ int run_cost_eval(dro_ctx *ctx, const dro_problem *p, const DensePlan &pl, const
     const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
     uint32_t *claim = ar.take<uint32_t>(dense_claim_words(p->C, p->K, p->M));
     HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
-    const int rc = run_dense(ctx, p, Sbuf, cb.pre, pl, claim, st);
-    if (rc) return rc;
-    HIPCHK(launch_min_over_lambda(Sbuf, p->offsets, p->seg, p->lam, eps, E, p->C, p->K, p->M, W,
-                                  m_star, st));
-    return DRO_OK;
+    return run_dense(ctx, p, E, eps, Sbuf, cb.pre, pl, claim, W, m_star, st);
 }
 
 }  // namespace
@@ -816,8 +807,8 @@ int dro_argmin_reservation(dro_ctx *ctx, const dro_problem *p, int32_t E, const 
     int32_t *m_star = ar.take<int32_t>(eck);
     // S is exact, so W (the exact-spec J minimised over m) is too, and the
     // lowest-index optimum is a plain minimum over k
-    HIPCHK(launch_min_over_lambda(S, p->offsets, p->seg, p->lam, eps, E, p->C, p->K, p->M, W, m_star,
-                                  st));
+    HIPCHK(launch_row_min(row_args(p, E, eps, const_cast<double *>(S), nullptr, W, m_star), false,
+                          ctx->num_cu, st));
     HIPCHK(launch_table_argmin(W, m_star, k_max, E, p->C, p->K, k_star, W_star, m_at_star, st));
     return DRO_OK;
 }
@@ -1035,10 +1026,8 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     // the value counts give the quantile and the dense epilogue's counts and sums
     HIPCHK(launch_counts(p->offsets, p->xi, p->S, cb, st));
     HIPCHK(launch_prefix_select(p->offsets, p->seg, p->c_p, p->c_w, cb.pre, C, out->q_value, st));
-    rc = run_dense(ctx, p, S, cb.pre, staged_plan(ctx, p), claim, st);
+    rc = run_dense(ctx, p, 1, eps, S, cb.pre, staged_plan(ctx, p), claim, W, nullptr, st);
     if (rc) return rc;
-    HIPCHK(launch_min_over_lambda(S, p->offsets, p->seg, p->lam, eps, 1, C, p->K, p->M, W, nullptr,
-                                  st));
     HIPCHK(hipMemcpyAsync(kcur, k_prev, sizeof(int32_t) * C, hipMemcpyDeviceToDevice, st));
     HIPCHK(launch_bcd_sweep(W, p->eta, C, p->K, grp->G, grp->cap, grp->conc, grp->kappa, kcur,
                             out->k_next, out->W_star, out->feasible, out->usage, st));

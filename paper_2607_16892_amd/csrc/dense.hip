@@ -589,111 +589,165 @@ __device__ __forceinline__ long long count_le(const PrefixEntry *pre, long long 
     return (long long)pre[v].cnt;
 }
 
-// S[c,k,m] from the per-sample sums sum |x - t_c| of the dense kernel (in R,
-// overwritten in place), the segment's value counts and its sample sum:
-// exactly, in 128-bit integers in units of 2^-33, then rounded to double once.
-__device__ __forceinline__ void dense_finish_one(const DenseFinishArgs &a, long long i)
+// ---- rows: the exact S and the minimum over the multipliers, in one pass ----
+//
+// A block takes RB consecutive rows (c, k) of the table, their pairs a chunk of
+// kRowPairs at a time (whole rows while M fits): every thread forms q = RN(S / N)
+// of its pairs in table order (coalesced, however small M is) and stages them in
+// LDS with the multipliers; then the block's 256 lanes split over the (radius,
+// row) tasks, lp lanes each (a power of two, at most a wave), lane j of a task
+// taking the multipliers j, j + lp, ...  Each lane keeps the smallest J of its
+// multipliers (the lowest m among equal values, as it visits them in ascending
+// order), then log2(lp) shuffle steps take the task's smallest, ties to the
+// lowest m: the same J bits and the same lowest m as a scan over m.
+//
+// kFinish: S comes from the dense kernels' sums of |x - t| (in the table, u64,
+// overwritten in place by S): exactly, in 128-bit integers in units of 2^-33 from
+// the segment's N, sample sum and one value count, rounded to double once.
+// Otherwise the table already holds S.
+// Bound by the integer arithmetic (kFinish) or by reading S; one pass instead of
+// the epilogue and the minimum apart saves reading S back: 68 us for the two
+// launches' 101 + 21 on 16 x 2048 rows of 256 multipliers, 7.0 for 4.6 + 4.7 on
+// 6 x 333 rows of 50 and three radii.  (1,024 pairs a block: 70 us, and 28 for 23
+// without kFinish; a resident grid that loads its next rows early: 77 us.)
+constexpr int kRowThreads = 256;
+constexpr int kRowPairs = 2048;  // pairs staged per block at a time
+constexpr int kRowMax = 64;      // rows per block
+
+struct RowInfo {
+    int64_t B, Cc, CP, CW, sx;
+    double N, rN;  // and RN(1 / N)
+    const PrefixEntry *pre;
+    int L;
+    bool upper;
+};
+
+// q = RN(S / N) from r = RN(1 / N): q0 = RN(S r) is within one unit of S / N, its
+// residual S - q0 N is exact in an fma, and one more fma rounds the quotient
+// correctly (Markstein; N is an integer below 2^27, so its significand is not all
+// ones; S is finite and far from underflow).
+__device__ __forceinline__ double div_by(double S, double N, double rN)
 {
-    const long long KM = (long long)a.K * a.M;
-    const int c = (int)(i / KM);
-    const int k = (int)((i / a.M) % a.K);
-    const int m = (int)(i % a.M);
-    const int s = seg_of(a.seg, c);
-    const int64_t N = a.offsets[s + 1] - a.offsets[s];
-    const PrefixEntry *cn = a.pre + (long long)s * kHistBins;
-    const int64_t sx = (int64_t)cn[kHistBins - 1].sum();
-    const float cpf = a.c_p[c], cwf = a.c_w[c];
-    const bool upper = cwf <= cpf;
-    const int L = a.L[c];
-    const PairLinesFix q = pair_lines_fix(fix33(cpf), fix33(cwf), fix33(a.lam[m]), a.eta[k], L);
-    const int64_t t = pair_kink(q, upper, L);
-    const int64_t sad = (int64_t)a.R[i];
+    const double q0 = __dmul_rn(S, rN);
+    return __fma_rn(__fma_rn(-q0, N, S), rN, q0);
+}
+
+// S of one pair from its sum of |x - t|.  With c_w <= c_p, t = floor(Nu / De)
+// and Rt = sum relu(x - t): S = N B - A1 sum x + De Rt - (Nu - De t) #{x > t};
+// the mirror image otherwise.
+__device__ __forceinline__ double finish_pair(const RowInfo &w, float lam, int64_t sad)
+{
+    const int64_t G = fix33(lam), N = (int64_t)w.N;
+    const int64_t A1 = G < w.CW ? G : w.CW, A2 = G < w.CP ? G : w.CP, De = A1 + A2;
+    const int64_t Nu = w.B - w.Cc + A2 * w.L;
+    const int64_t t = w.upper ? floor_div_clamped(Nu, De, -1, w.L)
+                              : -floor_div_clamped(-Nu, De, -w.L - 1, 0);
     __int128 S;
-    if (upper) {
-        const uint64_t Rt = (uint64_t)(sx - N * t + sad) / 2;
-        const uint32_t above = (uint32_t)(N - count_le(cn, t, N));
-        S = mul_i64_u31(q.B, (uint32_t)N) - mul_u43((uint64_t)q.A1, (uint64_t)sx) +
-            mul_u43((uint64_t)q.De, Rt) - mul_i64_u31(q.Nu - q.De * t, above);
+    if (w.upper) {
+        const uint64_t Rt = (uint64_t)(w.sx - N * t + sad) / 2;
+        const uint32_t above = (uint32_t)(N - count_le(w.pre, t, N));
+        S = mul_i64_u31(w.B, (uint32_t)N) - mul_u43((uint64_t)A1, (uint64_t)w.sx) +
+            mul_u43((uint64_t)De, Rt) - mul_i64_u31(Nu - De * t, above);
     } else {
-        const uint64_t Rt = (uint64_t)(N * t - sx + sad) / 2;
-        const uint32_t below = (uint32_t)count_le(cn, t - 1, N);
-        S = mul_i64_u31(q.Cc - q.A2 * L, (uint32_t)N) + mul_u43((uint64_t)q.A2, (uint64_t)sx) +
-            mul_u43((uint64_t)q.De, Rt) - mul_i64_u31(q.De * t - q.Nu, below);
+        const uint64_t Rt = (uint64_t)(N * t - w.sx + sad) / 2;
+        const uint32_t below = (uint32_t)count_le(w.pre, t - 1, N);
+        S = mul_i64_u31(w.Cc - A2 * w.L, (uint32_t)N) + mul_u43((uint64_t)A2, (uint64_t)w.sx) +
+            mul_u43((uint64_t)De, Rt) - mul_i64_u31(De * t - Nu, below);
     }
-    reinterpret_cast<double *>(a.R)[i] = sfix128_to_double(S);
+    return sfix128_to_double(S);
 }
 
-__global__ void dense_finish_kernel(DenseFinishArgs a)
+template <bool kFinish>
+__global__ __launch_bounds__(kRowThreads) void row_min_kernel(RowMinArgs a, int RB, int lp)
 {
-    const long long n = (long long)a.C * a.K * a.M;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x)
-        dense_finish_one(a, i);
-}
-
-hipError_t launch_dense_finish(const DenseFinishArgs &a, hipStream_t st)
-{
-    const long long n = (long long)a.C * a.K * a.M;
-    hipLaunchKernelGGL(dense_finish_kernel, dim3((unsigned)std::min((n + 255) / 256, kMaxGridBlocks)),
-                       dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-// One wave per (c, k) row.  The wave stages q_m = S[c,k,m] / N and lambda_m
-// for a chunk of multipliers in LDS (coalesced reads of the row, each quotient
-// computed once); then its 64 lanes split into g groups of 64/g, g the power of
-// two covering E (at most 64), group j taking radius e0 + j and its lanes the
-// multipliers m = part, part + 64/g, ... of the chunk.  Each lane keeps the
-// smallest J of its multipliers (the lowest m among equal values, as it visits
-// them in ascending order), then log2(64/g) shuffle steps take the smallest J
-// of the group, ties to the lowest m: the same J bits and the same lowest m as
-// a scan over m.
-constexpr int kMinWaves = 4;    // waves (rows) per block
-constexpr int kMinChunk = 256;  // multipliers staged per wave at a time
-
-__global__ __launch_bounds__(64 * kMinWaves) void min_over_lambda_kernel(
-    const double *S, const int64_t *offsets, const int32_t *seg, const float *lam, const float *eps,
-    int E, int C, int K, int M, double *W, int32_t *m_star)
-{
-    __shared__ double2 st[kMinWaves][kMinChunk];  // (q_m, lambda_m)
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // rows in a grid-stride loop of whole waves (no block barrier below)
-    for (long long ck = (long long)blockIdx.x * kMinWaves + w; ck < (long long)C * K;
-         ck += (long long)gridDim.x * kMinWaves) {
-        const int c = (int)(ck / K), k = (int)(ck % K);
-        const int s = seg_of(seg, c);
-        const double N = (double)(offsets[s + 1] - offsets[s]);
-        const double *row = S + ck * M;
-        int lg = 0;  // log2 of the groups
-        while (lg < 6 && (1 << lg) < E) ++lg;
-        const int lp = 6 - lg;  // log2 of the lanes per group
-        const int part = lane & ((1 << lp) - 1), grp = lane >> lp;
-        double2 *q = st[w];
-        for (int e0 = 0; e0 < E; e0 += 1 << lg) {
-            const int e = e0 + grp;
-            const double ev = e < E ? (double)eps[(long long)e * C + c] : 0.0;
+    __shared__ double q[kRowPairs + kRowMax];
+    __shared__ float s_lam[kRowPairs];
+    __shared__ RowInfo info[kRowMax];
+    const int t = threadIdx.x, M = a.M;
+    const long long rows = (long long)a.C * a.K;
+    for (long long row0 = (long long)blockIdx.x * RB; row0 < rows; row0 += (long long)gridDim.x * RB) {
+        const int rb = (int)min((long long)RB, rows - row0);
+        // the first chunk's table entries, every load in flight before the rows' data
+        constexpr int kPer = kRowPairs / kRowThreads;
+        double v[kPer];
+        auto load = [&](const double *S, int n) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (t + u * kRowThreads < n) v[u] = S[t + u * kRowThreads];
+        };
+        load(a.S + row0 * M, rb * min(M, kRowPairs));
+        const int c0 = (int)(row0 / a.K), k0 = (int)(row0 - (long long)c0 * a.K);
+        if (t < rb) {
+            const int c = c0 + (k0 + t) / a.K, k = (k0 + t) % a.K;
+            const int s = seg_of(a.seg, c);
+            RowInfo w{};
+            w.N = (double)(a.offsets[s + 1] - a.offsets[s]);
+            w.rN = __ddiv_rn(1.0, w.N);
+            if (kFinish) {
+                const float cpf = a.c_p[c], cwf = a.c_w[c];
+                w.CP = fix33(cpf);
+                w.CW = fix33(cwf);
+                w.upper = cwf <= cpf;
+                w.L = a.L[c];
+                w.B = w.CW * a.eta[k];
+                w.Cc = w.CP * (w.L - a.eta[k]);
+                w.pre = a.pre + (long long)s * kHistBins;
+                w.sx = (int64_t)w.pre[kHistBins - 1].sum();
+            }
+            info[t] = w;
+        }
+        __syncthreads();
+        const int tasks = rb * a.E, per = kRowThreads / lp;  // tasks at a time
+        const int ms = min(M, kRowPairs) | 1;                // odd row stride: no bank conflicts
+        for (int b0 = 0; b0 < tasks; b0 += per) {
+            const int task = b0 + t / lp, part = t % lp;
+            const int e = task / rb, rr = task % rb;  // a radius's rows on consecutive lanes
+            const int c = c0 + (k0 + rr) / a.K;
+            const double ev = task < tasks ? (double)a.eps[(long long)e * a.C + c] : 0.0;
             double best = __builtin_inf();
             int bm = M;  // no multiplier yet: loses every comparison below
-            for (int m0 = 0; m0 < M; m0 += kMinChunk) {
-                const int mc = min(kMinChunk, M - m0);
-                if (e0 == 0 || M > kMinChunk) {  // else the one chunk is still staged
-                    __builtin_amdgcn_wave_barrier();  // the last chunk's reads come first
-                    for (int i = lane; i < mc; i += 64)
-                        q[i] = make_double2(__ddiv_rn(row[m0 + i], N), (double)lam[m0 + i]);
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                }
-                for (int i = part; i < mc; i += 1 << lp) {
-                    const double2 v = q[i];
-                    const double J = __dadd_rn(__dmul_rn(v.y, ev), v.x);
-                    if (J < best) {
-                        best = J;
-                        bm = m0 + i;
+            for (int m0 = 0; m0 < M; m0 += kRowPairs) {
+                const int mc = min(kRowPairs, M - m0);
+                if (b0 == 0 || M > kRowPairs) {  // else the rows are still staged
+                    for (int i = t; i < mc; i += kRowThreads) s_lam[i] = a.lam[m0 + i];
+                    double *S = a.S + row0 * M + m0;  // (RB = 1 when M > kRowPairs)
+                    if (b0 > 0 || m0 > 0) load(S, rb * mc);
+                    int r = t / mc, m = t % mc;  // row and multiplier of entry i
+                    const int dr = kRowThreads / mc, dm = kRowThreads % mc;
+#pragma unroll
+                    for (int u = 0; u < kPer; ++u) {
+                        const int i = t + u * kRowThreads;
+                        if (i >= rb * mc) break;
+                        if (kFinish && b0 == 0) {
+                            v[u] = finish_pair(info[r], a.lam[m0 + m], __double_as_longlong(v[u]));
+                            S[i] = v[u];
+                        }
+                        // (a table from outside may hold anything: only a plain value takes the
+                        // short division)
+                        const uint32_t ex = ((uint32_t)__double2hiint(v[u]) >> 20) & 0x7ffu;
+                        q[r * ms + m] = kFinish || ex - 100u < 1800u
+                                            ? div_by(v[u], info[r].N, info[r].rN)
+                                            : __ddiv_rn(v[u], info[r].N);
+                        m += dm;
+                        r += dr;
+                        if (m >= mc) {
+                            m -= mc;
+                            ++r;
+                        }
                     }
+                    __syncthreads();
                 }
+                if (task < tasks)
+                    for (int m = part; m < mc; m += lp) {
+                        const double J = __dadd_rn(__dmul_rn((double)s_lam[m], ev), q[rr * ms + m]);
+                        if (J < best) {
+                            best = J;
+                            bm = m0 + m;
+                        }
+                    }
+                if (M > kRowPairs) __syncthreads();  // the next chunk overwrites the stage
             }
-            for (int d = (1 << lp) >> 1; d >= 1; d >>= 1) {
+            for (int d = lp >> 1; d >= 1; d >>= 1) {
                 const double ob = __shfl_xor(best, d, 64);
                 const int om = __shfl_xor(bm, d, 64);
                 if (ob < best || (ob == best && om < bm)) {
@@ -701,23 +755,27 @@ __global__ __launch_bounds__(64 * kMinWaves) void min_over_lambda_kernel(
                     bm = om;
                 }
             }
-            if (part == 0 && e < E) {
-                const long long o = ((long long)e * C + c) * K + k;
-                W[o] = best;
-                if (m_star) m_star[o] = bm;
+            if (part == 0 && task < tasks) {
+                const long long o = ((long long)e * a.C + c) * a.K + (k0 + rr) % a.K;
+                a.W[o] = best;
+                if (a.m_star) a.m_star[o] = bm;
             }
         }
+        __syncthreads();  // the next rows overwrite the stage
     }
 }
 
-hipError_t launch_min_over_lambda(const double *S, const int64_t *offsets, const int32_t *seg,
-                                  const float *lam, const float *eps, int E, int C, int K, int M,
-                                  double *W, int32_t *m_star, hipStream_t st)
+hipError_t launch_row_min(const RowMinArgs &a, bool finish, int num_cu, hipStream_t st)
 {
-    const long long n = (long long)C * K;
-    const long long blocks = std::min((n + kMinWaves - 1) / kMinWaves, kMaxGridBlocks);
-    hipLaunchKernelGGL(min_over_lambda_kernel, dim3((unsigned)blocks),
-                       dim3(64 * kMinWaves), 0, st, S, offsets, seg, lam, eps, E, C, K, M, W, m_star);
+    // whole rows up to the stage's pairs, but at least two blocks per compute unit
+    const long long rows = (long long)a.C * a.K;
+    const int RB = (int)std::max(1LL, std::min({(long long)kRowPairs / a.M, (long long)kRowMax,
+                                                rows / (2 * num_cu)}));
+    int lp = 64;
+    while (lp > 1 && (long long)RB * a.E * lp > kRowThreads) lp >>= 1;
+    const long long blocks = std::min((rows + RB - 1) / RB, kMaxGridBlocks);
+    hipLaunchKernelGGL(finish ? row_min_kernel<true> : row_min_kernel<false>,
+                       dim3((unsigned)blocks), dim3(kRowThreads), 0, st, a, RB, lp);
     return hipGetLastError();
 }
 

@@ -85,9 +85,12 @@ struct PrefixEntry {
 };
 
 // ---- dense epilogue ------------------------------------------------------------
-// S from the dense kernel's sums and the segments' prefix entries
-// (pre: [S][kHistBins], from launch_counts), written over R as doubles.
-struct DenseFinishArgs {
+// W[e,c,k] = min_m RN(RN(lam_m eps[e,c]) + RN(S[c,k,m] / N_c)) and the lowest m
+// (m_star may be null), for the table's rows.  With `finish`, S holds the dense
+// kernel's sums and is overwritten by the exact S from them and the segments'
+// prefix entries (pre: [S][kHistBins], from launch_counts); without it S is read
+// only and L, eta, c_p, c_w and pre are not used.
+struct RowMinArgs {
     const int64_t *offsets;
     const int32_t *seg;
     const int32_t *L;
@@ -95,15 +98,14 @@ struct DenseFinishArgs {
     const float *lam;
     const float *c_p;
     const float *c_w;
+    const float *eps;
     const PrefixEntry *pre;
-    int C, K, M;
-    unsigned long long *R;
+    int E, C, K, M;
+    double *S;
+    double *W;
+    int32_t *m_star;
 };
-hipError_t launch_dense_finish(const DenseFinishArgs &a, hipStream_t st);
-// W[e,c,k] = min_m RN(RN(lam_m eps[e,c]) + RN(S[c,k,m] / N_c)), lowest m
-hipError_t launch_min_over_lambda(const double *S, const int64_t *offsets, const int32_t *seg,
-                                  const float *lam, const float *eps, int E, int C, int K, int M,
-                                  double *W, int32_t *m_star, hipStream_t st);
+hipError_t launch_row_min(const RowMinArgs &a, bool finish, int num_cu, hipStream_t st);
 
 // ---- rows: the parts the samples are counted in ---------------------------------
 constexpr int kQTop = 32768;              // largest sample value, 2^15

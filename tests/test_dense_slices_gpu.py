@@ -3,7 +3,10 @@ for bit against the oracle: tables of one pair, of one pair less and more than a
 tile of each shape (512 to 8,192 pairs), class sizes around the staging buffer
 (16,384 samples) and the sixteens of a step, more unequal classes than one wave
 looks through at once (64), a class of one sample beside long ones, and sums of
-one slice (stored) as well as of several (added).
+one slice (stored) as well as of several (added).  The pass over the table's rows
+at its edges: rows longer than its stage (2,048 multipliers), more rows than a
+block takes, and more (radius, row) tasks than a block has lanes.  W, m_star and
+the optimum are checked with S.
 """
 import numpy as np
 import pytest
@@ -22,7 +25,7 @@ def ctx(dev):
     c.close()
 
 
-def _check(ctx, dev, sizes, K, M, L=32768, seg=None):
+def _check(ctx, dev, sizes, K, M, L=32768, seg=None, E=1):
     import torch
     import paper_2607_16892_amd as dro
     rng = np.random.default_rng(K * M + len(sizes))
@@ -33,7 +36,7 @@ def _check(ctx, dev, sizes, K, M, L=32768, seg=None):
     w = Workload("slices", C, off, None if seg is None else np.asarray(seg, np.int32), xi,
                  np.full(C, L, np.int32), eta_grid(K, L), lam_grid(M),
                  _f32([choice[c % 4][0] for c in range(C)]),
-                 _f32([choice[c % 4][1] for c in range(C)]), 1, _f32(rng.uniform(0, 50, C)))
+                 _f32([choice[c % 4][1] for c in range(C)]), E, _f32(rng.uniform(0, 50, E * C)))
     print(f"[gpu] slices: {C} classes, K={K} M={M}, {off[-1]} samples", flush=True)
     prob = dro.Problem.from_workload(w, dev)
     r = dro.dro_cost_eval(ctx, prob, torch.from_numpy(w.eps).to(dev))
@@ -44,6 +47,11 @@ def _check(ctx, dev, sizes, K, M, L=32768, seg=None):
     W, m = oracle.W_table(w, S)
     assert np.array_equal(r["W"].cpu().numpy().view(np.uint64), W.view(np.uint64))
     assert np.array_equal(r["m_star"].cpu().numpy(), m)
+    a = dro.dro_argmin_reservation(ctx, prob, torch.from_numpy(w.eps).to(dev), r["S"])
+    torch.cuda.synchronize()
+    k, ws = oracle.argmin(W)
+    assert np.array_equal(a["k_star"].cpu().numpy(), k)
+    assert np.array_equal(a["W_star"].cpu().numpy().view(np.uint64), ws.view(np.uint64))
 
 
 @pytest.mark.parametrize("K,M", [(1, 1), (1, 511), (64, 8), (27, 19), (32, 32), (25, 41),
@@ -64,3 +72,9 @@ def test_more_unequal_classes_than_a_wave_holds(ctx, dev):
     sizes[64] = 60_000
     _check(ctx, dev, sizes, 7, 11)
     _check(ctx, dev, sizes[60:70], 20, 30, seg=[c % 10 for c in range(70)])
+
+
+@pytest.mark.parametrize("K,M,E", [(3, 2047, 2), (3, 2048, 9), (2, 2049, 9), (2, 5000, 300),
+                                   (300, 1, 7), (130, 3, 70), (700, 2, 300), (65, 32, 5)])
+def test_rows_and_radii_around_the_stage(ctx, dev, K, M, E):
+    _check(ctx, dev, (40, 7, 300), K, M, E=E)
