@@ -1012,7 +1012,7 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
     const bool packed = packed_rows(rows);
     const size_t need = rup(ckm * 8) + cost_eval_scratch_bytes(p, rows, packed) +
-                        rup((size_t)C * p->K * 8) + rup((size_t)C * 4);
+                        rup((size_t)C * p->K * 8) + rup((size_t)C * p->K * 4) + rup((size_t)C * 4);
     rc = ensure_ws(ctx, need, st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
@@ -1020,6 +1020,7 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     double *S = ar.take<double>(ckm);
     const CountBufs cb = take_counts(ar, p, rows, packed, ctx->num_cu);
     double *W = ar.take<double>((size_t)C * p->K);
+    int32_t *best = ar.take<int32_t>((size_t)C * p->K);
     int32_t *kcur = ar.take<int32_t>(C);
     uint32_t *claim = ar.take<uint32_t>(dense_claim_words(C, p->K, p->M));
 
@@ -1028,8 +1029,8 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     HIPCHK(launch_prefix_select(p->offsets, p->seg, p->c_p, p->c_w, cb.pre, C, out->q_value, st));
     rc = run_dense(ctx, p, 1, eps, S, cb.pre, staged_plan(ctx, p), claim, W, nullptr, st);
     if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(kcur, k_prev, sizeof(int32_t) * C, hipMemcpyDeviceToDevice, st));
-    HIPCHK(launch_bcd_sweep(W, p->eta, C, p->K, grp->G, grp->cap, grp->conc, grp->kappa, kcur,
+    HIPCHK(launch_best_upto(W, C, p->K, best, st));
+    HIPCHK(launch_bcd_sweep(W, best, p->eta, C, p->K, grp->G, grp->cap, grp->conc, grp->kappa, k_prev, kcur,
                             out->k_next, out->W_star, out->feasible, out->usage, st));
     return DRO_OK;
 }
@@ -1126,37 +1127,27 @@ long long count_configs(dro_ctx *ctx, const dro_service *v, hipStream_t st)
 
 size_t config_bytes(int C, int G, int J, long long nz)
 {
-    const long long nb = (nz + 255) / 256;
-    return rup(config_pre_doubles(C, G) * 8) + rup((size_t)G * 4) + rup((size_t)(G + 1) * (J + 1) * 8) +
-           rup((size_t)G * 4) + rup((size_t)nb * 8) * 3 + 3 * rup(8) + rup(4 * 8);
+    const size_t nb = (size_t)config_parts(nz);
+    return rup(config_pre_doubles(C, G) * 8) + rup(config_pre_ints(C, G) * 4) +
+           rup((size_t)G * (J + 1) * 8) + rup((size_t)G * 4) + rup((size_t)(G + 1) * (J + 1) * 8) +
+           rup(nb * 8) * 3 + 3 * rup(8);
 }
-
-struct ConfigBufs {
-    double *pre_d;
-    int32_t *route, *gpus;
-    long long *ways;
-    double *part_obj;
-    long long *part_rank, *part_feas;
-    double *best_obj;
-    long long *best_rank, *n_feas;
-    int32_t *flag;
-};
 
 ConfigBufs take_config(Arena &ar, int C, int G, int J, long long nz)
 {
-    const long long nb = (nz + 255) / 256;
+    const size_t nb = (size_t)config_parts(nz);
     ConfigBufs b;
     b.pre_d = ar.take<double>(config_pre_doubles(C, G));
-    b.route = ar.take<int32_t>(G);
-    b.ways = ar.take<long long>((size_t)(G + 1) * (J + 1));
+    b.pre_i = ar.take<int32_t>(config_pre_ints(C, G));
+    b.wt = ar.take<double>((size_t)G * (J + 1));
     b.gpus = ar.take<int32_t>(G);
+    b.ways = ar.take<long long>((size_t)(G + 1) * (J + 1));
     b.part_obj = ar.take<double>(nb);
     b.part_rank = ar.take<long long>(nb);
     b.part_feas = ar.take<long long>(nb);
     b.best_obj = ar.take<double>(1);
     b.best_rank = ar.take<long long>(1);
     b.n_feas = ar.take<long long>(1);
-    b.flag = ar.take<int32_t>(8);
     return b;
 }
 
@@ -1228,14 +1219,13 @@ int bcd_routing_lp(dro_ctx *ctx, int32_t C, const dro_service *svc, const double
         return fail(ctx, DRO_EINVAL, "a routing-LP argument is NULL");
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    const int G = svc->G, m = 2 * C + G;
-    rc = ensure_ws(ctx, rup(lp1_tableau_doubles(C, G) * 8) + rup((size_t)m * 4), st);
+    const int G = svc->G;
+    rc = ensure_ws(ctx, rup(lp1_work_doubles(C, G) * 8), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
-    double *work = ar.take<double>(lp1_tableau_doubles(C, G));
-    int32_t *basis = ar.take<int32_t>(m);
-    HIPCHK(launch_lp1(svc_args(svc, C), Wc, T, Wq, z, eta_c, delta, work, basis, max_pivots(C, G),
-                      pi, lp_objective, info, st));
+    double *work = ar.take<double>(lp1_work_doubles(C, G));
+    HIPCHK(launch_lp1(svc_args(svc, C), Wc, T, Wq, z, eta_c, delta, work, max_pivots(C, G), pi,
+                      lp_objective, info, st));
     return DRO_OK;
 }
 
@@ -1289,11 +1279,12 @@ int bcd_config_search(dro_ctx *ctx, int32_t C, const dro_service *svc, const dou
     const ConfigBufs b = take_config(ar, C, G, J, nz);
     rc = upload_configs(ctx, b, G, J, st);
     if (rc) return rc;
-    HIPCHK(launch_config_search(svc_args(svc, C), nz, b.gpus, b.ways, Wc, T, ET2, pi, eta_c, delta,
-                                b.pre_d, b.route, b.part_obj, b.part_rank, b.part_feas, z, nullptr,
-                                nullptr, best_objective ? best_objective : b.best_obj,
+    const SvcArgs s = svc_args(svc, C);
+    HIPCHK(launch_config_prep(s, T, ET2, pi, eta_c, delta, b, st));
+    HIPCHK(launch_config_search(s, nz, Wc, b, z, nullptr, nullptr,
+                                best_objective ? best_objective : b.best_obj,
                                 best_rank ? (long long *)best_rank : b.best_rank,
-                                n_feasible ? (long long *)n_feasible : b.n_feas, b.flag, st));
+                                n_feasible ? (long long *)n_feasible : b.n_feas, nullptr, st));
     return DRO_OK;
 }
 
@@ -1312,7 +1303,7 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
         return fail(ctx, DRO_EINVAL, "max_outer and max_inner must be positive");
     ENTER_DEVICE(ctx);
     hipStream_t st = (hipStream_t)stream;
-    const int C = p->C, G = svc->G, K = p->K, J = svc->J, CG = C * G, m = 2 * C + G;
+    const int C = p->C, G = svc->G, K = p->K, J = svc->J, CG = C * G;
     const long long nz = count_configs(ctx, svc, st);
     if (nz < 0) return fail(ctx, DRO_EHIP, "stream synchronisation failed");
     if (nz > kMaxConfigs) return fail(ctx, DRO_ELIMIT, "%lld configurations exceed 2^32", nz);
@@ -1322,8 +1313,8 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
     const bool packed = packed_rows(rows);
     const size_t need = counts_bytes(p, rows, packed) + rup((size_t)rows.rows * sizeof(RowMoments)) +
                         rup((size_t)C * K * 8) + rup((size_t)C * K * 4) +
-                        4 * rup((size_t)C * 8) + rup(lp1_tableau_doubles(C, G) * 8) +
-                        rup((size_t)m * 4) + 4 * rup((size_t)CG * 8) + 2 * rup((size_t)CG) +
+                        4 * rup((size_t)C * 8) + rup(lp1_work_doubles(C, G) * 8) +
+                        4 * rup((size_t)CG * 8) + 2 * rup((size_t)CG) +
                         7 * rup((size_t)G * 8) + 5 * rup((size_t)C * 8) +
                         config_bytes(C, G, J, nz) + rup(64);
     rc = ensure_ws(ctx, need, st);
@@ -1337,16 +1328,14 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
     int32_t *mstar = ar.take<int32_t>((size_t)C * K);
     int64_t *cnt = ar.take<int64_t>(C), *sum = ar.take<int64_t>(C), *ssq = ar.take<int64_t>(C);
     int32_t *xmax = ar.take<int32_t>(C);
-    double *work = ar.take<double>(lp1_tableau_doubles(C, G));
-    int32_t *basis = ar.take<int32_t>(m);
+    double *work = ar.take<double>(lp1_work_doubles(C, G));
     double *T = ar.take<double>(CG), *ET2 = ar.take<double>(CG), *pi_new = ar.take<double>(CG);
     double *conc = ar.take<double>(CG);
-    uint8_t *d_new = ar.take<uint8_t>(CG), *feas = ar.take<uint8_t>(C);
-    double *Wq = ar.take<double>(G), *cap = ar.take<double>(G), *lpobj = ar.take<double>(1);
-    double *Wq_blk = ar.take<double>(G);
+    uint8_t *d_new = ar.take<uint8_t>(CG);
+    double *Wq = ar.take<double>(G), *cap = ar.take<double>(G);
     double *Wc = ar.take<double>(C);
     int32_t *eta_c = ar.take<int32_t>(C), *k_new = ar.take<int32_t>(C);
-    int32_t *ctl = ar.take<int32_t>(8);  // converge flag, lp pivots, lp status
+    int32_t *ctl = ar.take<int32_t>(8);  // Block 1's rounds, pivots, status, feasibility; change flag
     const ConfigBufs cb = take_config(ar, C, G, J, nz);
     rc = upload_configs(ctx, cb, G, J, st);
     if (rc) return rc;
@@ -1355,62 +1344,56 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
     HIPCHK(launch_counts(p->offsets, p->xi, p->S, vb, st));
     HIPCHK(launch_exact_table(p->offsets, p->seg, p->L, p->eta, p->lam, p->c_p, p->c_w, eps, nullptr,
                               vb.pre, 1, C, K, p->M, W, mstar, nullptr, nullptr, nullptr, st));
+    HIPCHK(launch_best_upto(W, C, K, mstar, st));  // (over the multipliers, which are not needed)
     HIPCHK(launch_moments(p->offsets, p->seg, p->xi, p->S, C, rows, rm, cnt, sum, ssq, xmax, p->eta,
                           K, k, st));
     HIPCHK(launch_service_times(s, cnt, sum, ssq, T, ET2, st));
-    HIPCHK(launch_fill_u32(reinterpret_cast<uint32_t *>(pi), 2LL * CG, 0u, st));
-    HIPCHK(launch_zero_u8(delta, CG, st));
-
     int outer = 0, inner = 0, pivots = 0, status = 0;
-    const int mp = max_pivots(C, G);
+    Block1Args b1{};
+    b1.W = W;
+    b1.best = mstar;
+    b1.eta = p->eta;
+    b1.K = K;
+    b1.T = T;
+    b1.ET2 = ET2;
+    b1.k = k;
+    b1.pi = pi;
+    b1.z = z;
+    b1.delta = delta;
+    b1.d_new = d_new;
+    b1.pi_new = pi_new;
+    b1.k_new = k_new;
+    b1.Wc = Wc;
+    b1.eta_c = eta_c;
+    b1.Wq = Wq;
+    b1.cap = cap;
+    b1.conc = conc;
+    b1.work = work;
+    b1.b = cb;
+    b1.ctl = ctl;
+    b1.max_inner = max_inner;
+    b1.max_pivots = max_pivots(C, G);
+    b1.tol = kPiTol;
     for (int it = 0; it < max_outer; ++it) {
         ++outer;
-        bool converged = false;
-        // the wait is linearised once per Block 1, at the state entering it
-        HIPCHK(launch_gather(W, p->eta, k, C, K, Wc, eta_c, st));
-        HIPCHK(launch_state(s, T, ET2, pi, z, eta_c, delta, Wq_blk, cap, conc, nullptr, st));
-        for (int jt = 0; jt < max_inner; ++jt) {
-            ++inner;
-            HIPCHK(launch_gather(W, p->eta, k, C, K, Wc, eta_c, st));
-            HIPCHK(launch_lp1(s, Wc, T, Wq_blk, z, eta_c, delta, work, basis, mp, pi_new, lpobj,
-                              ctl + 1, st));
-            HIPCHK(launch_state(s, T, ET2, pi_new, z, eta_c, delta, Wq, cap, conc, nullptr, st));
-            HIPCHK(launch_sweep(W, p->eta, C, K, G, conc, cap, svc->kappa, k, k_new, feas, st));
-            HIPCHK(launch_converge(C, G, kPiTol, k_new, k, pi_new, pi, ctl, st));
-            int32_t h[3];
-            HIPCHK(hipMemcpyAsync(h, ctl, sizeof(h), hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
-            pivots += h[1];
-            if (h[2] == 1) status |= 1;
-            if (h[2] == 2) status |= 2;
-            if (h[2] == 3) status |= 4;
-            if (h[0]) {
-                converged = true;
-                break;
-            }
-        }
-        if (!converged) status |= 16;
-        // Block 2, then Block 3 with the new delta
-        HIPCHK(launch_gather(W, p->eta, k, C, K, Wc, eta_c, st));
-        HIPCHK(launch_state(s, T, ET2, pi, z, eta_c, delta, Wq, cap, conc, nullptr, st));
-        HIPCHK(launch_cache(conc, CG, d_new, st));
-        HIPCHK(launch_config_search(s, nz, cb.gpus, cb.ways, Wc, T, ET2, pi, eta_c, d_new, cb.pre_d,
-                                    cb.route, cb.part_obj, cb.part_rank, cb.part_feas, z, d_new,
-                                    delta, cb.best_obj, cb.best_rank, cb.n_feas, cb.flag, st));
-        int32_t changed = 0;
-        HIPCHK(hipMemcpyAsync(&changed, cb.flag, sizeof(changed), hipMemcpyDeviceToHost, st));
+        b1.first = it == 0;
+        // Blocks 1 and 2, then Block 3 with the new delta
+        HIPCHK(launch_block1(s, b1, st));
+        HIPCHK(launch_config_search(s, nz, Wc, cb, z, d_new, delta, cb.best_obj, cb.best_rank,
+                                    cb.n_feas, ctl + 4, st));
+        // (if the loop ends here, the objective at the state reached is the one returned)
+        HIPCHK(launch_state_objective(s, T, ET2, pi, z, eta_c, delta, Wc, cb, objective, st));
+        int32_t h[5];
+        HIPCHK(hipMemcpyAsync(h, ctl, sizeof(h), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
-        if (!changed) break;
+        inner += h[0];
+        pivots += h[1];
+        status |= h[2];
+        if (h[3]) status &= ~8;
+        else status |= 8;
+        if (!h[4]) break;
         if (it == max_outer - 1) status |= 32;
     }
-    HIPCHK(launch_gather(W, p->eta, k, C, K, Wc, eta_c, st));
-    HIPCHK(launch_state_objective(s, T, ET2, pi, z, eta_c, delta, Wc, cb.pre_d, cb.route,
-                                  objective, st));
-    std::vector<uint8_t> fh(C);
-    HIPCHK(hipMemcpyAsync(fh.data(), feas, C, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    for (int c = 0; c < C; ++c)
-        if (!fh[c]) status |= 8;
     info[0] = outer;
     info[1] = inner;
     info[2] = pivots;

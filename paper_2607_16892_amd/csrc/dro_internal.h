@@ -207,12 +207,14 @@ hipError_t launch_baselines(int C, const int64_t *count, const int64_t *sum, con
                             int32_t *mean_r, int32_t *lp_r, int32_t *block_r, hipStream_t st);
 
 // ---- block step ----------------------------------------------------------------
-// The block step's Gauss-Seidel sweep over the exact W [C][K] (one radius row),
-// kcur [C] the state entering it (updated in place).
-hipError_t launch_bcd_sweep(const double *W, const int32_t *eta, int C, int K, int G,
-                            const float *cap, const float *conc, float kappa, int32_t *kcur,
-                            int32_t *k_next, double *W_star, uint8_t *feasible, double *usage,
-                            hipStream_t st);
+// best[c,k] = the lowest argmin of W[c, 0 .. k] (int32 [C][K])
+hipError_t launch_best_upto(const double *W, int C, int K, int32_t *best, hipStream_t st);
+// The block step's Gauss-Seidel sweep over the exact W [C][K] (one radius row) and
+// its best_upto, k_prev [C] the state entering it; kcur: [C] scratch.
+hipError_t launch_bcd_sweep(const double *W, const int32_t *best, const int32_t *eta, int C, int K,
+                            int G, const float *cap, const float *conc, float kappa,
+                            const int32_t *k_prev, int32_t *kcur, int32_t *k_next, double *W_star,
+                            uint8_t *feasible, double *usage, hipStream_t st);
 
 // ---- serving model: routing LP, prefix caching, configuration search -------------
 struct SvcArgs {
@@ -231,37 +233,73 @@ hipError_t launch_service_times(const SvcArgs &s, const int64_t *count, const in
 hipError_t launch_state(const SvcArgs &s, const double *T, const double *ET2, const double *pi,
                         const int32_t *z, const int32_t *eta_c, const uint8_t *delta, double *Wq,
                         double *cap, double *conc, double *mem, hipStream_t st);
-hipError_t launch_gather(const double *W, const int32_t *eta, const int32_t *k, int C, int K,
-                         double *Wc, int32_t *eta_c, hipStream_t st);
 hipError_t launch_cache(const double *conc, int n, uint8_t *delta, hipStream_t st);
-hipError_t launch_zero_u8(uint8_t *p, int n, hipStream_t st);
-// doubles of the LP1 work area (tableau and pivot column)
-size_t lp1_tableau_doubles(int C, int G);
+// doubles of the LP1 work area (tableau, pivot column and row, basis)
+size_t lp1_work_doubles(int C, int G);
 // allow lp1_kernel its dynamic LDS (once per device)
 hipError_t lp1_prepare();
 hipError_t launch_lp1(const SvcArgs &s, const double *Wc, const double *T, const double *Wq,
                       const int32_t *z, const int32_t *eta_c, const uint8_t *delta, double *work,
-                      int32_t *basis, int max_pivots, double *pi_out, double *obj_out,
-                      int32_t *info, hipStream_t st);
+                      int max_pivots, double *pi_out, double *obj_out, int32_t *info,
+                      hipStream_t st);
 hipError_t launch_sweep(const double *W, const int32_t *eta, int C, int K, int G,
                         const double *conc, const double *cap, double kappa, const int32_t *k_in,
                         int32_t *k_out, uint8_t *feasible, hipStream_t st);
-hipError_t launch_converge(int C, int G, double tol, const int32_t *k_new, int32_t *k,
-                           const double *pi_new, double *pi, int32_t *flag, hipStream_t st);
-// doubles of the z-independent sums of the configuration search
+// Scratch of the configuration search: the z-independent sums and routing entries,
+// the waits per configuration and count, the count table of the ranks and the
+// blocks' results.
+struct ConfigBufs {
+    double *pre_d;   // [config_pre_doubles]
+    int32_t *pre_i;  // [config_pre_ints]
+    double *wt;      // [G][J + 1]
+    int32_t *gpus;   // [G] tau pp
+    long long *ways; // [G + 1][J + 1]
+    double *part_obj;
+    long long *part_rank, *part_feas;  // [config_parts] each
+    double *best_obj;
+    long long *best_rank, *n_feas;
+};
 size_t config_pre_doubles(int C, int G);
-hipError_t launch_config_search(const SvcArgs &s, long long nz, const int32_t *gpus,
-                                const long long *ways, const double *Wc, const double *T,
-                                const double *ET2, const double *pi, const int32_t *eta_c,
-                                const uint8_t *delta_eval, double *pre_d, int32_t *pre_route,
-                                double *part_obj, long long *part_rank, long long *part_feas,
-                                int32_t *z, const uint8_t *delta_new, uint8_t *delta,
-                                double *best_obj, long long *best_rank, long long *n_feasible,
-                                int32_t *flag, hipStream_t st);
+size_t config_pre_ints(int C, int G);
+// blocks of the search over nz configurations
+long long config_parts(long long nz);
+hipError_t launch_config_prep(const SvcArgs &s, const double *T, const double *ET2, const double *pi,
+                              const int32_t *eta_c, const uint8_t *delta, const ConfigBufs &b,
+                              hipStream_t st);
+// after launch_config_prep (or launch_block1) on the same buffers
+hipError_t launch_config_search(const SvcArgs &s, long long nz, const double *Wc,
+                                const ConfigBufs &b, int32_t *z, const uint8_t *delta_new,
+                                uint8_t *delta, double *best_obj, long long *best_rank,
+                                long long *n_feasible, int32_t *flag, hipStream_t st);
+// Blocks 1 and 2 of one outer iteration of Alg. 1 and the sums of Block 3.
+struct Block1Args {
+    const double *W;      // [C][K]
+    const int32_t *best;  // its launch_best_upto
+    const int32_t *eta;   // [K]
+    int K;
+    const double *T, *ET2;
+    int32_t *k;           // [C] in and out
+    double *pi;           // [C * G] in and out
+    const int32_t *z;
+    uint8_t *delta;       // [C * G] the caching entering (zeroed with pi when first)
+    uint8_t *d_new;       // the caching of Block 2
+    double *pi_new;
+    int32_t *k_new;
+    double *Wc;           // W and eta at the reservations leaving
+    int32_t *eta_c;
+    double *Wq, *cap, *conc;
+    double *work;         // [lp1_work_doubles]
+    ConfigBufs b;
+    int32_t *ctl;         // out: rounds, pivots, status bits (1, 2, 4, 16 of dro_bcd_solve),
+                          // 1 if the last sweep found every class a feasible reservation
+    int max_inner, max_pivots, first;
+    double tol;
+};
+hipError_t launch_block1(const SvcArgs &s, const Block1Args &a, hipStream_t st);
 hipError_t launch_state_objective(const SvcArgs &s, const double *T, const double *ET2,
                                   const double *pi, const int32_t *z, const int32_t *eta_c,
-                                  const uint8_t *delta, const double *Wc, double *pre_d,
-                                  int32_t *pre_route, double *out, hipStream_t st);
+                                  const uint8_t *delta, const double *Wc, const ConfigBufs &b,
+                                  double *out, hipStream_t st);
 
 // ---- validation ----------------------------------------------------------------
 hipError_t launch_seg_minmax(const int64_t *offsets, const int32_t *xi, int S, long long max_seg,

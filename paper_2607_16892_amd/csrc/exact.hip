@@ -15,6 +15,7 @@
 
 #include "dro_internal.h"
 #include "fixed.h"
+#include "sweep.h"
 #include "wave.h"
 
 namespace dro {
@@ -571,108 +572,105 @@ hipError_t launch_class_quantile(const int64_t *offsets, const int32_t *seg, con
 }
 
 // ------------------------------------------------------------ block step ----
-// Grid indices arriving from the caller (k_prev) are clamped into [0, K).
-__device__ __forceinline__ int clampk(int k, int K) { return k < 0 ? 0 : (k >= K ? K - 1 : k); }
+// best[c, k] = the lowest k' <= k with the smallest W[c, k'] (K - 1 where no value
+// is below infinity): one block per class, a run of consecutive points per thread,
+// the runs' minima scanned over the block.
+constexpr int kBestThreads = 256;
 
-// Capacity bound of class c (the memory-capacity constraint of Sec. 3.4), then the largest admissible k.
-// The Gauss-Seidel sweep of the block step, one workgroup: for c = 0..C-1 in
-// order, thread 0 forms the capacity bound of class c from the other classes'
-// current grid points (fp64, no contraction, ascending class order), then the
-// block takes the lowest argmin of the exact W[c, 0..kmax_c] (lowest k on
-// equal values), which updates k[c] before the next class.  kcur[C] holds the
-// state entering the sweep and is updated in place.
-constexpr int kSweepThreads = 1024;
-
-__global__ __launch_bounds__(kSweepThreads) void bcd_sweep_kernel(
-    const double *W, const int32_t *eta, int C, int K, int G, const float *cap, const float *conc,
-    float kappa, int32_t *kcur, int32_t *k_next, double *W_star, uint8_t *feasible,
-    double *usage)
+__global__ __launch_bounds__(kBestThreads) void best_upto_kernel(const double *W, int K,
+                                                                 int32_t *best)
 {
-    __shared__ int s_kmax;
-    __shared__ double sw[kSweepThreads / 64];
-    __shared__ int sk[kSweepThreads / 64];
+    __shared__ double sw[kBestThreads / 64];
+    __shared__ int sk[kBestThreads / 64];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const double onek = __dadd_rn(1.0, (double)kappa);
-    for (int c = 0; c < C; ++c) {
-        if (t == 0) {
-            double bound = __builtin_inf();
-            for (int g = 0; g < G; ++g) {
-                const double u = (double)conc[c * G + g];
-                if (!(u > 0.0)) continue;
-                double sum = 0.0;
-                for (int c2 = 0; c2 < C; ++c2) {
-                    if (c2 == c) continue;
-                    sum = __dadd_rn(sum, __dmul_rn((double)conc[c2 * G + g],
-                                                   (double)eta[clampk(kcur[c2], K)]));
-                }
-                const double other = __dmul_rn(onek, sum);
-                const double b = __ddiv_rn(__dsub_rn((double)cap[g], other), __dmul_rn(onek, u));
-                bound = b < bound ? b : bound;
-            }
-            // eta ascending: the largest k with eta[k] <= bound, or none
-            int km = -1, lo = 0, hi = K - 1;
-            while (lo <= hi) {
-                const int mid = (lo + hi) / 2;
-                if ((double)eta[mid] <= bound) {
-                    km = mid;
-                    lo = mid + 1;
-                } else {
-                    hi = mid - 1;
-                }
-            }
-            feasible[c] = km >= 0 ? 1 : 0;
-            s_kmax = km >= 0 ? km : 0;
+    const double *w = W + (long long)blockIdx.x * K;
+    int32_t *o = best + (long long)blockIdx.x * K;
+    const int per = (K + kBestThreads - 1) / kBestThreads;
+    const int k0 = min(t * per, K), k1 = min(k0 + per, K);
+    double bw = __builtin_inf();
+    int bk = 0x7fffffff;
+    for (int k = k0; k < k1; ++k)
+        if (w[k] < bw) {
+            bw = w[k];
+            bk = k;
         }
-        __syncthreads();
-        const int kmax = s_kmax;
-        const double *w = W + (long long)c * K;
-        double bw = __builtin_inf();
-        int bk = 0x7fffffff;
-        for (int k = t; k <= kmax; k += kSweepThreads)
-            if (w[k] < bw) {  // k ascending per thread: its first minimiser
-                bw = w[k];
-                bk = k;
-            }
-        for (int d = 32; d > 0; d >>= 1) {
-            const double w2 = __shfl_xor(bw, d, 64);
-            const int k2 = __shfl_xor(bk, d, 64);
-            if (w2 < bw || (w2 == bw && k2 < bk)) {
-                bw = w2;
-                bk = k2;
-            }
+    // the minimum of the runs before this one, the earlier among equals
+    for (int d = 1; d < 64; d <<= 1) {
+        const double w2 = __shfl_up(bw, d, 64);
+        const int k2 = __shfl_up(bk, d, 64);
+        if (lane >= d && !(bw < w2)) {
+            bw = w2;
+            bk = k2;
         }
-        if (lane == 0) {
-            sw[wave] = bw;
-            sk[wave] = bk;
-        }
-        __syncthreads();
-        if (t == 0) {
-            for (int i = 1; i < kSweepThreads / 64; ++i)
-                if (sw[i] < bw || (sw[i] == bw && sk[i] < bk)) {
-                    bw = sw[i];
-                    bk = sk[i];
-                }
-            kcur[c] = bk;
-            W_star[c] = bw;
-        }
-        __syncthreads();
     }
-    for (int g = t; g < G; g += kSweepThreads) {
-        double sum = 0.0;
-        for (int c = 0; c < C; ++c)
-            sum = __dadd_rn(sum, __dmul_rn((double)conc[c * G + g], (double)eta[clampk(kcur[c], K)]));
-        usage[g] = __dmul_rn(onek, sum);
+    if (lane == 63) {
+        sw[wave] = bw;
+        sk[wave] = bk;
     }
-    for (int c = t; c < C; c += kSweepThreads) k_next[c] = clampk(kcur[c], K);
+    const double ew = __shfl_up(bw, 1, 64);
+    const int ek = __shfl_up(bk, 1, 64);
+    __syncthreads();
+    double cw = __builtin_inf();
+    int ck = 0x7fffffff;
+    for (int i = 0; i < wave; ++i)
+        if (sw[i] < cw) {
+            cw = sw[i];
+            ck = sk[i];
+        }
+    if (lane > 0 && ew < cw) {
+        cw = ew;
+        ck = ek;
+    }
+    for (int k = k0; k < k1; ++k) {
+        if (w[k] < cw) {
+            cw = w[k];
+            ck = k;
+        }
+        o[k] = min(ck, K - 1);
+    }
 }
 
-hipError_t launch_bcd_sweep(const double *W, const int32_t *eta, int C, int K, int G,
-                            const float *cap, const float *conc, float kappa, int32_t *kcur,
-                            int32_t *k_next, double *W_star, uint8_t *feasible, double *usage,
-                            hipStream_t st)
+hipError_t launch_best_upto(const double *W, int C, int K, int32_t *best, hipStream_t st)
 {
-    hipLaunchKernelGGL(bcd_sweep_kernel, dim3(1), dim3(kSweepThreads), 0, st, W, eta, C, K, G, cap,
-                       conc, kappa, kcur, k_next, W_star, feasible, usage);
+    hipLaunchKernelGGL(best_upto_kernel, dim3((unsigned)C), dim3(kBestThreads), 0, st, W, K, best);
+    return hipGetLastError();
+}
+
+// The Gauss-Seidel sweep of the block step, one wave (sweep.h), then the values at
+// the new grid points and every group's usage.
+__global__ __launch_bounds__(64) void bcd_sweep_kernel(const double *W, const int32_t *best,
+                                                       const int32_t *eta, int C, int K, int G,
+                                                       const float *cap, const float *conc,
+                                                       float kappa, const int32_t *k_prev,
+                                                       int32_t *kcur, int32_t *k_next,
+                                                       double *W_star, uint8_t *feasible,
+                                                       double *usage)
+{
+    __shared__ double lds[kSweepLds];
+    const int t = threadIdx.x;
+    const double onek = __dadd_rn(1.0, (double)kappa);
+    sweep_wave(best, eta, C, K, G, conc, cap, onek, 0.0, k_prev, kcur, lds,
+               [&](int c, int, bool feas) { feasible[c] = feas ? 1 : 0; });
+    wave_sync();
+    for (int g = t; g < G; g += 64) {
+        double sum = 0.0;
+        for (int c = 0; c < C; ++c)
+            sum = __dadd_rn(sum, __dmul_rn((double)conc[(long long)c * G + g], (double)eta[kcur[c]]));
+        usage[g] = __dmul_rn(onek, sum);
+    }
+    for (int c = t; c < C; c += 64) {
+        k_next[c] = kcur[c];
+        W_star[c] = W[(long long)c * K + kcur[c]];
+    }
+}
+
+hipError_t launch_bcd_sweep(const double *W, const int32_t *best, const int32_t *eta, int C, int K,
+                            int G, const float *cap, const float *conc, float kappa,
+                            const int32_t *k_prev, int32_t *kcur, int32_t *k_next, double *W_star,
+                            uint8_t *feasible, double *usage, hipStream_t st)
+{
+    hipLaunchKernelGGL(bcd_sweep_kernel, dim3(1), dim3(64), 0, st, W, best, eta, C, K, G, cap, conc,
+                       kappa, k_prev, kcur, k_next, W_star, feasible, usage);
     return hipGetLastError();
 }
 

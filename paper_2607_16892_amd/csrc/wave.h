@@ -50,4 +50,71 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t x, int l)
     return (uint64_t)lane_value((uint32_t)x, l) | ((uint64_t)lane_value((uint32_t)(x >> 32), l) << 32);
 }
 
+// x of the lane a DPP control names, or the lane's own x where there is none
+template <int kCtrl, int kRows = 0xf> __device__ __forceinline__ int dpp_or_own(int x)
+{
+    return __builtin_amdgcn_update_dpp(x, x, kCtrl, kRows, 0xf, false);
+}
+template <int kCtrl, int kRows = 0xf> __device__ __forceinline__ double dpp_or_own(double x)
+{
+    return __hiloint2double(dpp_or_own<kCtrl, kRows>(__double2hiint(x)),
+                            dpp_or_own<kCtrl, kRows>(__double2loint(x)));
+}
+__device__ __forceinline__ double lane_value(double x, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                            __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
+// Makes what a wave's lanes wrote visible to its other lanes.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Minimum over a wave; every lane gets it.  Every lane is active.
+__device__ __forceinline__ double wave_min(double x)
+{
+    auto take = [&](double y) { x = y < x ? y : x; };
+    take(dpp_or_own<0x111>(x));
+    take(dpp_or_own<0x112>(x));
+    take(dpp_or_own<0x114>(x));
+    take(dpp_or_own<0x118>(x));
+    take(dpp_or_own<0x142, 0xa>(x));
+    take(dpp_or_own<0x143, 0xc>(x));
+    return lane_value(x, 63);
+}
+
+// Lexicographic minimum of (key, idx) over a wave (smallest key, then the
+// smallest idx), carrying aux along; every lane gets it.  Every lane is active.
+struct KeyIdx {
+    double key;
+    int idx, aux;
+};
+
+template <int kCtrl, int kRows> __device__ __forceinline__ void min_key_step(KeyIdx &m)
+{
+    const double k = dpp_or_own<kCtrl, kRows>(m.key);
+    const int i = dpp_or_own<kCtrl, kRows>(m.idx), a = dpp_or_own<kCtrl, kRows>(m.aux);
+    const bool less = k < m.key || (k == m.key && i < m.idx);
+    m.key = less ? k : m.key;
+    m.idx = less ? i : m.idx;
+    m.aux = less ? a : m.aux;
+}
+
+__device__ __forceinline__ KeyIdx wave_min_key(double k, int i, int a)
+{
+    KeyIdx m{k, i, a};
+    min_key_step<0x111, 0xf>(m);  // row_shr:1, 2, 4, 8: lane 15 of a row has its minimum
+    min_key_step<0x112, 0xf>(m);
+    min_key_step<0x114, 0xf>(m);
+    min_key_step<0x118, 0xf>(m);
+    min_key_step<0x142, 0xa>(m);  // row_bcast:15 into rows 1 and 3
+    min_key_step<0x143, 0xc>(m);  // row_bcast:31 into rows 2 and 3: lane 63 has it all
+    return KeyIdx{lane_value(m.key, 63), __builtin_amdgcn_readlane(m.idx, 63),
+                  __builtin_amdgcn_readlane(m.aux, 63)};
+}
+
 }  // namespace dro
