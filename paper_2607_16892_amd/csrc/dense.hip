@@ -622,16 +622,6 @@ struct RowInfo {
     bool upper;
 };
 
-// q = RN(S / N) from r = RN(1 / N): q0 = RN(S r) is within one unit of S / N, its
-// residual S - q0 N is exact in an fma, and one more fma rounds the quotient
-// correctly (Markstein; N is an integer below 2^27, so its significand is not all
-// ones; S is finite and far from underflow).
-__device__ __forceinline__ double div_by(double S, double N, double rN)
-{
-    const double q0 = __dmul_rn(S, rN);
-    return __fma_rn(__fma_rn(-q0, N, S), rN, q0);
-}
-
 // S of one pair from its sum of |x - t|.  With c_w <= c_p, t = floor(Nu / De)
 // and Rt = sum relu(x - t): S = N B - A1 sum x + De Rt - (Nu - De t) #{x > t};
 // the mirror image otherwise.

@@ -28,51 +28,6 @@ __device__ __forceinline__ int seg_of_x(const int32_t *seg, int c) { return seg 
         if (e_ != hipSuccess) return e_;             \
     } while (0)
 
-// One (class, grid point) of the exact table.  For 0 <= x, eta <= L the three
-// candidates of Step 4 reduce to the larger of two lines, B - a1 x and
-// C - a2 (L - x) with B = c_w eta, C = c_p (L - eta), a1 = min(g, c_w),
-// a2 = min(g, c_p); the first is the larger up to t = floor((B - C + a2 L) /
-// (a1 + a2)).  All integers in units of 2^-33.
-struct TableRow {
-    const PrefixEntry *pre;  // of the class's segment
-    int64_t B, C, CP, CW;
-    uint64_t SX;             // sum of the samples
-    uint32_t N;
-    int L, tmax;
-};
-
-__device__ __forceinline__ PrefixEntry row_split(const TableRow &r, int64_t A1, int64_t A2)
-{
-    const int t = floor_div_clamped(r.B - r.C + A2 * r.L, A1 + A2, -1, r.tmax);
-    const PrefixEntry e = r.pre[max(t, 0)];
-    return t >= 0 ? e : PrefixEntry::of(0u, 0ull);
-}
-
-// S at multiplier G: with cnt and sum over the samples <= t,
-//   S = B cnt - a1 sum + (C - a2 L)(N - cnt) + a2 (sum_all - sum),
-// every term an exact integer (the sum is non-negative, as phi is).
-__device__ __forceinline__ double row_S(const TableRow &r, int64_t G)
-{
-    const int64_t A1 = G < r.CW ? G : r.CW, A2 = G < r.CP ? G : r.CP;
-    const PrefixEntry e = row_split(r, A1, A2);
-    const __int128 S = mul_i64_u31(r.B, e.cnt) + mul_i64_u31(r.C - A2 * r.L, r.N - e.cnt) +
-                       mul_u43((uint64_t)A2, r.SX) - mul_u43((uint64_t)(A1 + A2), e.sum());
-    return fix128_to_double((uint64_t)S, (uint64_t)((unsigned __int128)S >> 64));
-}
-
-// N times a subgradient of gamma -> gamma eps + S(gamma) / N at multiplier G:
-// eN = RN(eps N) less the slopes of the active lines, an exact integer below
-// 2^42 (a sample where the lines meet may take either line's slope).
-__device__ __forceinline__ double row_slope(const TableRow &r, int64_t G, double eN)
-{
-    const int64_t A1 = G < r.CW ? G : r.CW, A2 = G < r.CP ? G : r.CP;
-    const PrefixEntry e = row_split(r, A1, A2);
-    const int64_t below = G < r.CW ? (int64_t)e.sum() : 0;
-    const int64_t above =
-        G < r.CP ? (int64_t)(r.N - e.cnt) * r.L - (int64_t)(r.SX - e.sum()) : 0;
-    return eN - (double)(below + above);
-}
-
 __global__ void fill_u32_kernel(uint32_t *p, long long n, uint32_t v)
 {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -991,7 +946,65 @@ hipError_t launch_counts(const int64_t *offsets, const int32_t *xi, int S, const
     return hipGetLastError();
 }
 
-// One thread per (e, c, k): W = min over m of J_m = RN(RN(lam_m eps) +
+// One (class, grid point) of the exact table.  For 0 <= x, eta <= L the three
+// candidates of Step 4 reduce to the larger of two lines, B - a1 x and
+// C - a2 (L - x) with B = c_w eta, C = c_p (L - eta), a1 = min(g, c_w),
+// a2 = min(g, c_p); the first is the larger up to t = floor((B - C + a2 L) /
+// (a1 + a2)).  All integers in units of 2^-33.
+struct TableRow {
+    const PrefixEntry *pre;  // of the class's segment
+    int64_t B, C, CP, CW;
+    uint64_t SX;             // sum of the samples
+    uint32_t N;
+    int L, tmax;
+    double Nd, rN;           // N and RN(1 / N)
+};
+
+// What a row needs of one multiplier, the same for every grid point of a class.
+struct __attribute__((aligned(16))) TableLam {
+    int64_t A2L, A12;  // a2 L and a1 + a2
+    double rcp;        // an estimate of 1 / (a1 + a2)
+    int64_t A2;
+};
+
+__device__ __forceinline__ TableLam table_lam(int64_t G, int64_t CP, int64_t CW, int L)
+{
+    const int64_t A1 = G < CW ? G : CW, A2 = G < CP ? G : CP;
+    return TableLam{A2 * L, A1 + A2, __builtin_amdgcn_rcp((double)(A1 + A2)), A2};
+}
+
+// the prefix entry at t
+__device__ __forceinline__ PrefixEntry row_split(const TableRow &r, const TableLam &g)
+{
+    const int t = floor_div_clamped(r.B - r.C + g.A2L, g.A12, g.rcp, -1, r.tmax);
+    const PrefixEntry e = r.pre[max(t, 0)];
+    return t >= 0 ? e : PrefixEntry::of(0u, 0ull);
+}
+
+// RN(RN(S) / N) at a multiplier: with cnt and sum over the samples <= t,
+//   S = B cnt - a1 sum + (C - a2 L)(N - cnt) + a2 (sum_all - sum),
+// every term an exact integer (the sum is non-negative, as phi is).
+__device__ __forceinline__ double row_mean(const TableRow &r, const TableLam &g,
+                                           const PrefixEntry &e)
+{
+    const __int128 S = mul_i64_u31(r.B, e.cnt) + mul_i64_u31(r.C - g.A2L, r.N - e.cnt) +
+                       mul_u43((uint64_t)g.A2, r.SX) - mul_u43((uint64_t)g.A12, e.sum());
+    return div_by(fix128_to_double((uint64_t)S, (uint64_t)((unsigned __int128)S >> 64)), r.Nd, r.rN);
+}
+
+// The slopes of the active lines of S at a multiplier: less RN(eps N), it is N
+// times a subgradient of gamma -> gamma eps + S(gamma) / N, with the sign changed;
+// an exact integer below 2^42 (a sample where the lines meet may take either
+// line's slope), not increasing in the multiplier.
+__device__ __forceinline__ double row_lines(const TableRow &r, bool below_cw, bool below_cp,
+                                            const PrefixEntry &e)
+{
+    const int64_t below = below_cw ? (int64_t)e.sum() : 0;
+    const int64_t above = below_cp ? (int64_t)(r.N - e.cnt) * r.L - (int64_t)(r.SX - e.sum()) : 0;
+    return (double)(below + above);
+}
+
+// One thread per (c, k), for `per` radii: W = min over m of J_m = RN(RN(lam_m eps) +
 // RN(RN(S_m) / N)) and the lowest m attaining it, without evaluating every m.
 // J without its roundings, j(gamma) = gamma eps + S(gamma) / N, is convex (Step 4
 // is a supremum of lines in gamma), so a binary search on the sign of its
@@ -1005,35 +1018,40 @@ hipError_t launch_counts(const int64_t *offsets, const int32_t *xi, int S, const
 // the same integer, so J ties and b is the lower index.  Where the rise is too
 // small the neighbours are evaluated, one after the other, until it is not: the
 // same W and the same lowest m as a scan over all m.
-// About 9 subgradients and 2 values of S instead of M = 256 values: 16 x 2048
-// grid points of 1e6 samples 83 -> 10 us, 128 classes x 1024 points x 16 radii
-// 248 -> 83 us (M = 128).  Few rows are bound by the search's chain of dependent
-// instructions and loads, many by the integer arithmetic (three subgradients in
-// flight per step, on quarters of the range, took 12.7 us for the 10.2).
-// The multipliers are staged in LDS; a grid that is not ascending (outside the
-// contract) is scanned.
+// About 9 subgradients and 2 values of S instead of M values.  A block holds one
+// class: what depends on class and multiplier (the fixed-point slopes, a2 L, the
+// reciprocal of the division) is staged in LDS once, the prefix entry met by a
+// subgradient serves the value there, and the next radius starts from the bracket
+// of the one before (its two subgradients less their own eps N) in doubling steps.
+// Bound by the search's chain of dependent loads and instructions and, with many
+// rows, by the gathers of prefix entries (64 lines a wave) and the 64-bit integer
+// arithmetic: 128 classes x 1024 points x 16 radii (M = 128) 45 us, 73 with one
+// radius a block, 82 with a thread per (e, c, k) and nothing staged; 16 x 2048
+// points of 1e6 samples (M = 256, one radius) 10 us, as before.
+// kStaged: M <= kTableLam; beyond, those terms are computed where they are used.
+// A grid of multipliers that is not ascending (outside the contract) is scanned.
 constexpr int kTableThreads = 128;
-constexpr int kTableLam = 2048;  // multipliers staged per block
+constexpr int kTableLam = 1024;  // multipliers staged per block (36 KB)
+// a block takes as many radii as leave this many blocks (16 radii on 1,024 blocks'
+// worth of rows: 69 us with 1,024, 53 with 2,048, 52 with 4,096, 55 with 8,192)
+constexpr int kTableBlocks = 4096;
 
+template <bool kStaged>
 __global__ __launch_bounds__(kTableThreads) void exact_table_kernel(
     const int64_t *offsets, const int32_t *seg, const int32_t *L_, const int32_t *eta_,
     const float *lam, const float *c_p, const float *c_w, const float *eps,
-    const PrefixEntry *pre, long long rows, int C, int K, int M, double *W, int32_t *m_star)
+    const PrefixEntry *pre, long long units, int per, int E, int C, int K, int M, double *W,
+    int32_t *m_star)
 {
-    __shared__ float s_lam[kTableLam];
-    bool up = true;
-    for (int m = threadIdx.x; m < M; m += kTableThreads) {
-        const float l = lam[m];
-        if (m < kTableLam) s_lam[m] = l;
-        if (m > 0 && !(l > lam[m - 1])) up = false;
-    }
-    const bool ascending = __syncthreads_and(up);
-    auto lam_at = [&](int m) { return m < kTableLam ? s_lam[m] : lam[m]; };
-    for (long long i = (long long)blockIdx.x * kTableThreads + threadIdx.x; i < rows;
-         i += (long long)gridDim.x * kTableThreads) {
-        const int k = (int)(i % K);
-        const long long ec = i / K;
-        const int c = (int)(ec % C);
+    extern __shared__ __attribute__((aligned(16))) char table_lds[];
+    TableLam *const s_tab = reinterpret_cast<TableLam *>(table_lds);
+    float *const s_lam = reinterpret_cast<float *>(s_tab + (kStaged ? M : 0));
+    __shared__ int s_mw, s_mp;  // the multipliers below c_w and below c_p
+    const int t = threadIdx.x, chunks = (K + kTableThreads - 1) / kTableThreads;
+    for (long long unit = blockIdx.x; unit < units; unit += gridDim.x) {
+        const long long rest = unit / chunks;
+        const int k = (int)(unit - rest * chunks) * kTableThreads + t;
+        const int eg = (int)(rest / C), c = (int)(rest - (long long)eg * C);
         const int s = seg_of_x(seg, c);
         TableRow r;
         r.pre = pre + (long long)s * kHistBins;
@@ -1043,78 +1061,141 @@ __global__ __launch_bounds__(kTableThreads) void exact_table_kernel(
         r.tmax = min(r.L, kHistBins - 1);
         r.CP = fix33(c_p[c]);
         r.CW = fix33(c_w[c]);
-        const int64_t eta = eta_[k];
-        r.B = r.CW * eta;
-        r.C = r.CP * (r.L - eta);
-        const double ev = (double)eps[ec], Nd = (double)r.N, eN = __dmul_rn(ev, Nd);
-        auto slope = [&](int m) { return row_slope(r, fix33(lam_at(m)), eN); };
-        auto value = [&](int m) {
-            const float l = lam_at(m);
-            return __dadd_rn(__dmul_rn((double)l, ev), __ddiv_rn(row_S(r, fix33(l)), Nd));
-        };
-        // m and all beyond it are settled: the rise over the gap to the next
-        // multiplier, of slope h at a point of value J
-        auto clear = [&](double h, double J, int m0) {
-            const double gap = (double)lam_at(m0 + 1) - (double)lam_at(m0);
-            return h * gap > Nd * fabs(J) * 0x1p-44 && h > fabs(eN) * 0x1p-50;
-        };
-        double best = __builtin_inf();
-        int bm = M;
-        if (ascending) {
+        r.Nd = (double)r.N;
+        r.rN = __ddiv_rn(1.0, r.Nd);
+        if (t == 0) s_mw = s_mp = 0;
+        __syncthreads();
+        bool up = true;
+        for (int m = t; m < M; m += kTableThreads) {
+            const float l = lam[m], next = m + 1 < M ? lam[m + 1] : INFINITY;
+            if (!(l < next)) up = false;
+            const int64_t G = fix33(l);
+            if (kStaged) {
+                s_lam[m] = l;
+                s_tab[m] = table_lam(G, r.CP, r.CW, r.L);
+            }
+            const int64_t G1 = m + 1 < M ? fix33(next) : INT64_MAX;
+            if (G < r.CW && G1 >= r.CW) s_mw = m + 1;
+            if (G < r.CP && G1 >= r.CP) s_mp = m + 1;
+        }
+        const bool ascending = __syncthreads_and(up);
+        const int mw = s_mw, mp = s_mp;
+        __syncthreads();  // (the next unit sets them again)
+        if (k < K) {
+            const int64_t eta = eta_[k];
+            r.B = r.CW * eta;
+            r.C = r.CP * (r.L - eta);
+            auto lam_at = [&](int m) { return kStaged ? s_lam[m] : lam[m]; };
+            auto tab_at = [&](int m) {
+                return kStaged ? s_tab[m] : table_lam(fix33(lam[m]), r.CP, r.CW, r.L);
+            };
+            auto lines = [&](int m, const PrefixEntry &p) { return row_lines(r, m < mw, m < mp, p); };
             int a = -1, b = M;  // the slope is negative at a, not at b
-            double ha = 0.0, hb = 0.0;
-            while (b - a > 1) {
-                const int mid = (a + b) >> 1;
-                const double h = slope(mid);
-                if (h < 0.0) {
-                    a = mid;
-                    ha = h;
+            double da = 0.0, db = 0.0, qa = 0.0, qb = 0.0;  // their lines and means
+            PrefixEntry pa{}, pb{};
+            int step = 1;
+            for (int e = eg * per; e < min((eg + 1) * per, E); ++e) {
+                const long long ec = (long long)e * C + c;
+                const double ev = (double)eps[ec], eN = __dmul_rn(ev, r.Nd);
+                auto J_of = [&](int m, double q) {
+                    return __dadd_rn(__dmul_rn((double)lam_at(m), ev), q);
+                };
+                // m and all beyond it are settled: the rise over the gap to the next
+                // multiplier, of slope h at a point of value J
+                auto clear = [&](double h, double J, int m0) {
+                    const double gap = (double)lam_at(m0 + 1) - (double)lam_at(m0);
+                    return h * gap > r.Nd * fabs(J) * 0x1p-44 && h > fabs(eN) * 0x1p-50;
+                };
+                double best = __builtin_inf();
+                int bm = M;
+                if (ascending) {
+                    bool na = false, nb = false;
+                    const int a0 = a;
+                    int dir = 0;
+                    if (a >= 0 && !(eN - da < 0.0)) {
+                        b = a;
+                        db = da;
+                        qb = qa;
+                        a = -1;
+                        dir = -1;
+                    } else if (b < M && eN - db < 0.0) {
+                        a = b;
+                        da = db;
+                        qa = qb;
+                        b = M;
+                        dir = 1;
+                    }
+                    while (b - a > 1) {
+                        const int mid = dir == 0 ? (a + b) >> 1
+                                                 : (dir < 0 ? max(b - step, a + 1) : min(a + step, b - 1));
+                        const PrefixEntry p = row_split(r, tab_at(mid));
+                        const double d = lines(mid, p);
+                        if (eN - d < 0.0) {
+                            a = mid;
+                            da = d;
+                            pa = p;
+                            na = true;
+                            if (dir < 0) dir = 0;
+                            else step *= 2;
+                        } else {
+                            b = mid;
+                            db = d;
+                            pb = p;
+                            nb = true;
+                            if (dir > 0) dir = 0;
+                            else step *= 2;
+                        }
+                    }
+                    step = max(abs(a - a0), 1);
+                    double Ja = 0.0, Jb = 0.0;
+                    if (b < M) {
+                        if (nb) qb = row_mean(r, tab_at(b), pb);
+                        best = Jb = J_of(b, qb);
+                        bm = b;
+                    }
+                    if (a >= 0) {
+                        if (na) qa = row_mean(r, tab_at(a), pa);
+                        Ja = J_of(a, qa);
+                        if (Ja <= best) {
+                            best = Ja;
+                            bm = a;
+                        }
+                    }
+                    double h = eN - da;
+                    for (int m = a; m > 0 && !clear(-h, Ja, m - 1);) {
+                        const PrefixEntry p = row_split(r, tab_at(--m));
+                        h = eN - lines(m, p);
+                        Ja = J_of(m, row_mean(r, tab_at(m), p));
+                        if (Ja <= best) {
+                            best = Ja;
+                            bm = m;
+                        }
+                    }
+                    h = eN - db;
+                    for (int m = b; m < M - 1 && ev != 0.0 && !clear(h, Jb, m);) {
+                        const PrefixEntry p = row_split(r, tab_at(++m));
+                        h = eN - lines(m, p);
+                        Jb = J_of(m, row_mean(r, tab_at(m), p));
+                        if (Jb < best) {
+                            best = Jb;
+                            bm = m;
+                        }
+                    }
                 } else {
-                    b = mid;
-                    hb = h;
+                    for (int m = 0; m < M; ++m) {
+                        const TableLam g = tab_at(m);
+                        const double J = J_of(m, row_mean(r, g, row_split(r, g)));
+                        if (J < best) {
+                            best = J;
+                            bm = m;
+                        }
+                    }
                 }
-            }
-            double Ja = 0.0, Jb = 0.0;
-            if (b < M) {
-                best = Jb = value(b);
-                bm = b;
-            }
-            if (a >= 0) {
-                Ja = value(a);
-                if (Ja <= best) {
-                    best = Ja;
-                    bm = a;
-                }
-            }
-            while (a > 0 && !clear(-ha, Ja, a - 1)) {
-                --a;
-                ha = slope(a);
-                Ja = value(a);
-                if (Ja <= best) {
-                    best = Ja;
-                    bm = a;
-                }
-            }
-            while (b < M - 1 && ev != 0.0 && !clear(hb, Jb, b)) {
-                ++b;
-                hb = slope(b);
-                Jb = value(b);
-                if (Jb < best) {
-                    best = Jb;
-                    bm = b;
-                }
-            }
-        } else {
-            for (int m = 0; m < M; ++m) {
-                const double J = value(m);
-                if (J < best) {
-                    best = J;
-                    bm = m;
-                }
+                W[ec * K + k] = best;
+                m_star[ec * K + k] = bm;
             }
         }
-        W[i] = best;
-        m_star[i] = bm;
+        __syncthreads();  // the next unit reuses the LDS
     }
 }
 
@@ -1205,10 +1286,15 @@ hipError_t launch_exact_table(const int64_t *offsets, const int32_t *seg, const 
                               int32_t *m_star, int32_t *k_star, double *W_star, int32_t *m_at_star,
                               hipStream_t st)
 {
-    const long long rows = (long long)E * C * K;
-    const long long blocks = std::min((rows + kTableThreads - 1) / kTableThreads, kMaxGridBlocks);
-    hipLaunchKernelGGL(exact_table_kernel, dim3((unsigned)blocks), dim3(kTableThreads), 0, st, offsets, seg, L,
-                       eta, lam, c_p, c_w, eps, pre, rows, C, K, M, W, m_star);
+    // radii per block: blocks enough to fill the chip come first
+    const long long groups = (long long)C * ((K + kTableThreads - 1) / kTableThreads);
+    const int per = (int)std::min<long long>(E, std::max(1LL, groups * E / kTableBlocks));
+    const long long units = groups * ((E + per - 1) / per);
+    const bool staged = M <= kTableLam;
+    hipLaunchKernelGGL(staged ? exact_table_kernel<true> : exact_table_kernel<false>,
+                       dim3((unsigned)std::min(units, kMaxGridBlocks)), dim3(kTableThreads),
+                       staged ? (size_t)M * (sizeof(TableLam) + sizeof(float)) : 0, st, offsets, seg, L,
+                       eta, lam, c_p, c_w, eps, pre, units, per, E, C, K, M, W, m_star);
     HIPRET(hipGetLastError());
     if (k_star) HIPRET(launch_table_argmin(W, m_star, k_max, E, C, K, k_star, W_star, m_at_star, st));
     return hipGetLastError();

@@ -34,13 +34,28 @@ __device__ __forceinline__ int64_t floor_div(int64_t a, int64_t b)
 // floor(a / b) clamped to [lo, hi] for b > 0 and -2^16 < lo <= hi < 2^16: the
 // quotient by the reciprocal instruction (about 2^-26 relative, so within one of
 // the floor after the clamp) corrected once with the exact remainder.
-__device__ __forceinline__ int floor_div_clamped(int64_t a, int64_t b, int lo, int hi)
+__device__ __forceinline__ int floor_div_clamped(int64_t a, int64_t b, double rb, int lo, int hi)
 {
-    const double q = (double)a * __builtin_amdgcn_rcp((double)b);
+    const double q = (double)a * rb;
     int t = (int)floor(fmin(fmax(q, (double)lo), (double)hi));
     const int64_t r = a - b * t;
     t += r < 0 ? -1 : (r >= b ? 1 : 0);
     return t < lo ? lo : (t > hi ? hi : t);
+}
+
+__device__ __forceinline__ int floor_div_clamped(int64_t a, int64_t b, int lo, int hi)
+{
+    return floor_div_clamped(a, b, __builtin_amdgcn_rcp((double)b), lo, hi);
+}
+
+// q = RN(S / N) from r = RN(1 / N): q0 = RN(S r) is within one unit of S / N, its
+// residual S - q0 N is exact in an fma, and one more fma rounds the quotient
+// correctly (Markstein; N is an integer below 2^27, so its significand is not all
+// ones; S is finite and far from underflow).
+__device__ __forceinline__ double div_by(double S, double N, double rN)
+{
+    const double q0 = __dmul_rn(S, rN);
+    return __fma_rn(__fma_rn(-q0, N, S), rN, q0);
 }
 
 // a * b for a of 64 bits and b < 2^31, and for a, b < 2^43, exactly: two and
