@@ -50,6 +50,12 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t x, int l)
     return (uint64_t)lane_value((uint32_t)x, l) | ((uint64_t)lane_value((uint32_t)(x >> 32), l) << 32);
 }
 
+// x of lane kLane of each group of four lanes (all of them active)
+template <int kLane> __device__ __forceinline__ int quad_lane(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, kLane * 0x55, 0xf, 0xf, true);
+}
+
 // x of the lane a DPP control names, or the lane's own x where there is none
 template <int kCtrl, int kRows = 0xf> __device__ __forceinline__ int dpp_or_own(int x)
 {
