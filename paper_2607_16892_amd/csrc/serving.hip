@@ -156,8 +156,9 @@ __global__ void cache_kernel(const double *conc, int n, uint8_t *delta)
 // the tableau ((m + 1) x (n + m + 1) doubles, in LDS when it fits), the pivot
 // column, the scaled pivot row and the basis lie in `work`.
 // A pivot is latency: the first wave alone finds the entering column and the
-// leaving row (a reduced cost or a ratio or two per lane, then shuffles; a
-// block-wide reduction costs two barriers and a pass over the waves each), all
+// leaving row (four reduced costs in flight per lane, a ratio or two, then 32-bit
+// minima; a block-wide reduction costs two barriers and a pass over the waves
+// each), all
 // threads copy the pivot's column and scale its row once, then update a column of
 // every fourth row each.  15 pivots on 15 x 12 routings (43 x 238 doubles) take
 // 62 us with the rest of the kernel, 159 before (256 threads, block-wide
@@ -264,12 +265,18 @@ __device__ __forceinline__ void lp1_block(const SvcArgs &s, const double *Wc, co
             const bool bland = degenerate >= kLpDegenerateRun;
             double dmin = 0.0;
             int cand = 0x7fffffff;
-            for (int j = lane; j < nv + m; j += 64) {
-                const double d = tab[(long long)m * w + j];
-                if (d < -tol_d && (bland ? cand == 0x7fffffff : d < dmin)) {
-                    dmin = d;
-                    cand = j;
-                }
+            for (int j0 = lane; j0 < nv + m; j0 += 256) {  // four loads in flight
+                double d[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    d[q] = tab[(long long)m * w + min(j0 + 64 * q, nv + m - 1)];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (j0 + 64 * q < nv + m && d[q] < -tol_d &&
+                        (bland ? cand == 0x7fffffff : d[q] < dmin)) {
+                        dmin = d[q];
+                        cand = j0 + 64 * q;
+                    }
             }
             const int jin = wave_min_key(bland ? 0.0 : dmin, cand, 0).idx;
             int rsel = -1;
@@ -880,9 +887,9 @@ __device__ void gather_block(const double *W, const int32_t *eta, const int32_t 
 // steps: as launches of their own (six per round and seven more per iteration,
 // with a copy and a wait for the host per round) the launches and waits took
 // most of the time.  15 classes, 12 configurations,
-// K = 2048: 103 us for one round of 15 pivots and 195 for two, of which the LPs are
-// 62 and 124; the whole solve 600 to 4,500 us on eight instances, 1,570 to 10,740
-// before.
+// K = 2048: 98 us for one round of 15 pivots and 184 for two (103 and 195 while the
+// simplex's minima were fp64 steps that carried their index), the whole solve 600 to
+// 4,500 us on eight instances, 1,570 to 10,740 before.
 template <bool kLds>
 __global__ __launch_bounds__(kBlockThreads) void block1_kernel(SvcArgs s, Block1Args a)
 {

@@ -100,27 +100,32 @@ struct KeyIdx {
     int idx, aux;
 };
 
-template <int kCtrl, int kRows> __device__ __forceinline__ void min_key_step(KeyIdx &m)
+__device__ __forceinline__ uint32_t wave_min(uint32_t x)
 {
-    const double k = dpp_or_own<kCtrl, kRows>(m.key);
-    const int i = dpp_or_own<kCtrl, kRows>(m.idx), a = dpp_or_own<kCtrl, kRows>(m.aux);
-    const bool less = k < m.key || (k == m.key && i < m.idx);
-    m.key = less ? k : m.key;
-    m.idx = less ? i : m.idx;
-    m.aux = less ? a : m.aux;
+    auto take = [&](int y) { x = (uint32_t)y < x ? (uint32_t)y : x; };
+    take(dpp_or_own<0x111>((int)x));  // row_shr:1, 2, 4, 8: lane 15 of a row has its minimum
+    take(dpp_or_own<0x112>((int)x));
+    take(dpp_or_own<0x114>((int)x));
+    take(dpp_or_own<0x118>((int)x));
+    take(dpp_or_own<0x142, 0xa>((int)x));  // row_bcast:15 into rows 1 and 3
+    take(dpp_or_own<0x143, 0xc>((int)x));  // row_bcast:31 into rows 2 and 3: lane 63 has it all
+    return lane_value(x, 63);
 }
 
+// The key's bits as an unsigned integer in the key's order (-0 as 0), then three
+// 32-bit minima: its high half, the low half among the lanes that hold it, the idx
+// among those (idx >= 0).  One fp64 minimum that carries idx and aux along is some
+// ninety dependent instructions.
 __device__ __forceinline__ KeyIdx wave_min_key(double k, int i, int a)
 {
-    KeyIdx m{k, i, a};
-    min_key_step<0x111, 0xf>(m);  // row_shr:1, 2, 4, 8: lane 15 of a row has its minimum
-    min_key_step<0x112, 0xf>(m);
-    min_key_step<0x114, 0xf>(m);
-    min_key_step<0x118, 0xf>(m);
-    min_key_step<0x142, 0xa>(m);  // row_bcast:15 into rows 1 and 3
-    min_key_step<0x143, 0xc>(m);  // row_bcast:31 into rows 2 and 3: lane 63 has it all
-    return KeyIdx{lane_value(m.key, 63), __builtin_amdgcn_readlane(m.idx, 63),
-                  __builtin_amdgcn_readlane(m.aux, 63)};
+    const long long b = __double_as_longlong(k + 0.0);
+    const unsigned long long u = (unsigned long long)b ^ ((unsigned long long)(b >> 63) | (1ull << 63));
+    const uint32_t hi = (uint32_t)(u >> 32), lo = (uint32_t)u;
+    const uint32_t h = wave_min(hi), l = wave_min(hi == h ? lo : 0xffffffffu);
+    const bool least = hi == h && lo == l;
+    const uint32_t first = wave_min(least ? (uint32_t)i : 0xffffffffu);
+    const int owner = __builtin_ctzll(__ballot(least && (uint32_t)i == first));
+    return KeyIdx{lane_value(k, owner), (int)first, __builtin_amdgcn_readlane(a, owner)};
 }
 
 }  // namespace dro
