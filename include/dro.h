@@ -152,9 +152,9 @@ int dro_cost_eval(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *ep
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, results and errors as dro_cost_eval, except that S is
  * required (the dense sums accumulate in it) and the scratch (the staged
- * offsets and segment map, the value histogram, the prefix counts and sums,
- * the dense kernel's work counters, one per tile) comes from a static device array of DRO_NOALLOC_SCRATCH_BYTES instead of
- * the ctx workspace, so the call allocates nothing.  The scratch grows with
+ * offsets and segment map, the value counts, the prefix counts and sums,
+ * the dense kernel's work counters, one per tile) comes from a static device
+ * array of DRO_NOALLOC_SCRATCH_BYTES instead of the ctx workspace, so the call allocates nothing.  The scratch grows with
  * the number of sample segments, about 0.5 MB each: a problem that needs
  * more than the array (beyond about 60 segments) gets DRO_ELIMIT before any
  * work is enqueued.  Every call on one device shares that device's array and
@@ -186,9 +186,10 @@ int class_quantile(dro_ctx *ctx, const dro_problem *p, int32_t *q_value, int64_t
  * candidates of Step 4 reduce to the larger of two lines in x, so with the
  * per-segment counts and sums of the sample values every S[c,k,m] is a closed
  * form in 128-bit integers, and the dual is convex in the multiplier: O(N + L)
- * per segment plus O(log M) per (e,c,k), instead of O(N) per (c,k,m).  This is the production alternative to the dense
- * evaluation when only the results are needed (it does not evaluate every
- * per-sample term, so it is not the dense throughput measurement):
+ * per segment plus O(log M) per (e,c,k), instead of O(N) per (c,k,m).  This is
+ * the production alternative to the dense evaluation when only the results are
+ * needed (it does not evaluate every per-sample term, so it is not the dense
+ * throughput measurement):
  *   W[e,c,k], m_star[e,c,k] = exact-spec values (the expression of
  *                             dro_argmin_reservation for every k), lowest m
  *   k_star, W_star, m_at_star [E*C] = lowest-index optimum with k <= k_max[c]
