@@ -40,7 +40,9 @@
  *    (sizing the workspace and staging the offsets), class_quantile,
  *    dro_cost_eval and dro_argmin_reservation enqueue kernels only, with no
  *    allocation, host copy or memset, so a stream capture of them replays
- *    correctly.
+ *    correctly.  A replay uses the ctx's workspace and staged offsets as they
+ *    are then: after any call on that ctx with another problem or on another
+ *    stream, capture again.  (dro_cost_eval_noalloc has no such bond to its ctx.)
  *  - Exactness limits (DRO_ELIMIT when exceeded): 0 <= x, eta <= L <= 2^15,
  *    N_c <= 2^26 samples per class, every lam, c_p, c_w in [2^-10, 2^7];
  *    K <= 2^15 + 1 grid points, M <= 65536 multipliers, K * M < 2^31 pairs,
@@ -154,12 +156,15 @@ int dro_cost_eval(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *ep
  * required (the dense sums accumulate in it) and the scratch (the staged
  * offsets and segment map, the value counts, the prefix counts and sums,
  * the dense kernel's work counters, one per tile) comes from a static device
- * array of DRO_NOALLOC_SCRATCH_BYTES instead of the ctx workspace, so the call allocates nothing.  The scratch grows with
- * the number of sample segments, about 0.5 MB each: a problem that needs
- * more than the array (beyond about 60 segments) gets DRO_ELIMIT before any
- * work is enqueued.  Every call on one device shares that device's array and
- * leaves its contents behind; two calls that overlap on one device (from
- * different streams or host threads) race. */
+ * array of DRO_NOALLOC_SCRATCH_BYTES instead of the ctx workspace, so the call
+ * allocates nothing.  The scratch grows with the number of sample segments,
+ * about 0.5 MB each: a problem that needs more than the array (beyond about 60
+ * segments) gets DRO_ELIMIT before any work is enqueued.  Every call on one
+ * device shares that device's array and leaves its contents behind; two calls
+ * that overlap on one device (from different streams or host threads) race.
+ * The call enqueues kernels only, with the offsets and the segment map in their
+ * arguments, so a captured call needs no earlier call with the same problem,
+ * and its replays read nothing of the ctx or of the caller's host arrays. */
 int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
                           double *W, int32_t *m_star, double *S, dro_stream_t stream);
 

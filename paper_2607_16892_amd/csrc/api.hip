@@ -319,23 +319,21 @@ int stage_problem(dro_ctx *ctx, const dro_problem *p, hipStream_t st, dro_proble
 
 // The same into the arena, on every call (the no-allocation path: its static
 // array is shared by every ctx of the device); the row table only if `packed`.
+// Everything goes to the device in kernel arguments: a copy of host memory that a
+// stream capture records reads its source again at every replay, when the caller's
+// arrays may be gone and ctx->boff_h holds another problem's table.
 int stage_in_arena(dro_ctx *ctx, const dro_problem *p, Arena &ar, bool packed, hipStream_t st,
                    dro_problem *q, RowPlan *rows)
 {
     *q = *p;
-    const size_t ob = (size_t)(p->S + 1) * 8;
-    char *dst = ar.take<char>(stage_bytes(p));
-    HIPCHK(hipMemcpyAsync(dst, p->offsets_h, ob, hipMemcpyHostToDevice, st));
-    q->offsets = reinterpret_cast<int64_t *>(dst);
-    if (p->seg_h) {
-        HIPCHK(hipMemcpyAsync(dst + rup(ob), p->seg_h, (size_t)p->C * 4, hipMemcpyHostToDevice, st));
-        q->seg = reinterpret_cast<int32_t *>(dst + rup(ob));
-    }
-    if (packed && !rows->B) {
-        int64_t *boff = ar.take<int64_t>((size_t)p->S + 1);
-        HIPCHK(hipMemcpyAsync(boff, ctx->boff_h.data(), ob, hipMemcpyHostToDevice, st));
-        rows->boff = boff;
-    }
+    int64_t *off = ar.take<int64_t>((size_t)p->S + 1), *boff = nullptr;
+    int32_t *seg = p->seg_h ? ar.take<int32_t>(p->C) : nullptr;
+    if (packed && !rows->B) boff = ar.take<int64_t>((size_t)p->S + 1);
+    HIPCHK(launch_stage_args(p->offsets_h, boff ? ctx->boff_h.data() : nullptr, p->S, p->seg_h, p->C,
+                             off, boff, seg, st));
+    q->offsets = off;
+    q->seg = seg;
+    if (boff) rows->boff = boff;
     return DRO_OK;
 }
 
@@ -764,6 +762,8 @@ int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const f
         return fail(ctx, DRO_EHIP, "the scratch array's device address is unknown on device %d",
                     ctx->device);
     const size_t need = noalloc_need(p);
+    static_assert((kStageSegs + 1) * 16ull * kHistBins > DRO_NOALLOC_SCRATCH_BYTES,
+                  "the segments the array can hold fit the staging kernel's arguments");
     if (need > (size_t)DRO_NOALLOC_SCRATCH_BYTES)
         return fail(ctx, DRO_ELIMIT,
                     "the problem needs %zu bytes of scratch; the no-allocation array holds %zu",

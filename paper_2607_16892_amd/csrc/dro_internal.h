@@ -126,6 +126,13 @@ long long row_part_len(const int64_t *offsets_h, int S, int num_cu);
 inline long long row_parts(long long n, long long len) { return n <= len ? 1 : (n + len - 1) / len; }
 
 hipError_t launch_fill_u32(uint32_t *p, long long n, uint32_t v, hipStream_t st);
+// Writes offsets [S+1], the row table [S+1] (both pointers null: none) and the segment
+// map [C] (null: none) to the device, taking them from host memory in kernel arguments
+// before it returns.  S <= kStageSegs.
+constexpr int kStageSegs = 63;
+hipError_t launch_stage_args(const int64_t *offsets_h, const int64_t *boff_h, int S,
+                             const int32_t *seg_h, int C, int64_t *offsets, int64_t *boff,
+                             int32_t *seg, hipStream_t st);
 // allows the histogram and quantile kernels their 128 KB of dynamic LDS (once per device)
 hipError_t hist_prepare();
 

@@ -44,6 +44,51 @@ hipError_t launch_fill_u32(uint32_t *p, long long n, uint32_t v, hipStream_t st)
     return hipGetLastError();
 }
 
+// ------------------------------------------- staging in kernel arguments ----
+// One launch for the offsets, the row table and the first kStageClasses classes'
+// segments, one more for every further kStageClasses.
+constexpr int kStageClasses = 2048;
+struct StageArgs {
+    int64_t off[kStageSegs + 1];
+    int32_t row[kStageSegs + 1];
+    uint8_t seg[kStageClasses];
+};
+static_assert(sizeof(StageArgs) <= 3584 && kStageSegs < 256, "within a launch's 4 KB of arguments");
+
+__global__ void stage_args_kernel(StageArgs a, int entries, int classes, int64_t *offsets,
+                                  int64_t *boff, int32_t *seg)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < entries) {
+        offsets[t] = a.off[t];
+        if (boff) boff[t] = a.row[t];
+    }
+    if (t < classes) seg[t] = a.seg[t];
+}
+
+hipError_t launch_stage_args(const int64_t *offsets_h, const int64_t *boff_h, int S,
+                             const int32_t *seg_h, int C, int64_t *offsets, int64_t *boff,
+                             int32_t *seg, hipStream_t st)
+{
+    if (S > kStageSegs) return hipErrorInvalidValue;
+    StageArgs a{};
+    for (int s = 0; s <= S; ++s) {
+        a.off[s] = offsets_h[s];
+        if (boff_h) a.row[s] = (int32_t)boff_h[s];
+    }
+    int c0 = 0;
+    do {
+        const int n = seg_h ? std::min(C - c0, kStageClasses) : 0;
+        const int entries = c0 == 0 ? S + 1 : 0;
+        for (int i = 0; i < n; ++i) a.seg[i] = (uint8_t)seg_h[c0 + i];
+        hipLaunchKernelGGL(stage_args_kernel, dim3((unsigned)(std::max(entries, n) + 255) / 256),
+                           dim3(256), 0, st, a, entries, n, offsets, boff, seg ? seg + c0 : nullptr);
+        HIPRET(hipGetLastError());
+        c0 += n;
+    } while (seg_h && c0 < C);
+    return hipSuccess;
+}
+
 // Calls count(x) for every sample of xi[lo, hi) handed to this thread of a
 // kThreadsT-thread block: an unaligned head (up to the first 16-byte aligned
 // address), a 16-byte body and a tail.  In the body every thread keeps eight

@@ -8,6 +8,12 @@ Every replay is checked against the eager results, with eager calls of the
 same step between replays: a one-class workload, ragged aliased segments
 (one block per sample slice) and ratios-8x250k (the persistent grid that
 claims slices, whose claim counters a fill kernel in the graph clears).
+
+dro_cost_eval_noalloc enqueues kernels only on its first call too, and its
+replays depend on no host memory: it is captured without an earlier call on
+segments of unequal sizes (which are counted through a row table), and replayed
+after other unequal segments were evaluated on the same context, after the
+caller's host arrays were overwritten and after the context was closed.
 """
 import pytest
 
@@ -68,3 +74,54 @@ def test_captured_step_replays_bit_for_bit(dev, name):
             torch.cuda.synchronize()
             for k in out:
                 assert torch.equal(bits(out[k]), bits(ref[k])), f"eager after replay {rep}: {k}"
+
+
+@pytest.mark.parametrize("C,alias", [(3, False), (5, True), (4500, True)])
+def test_captured_noalloc_replays_without_its_host_arrays(dev, C, alias):
+    import torch
+    import paper_2607_16892_amd as dro
+    # three segments of 3, 1 and 5 parts, and others whose parts are 1, 13 and 1
+    w = random_workload(seed=62, C=C, N=(40_000, 3, 70_000), alias=alias, L=2000, K=13, M=7, E=2)
+    other = random_workload(seed=63, C=3, N=(90, 200_000, 1), L=2000, K=9, M=4, E=1)
+    print(f"[gpu] no-alloc graph: C={w.C} S={w.offsets.size - 1}", flush=True)
+
+    def outputs(w):
+        return dict(S=torch.empty((w.C, w.K, w.M), dtype=torch.float64, device=dev),
+                    W=torch.empty((w.E, w.C, w.K), dtype=torch.float64, device=dev),
+                    m_star=torch.empty((w.E, w.C, w.K), dtype=torch.int32, device=dev))
+
+    def run(ctx, prob, eps, out):
+        dro.dro_cost_eval_noalloc(ctx, prob, eps, out["S"], out["W"], out["m_star"])
+
+    ctx = dro.Context(dev.index or 0)
+    prob, prob2 = dro.Problem.from_workload(w, dev), dro.Problem.from_workload(other, dev)
+    eps, eps2 = (torch.from_numpy(x.eps.copy()).to(dev) for x in (w, other))
+    ref, ref2 = dro.dro_cost_eval(ctx, prob, eps), dro.dro_cost_eval(ctx, prob2, eps2)
+    out, out2 = outputs(w), outputs(other)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run(ctx, prob, eps, out)
+    torch.cuda.synchronize()
+
+    def replay(when):
+        for t in out.values():
+            t.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        for k in out:
+            assert torch.equal(out[k], ref[k]), f"{when}: {k} differs"
+
+    replay("first replay")
+    for _ in range(2):
+        run(ctx, prob2, eps2, out2)  # eager, with another row table
+        torch.cuda.synchronize()
+        for k in out2:
+            assert torch.equal(out2[k], ref2[k]), f"eager: {k} differs"
+        replay("after another problem")
+    prob.offsets_h[1:] = 1
+    if prob.seg_h is not None:
+        prob.seg_h[:] = 0
+    replay("after the host arrays changed")
+    ctx.close()
+    replay("after the context was closed")
