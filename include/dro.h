@@ -34,7 +34,10 @@
  *    is written; dro_last_error(ctx) holds the detail.
  *  - Hot calls check host-visible arguments only.  Device data (sample range,
  *    grid order, coefficient range) is checked by dro_validate; kernels never
- *    read outside the segments given by the offsets, whatever the data.
+ *    read outside the segments given by the offsets, whatever the data.  Where
+ *    no value of a minimum is below infinity (a radius or an S that is infinite
+ *    or NaN), W is infinity and the index the last one searched: m_star = M - 1,
+ *    k_star = min(k_max, K - 1), in a sweep the largest admissible k.
  *  - A ctx is not thread-safe: use one ctx per host thread / stream.
  *  - HIP graphs: once a call has run with the same problem on the same stream
  *    (sizing the workspace and staging the offsets), class_quantile,

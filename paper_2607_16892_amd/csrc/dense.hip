@@ -748,7 +748,7 @@ __global__ __launch_bounds__(kRowThreads) void row_min_kernel(RowMinArgs a, int 
             if (part == 0 && task < tasks) {
                 const long long o = ((long long)e * a.C + c) * a.K + (k0 + rr) % a.K;
                 a.W[o] = best;
-                if (a.m_star) a.m_star[o] = bm;
+                if (a.m_star) a.m_star[o] = min(bm, M - 1);  // (no J below infinity: the last)
             }
         }
         __syncthreads();  // the next rows overwrite the stage

@@ -566,8 +566,8 @@ hipError_t launch_class_quantile(const int64_t *offsets, const int32_t *seg, con
 }
 
 // ------------------------------------------------------------ block step ----
-// best[c, k] = the lowest k' <= k with the smallest W[c, k'] (K - 1 where no value
-// is below infinity): one block per class, a run of consecutive points per thread,
+// best[c, k] = the lowest k' <= k with the smallest W[c, k'] (k where no value is
+// below infinity): one block per class, a run of consecutive points per thread,
 // the runs' minima scanned over the block.
 constexpr int kBestThreads = 256;
 
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(kBestThreads) void best_upto_kernel(const double *W
             cw = w[k];
             ck = k;
         }
-        o[k] = min(ck, K - 1);
+        o[k] = min(ck, k);
     }
 }
 
@@ -1189,8 +1189,11 @@ __global__ __launch_bounds__(kTableThreads) void exact_table_kernel(
                     double Ja = 0.0, Jb = 0.0;
                     if (b < M) {
                         if (nb) qb = row_mean(r, tab_at(b), pb);
-                        best = Jb = J_of(b, qb);
-                        bm = b;
+                        Jb = J_of(b, qb);
+                        if (Jb < best) {
+                            best = Jb;
+                            bm = b;
+                        }
                     }
                     if (a >= 0) {
                         if (na) qa = row_mean(r, tab_at(a), pa);
@@ -1231,7 +1234,7 @@ __global__ __launch_bounds__(kTableThreads) void exact_table_kernel(
                     }
                 }
                 W[ec * K + k] = best;
-                m_star[ec * K + k] = bm;
+                m_star[ec * K + k] = min(bm, M - 1);  // (no J below infinity: the last)
             }
         }
         __syncthreads();  // the next unit reuses the LDS
@@ -1239,7 +1242,8 @@ __global__ __launch_bounds__(kTableThreads) void exact_table_kernel(
 }
 
 // Block per (e, c): lowest k <= kmax with the smallest W, and the values there
-// (the exact optimum over a W table whose entries are exact-spec values).  Bound
+// (the exact optimum over a W table whose entries are exact-spec values; kmax where
+// no entry is below infinity).  Bound
 // by latency: each thread loads four values at a time, then 32-bit minima within the
 // waves and one pass over their results (8,193 points of 42 rows: 5.6 us, 7.9 with
 // fp64 shuffles).
@@ -1287,6 +1291,7 @@ __device__ void table_argmin_row(const double *W, const int32_t *m_star, const i
                 bw = sw[i];
                 bk = sk[i];
             }
+        bk = min(bk, kmax);  // no W below infinity: the last point
         k_star[ec] = bk;
         W_star[ec] = bw;
         if (m_at_star) m_at_star[ec] = m_star[(long long)ec * K + bk];

@@ -442,7 +442,10 @@ __global__ __launch_bounds__(kBlockThreads) void sweep_kernel(
                                           lane < kBlockThreads / 64 ? sk[lane] : 0x7fffffff, 0);
             if (lane == 0) {
                 const bool feas = (double)eta[0] <= top;
-                k_out[c] = feas ? min(r.idx, K - 1) : 0;
+                int k = r.idx;
+                if (k > K - 1)  // no W below infinity: the last admissible point
+                    for (k = K - 1; k > 0 && !((double)eta[k] <= top);) --k;
+                k_out[c] = feas ? k : 0;
                 if (feasible) feasible[c] = feas ? 1 : 0;
             }
         }
