@@ -689,7 +689,8 @@ __global__ __launch_bounds__(kRowThreads) void row_min_kernel(RowMinArgs a, int 
         __syncthreads();
         const int tasks = rb * a.E, per = kRowThreads / lp;  // tasks at a time
         const int ms = min(M, kRowPairs) | 1;                // odd row stride: no bank conflicts
-        for (int b0 = 0; b0 < tasks; b0 += per) {
+        // (tasks reaches 2^31 - 1: the loop ends before b0 would pass it)
+        for (int b0 = 0;; b0 += per) {
             const int task = b0 + t / lp, part = t % lp;
             const int e = task / rb, rr = task % rb;  // a radius's rows on consecutive lanes
             const int c = c0 + (k0 + rr) / a.K;
@@ -750,6 +751,7 @@ __global__ __launch_bounds__(kRowThreads) void row_min_kernel(RowMinArgs a, int 
                 a.W[o] = best;
                 if (a.m_star) a.m_star[o] = min(bm, M - 1);  // (no J below infinity: the last)
             }
+            if (tasks - b0 <= per) break;
         }
         __syncthreads();  // the next rows overwrite the stage
     }
@@ -757,10 +759,11 @@ __global__ __launch_bounds__(kRowThreads) void row_min_kernel(RowMinArgs a, int 
 
 hipError_t launch_row_min(const RowMinArgs &a, bool finish, int num_cu, hipStream_t st)
 {
-    // whole rows up to the stage's pairs, but at least two blocks per compute unit
+    // whole rows up to the stage's pairs, but at least two blocks per compute unit (and
+    // (radius, row) tasks counted in 32 bits)
     const long long rows = (long long)a.C * a.K;
     const int RB = (int)std::max(1LL, std::min({(long long)kRowPairs / a.M, (long long)kRowMax,
-                                                rows / (2 * num_cu)}));
+                                                rows / (2 * num_cu), 0x7fffffffLL / a.E}));
     int lp = 64;
     while (lp > 1 && (long long)RB * a.E * lp > kRowThreads) lp >>= 1;
     const long long blocks = std::min((rows + RB - 1) / RB, kMaxGridBlocks);

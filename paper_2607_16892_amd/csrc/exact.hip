@@ -434,8 +434,8 @@ __global__ __launch_bounds__(kQThreads) void qselect_kernel(const int64_t *offse
                                                             const int64_t *boff, int C,
                                                             int32_t *q_value, int64_t *q_rank)
 {
-    for (int c = blockIdx.x; c < C; c += gridDim.x) {
-        qselect_class(offsets, seg, c_p, c_w, fine, coarse, B, boff, c, q_value, q_rank);
+    for (long long c = blockIdx.x; c < C; c += gridDim.x) {
+        qselect_class(offsets, seg, c_p, c_w, fine, coarse, B, boff, (int)c, q_value, q_rank);
         __syncthreads();
     }
 }
@@ -1133,7 +1133,8 @@ __global__ __launch_bounds__(kTableThreads) void exact_table_kernel(
             double da = 0.0, db = 0.0, qa = 0.0, qb = 0.0;  // their lines and means
             PrefixEntry pa{}, pb{};
             int step = 1;
-            for (int e = eg * per; e < min((eg + 1) * per, E); ++e) {
+            const int e1 = (int)min((long long)(eg + 1) * per, (long long)E);
+            for (int e = eg * per; e < e1; ++e) {
                 const long long ec = (long long)e * C + c;
                 const double ev = (double)eps[ec], eN = __dmul_rn(ev, r.Nd);
                 auto J_of = [&](int m, double q) {
@@ -1303,8 +1304,9 @@ __global__ __launch_bounds__(kArgThreads) void table_argmin_kernel(
     const double *W, const int32_t *m_star, const int32_t *k_max, int C, int K, int rows,
     int32_t *k_star, double *W_star, int32_t *m_at_star)
 {
-    for (int ec = blockIdx.x; ec < rows; ec += gridDim.x) {
-        table_argmin_row(W, m_star, k_max, C, K, ec, k_star, W_star, m_at_star);
+    // (rows reaches 2^31 - 1: the last step would pass the 32-bit range)
+    for (long long ec = blockIdx.x; ec < rows; ec += gridDim.x) {
+        table_argmin_row(W, m_star, k_max, C, K, (int)ec, k_star, W_star, m_at_star);
         __syncthreads();
     }
 }
@@ -1329,7 +1331,7 @@ hipError_t launch_exact_table(const int64_t *offsets, const int32_t *seg, const 
     // radii per block: blocks enough to fill the chip come first
     const long long groups = (long long)C * ((K + kTableThreads - 1) / kTableThreads);
     const int per = (int)std::min<long long>(E, std::max(1LL, groups * E / kTableBlocks));
-    const long long units = groups * ((E + per - 1) / per);
+    const long long units = groups * (((long long)E + per - 1) / per);
     const bool staged = M <= kTableLam;
     hipLaunchKernelGGL(staged ? exact_table_kernel<true> : exact_table_kernel<false>,
                        dim3((unsigned)std::min(units, kMaxGridBlocks)), dim3(kTableThreads),

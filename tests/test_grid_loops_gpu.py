@@ -9,7 +9,9 @@ take each loop past one pass, against the oracle's exact definitions:
 - class_quantile on 2^20 + 5 classes (the select, one block per class);
 - dro_cost_eval on a C K M = 268,500,992-entry table, past the 2^28 items
   of one pass of the zero fill and the exact epilogue, checked at sampled
-  entries that include the last ones (App. A Steps 4-5).
+  entries that include the last ones (App. A Steps 4-5);
+- 2^31 - 1 radius rows, the limit, of which the last step of a 32-bit loop
+  index would pass its range.
 """
 import numpy as np
 import pytest
@@ -118,3 +120,44 @@ def test_cost_eval_table_past_one_pass(ctx, dev):
         J = [oracle.J(S_row.hi[m], S_row.lo[m], float(w.lam[m]), float(eps[c]), N) for m in range(M)]
         m_best = int(np.argmin(J))  # first index of the minimum
         assert Wg[0, c, k] == J[m_best] and mg[0, c, k] == m_best
+
+
+def test_radius_rows_up_to_the_limit(dev):
+    """E C = 2^31 - 1, the most the entry points take: every radius of a table of one
+    class, one grid point and two multipliers (75 GB of tables in all), against the
+    definition in torch's fp64, a part of the radii at a time."""
+    import torch
+    import paper_2607_16892_amd as dro
+    from workloads.configs import random_workload
+    E, step = (1 << 31) - 1, 1 << 28
+    w = random_workload(seed=34, C=1, N=5, L=300, K=1, M=2, E=1)
+    print(f"[gpu] {E} radius rows", flush=True)
+    lam = w.lam.astype(np.float64)
+    eps = torch.empty(E, dtype=torch.float32, device=dev)
+    for a in range(0, E, step):
+        eps[a:a + step] = (torch.arange(a, min(a + step, E), device=dev) % 999_983).float() / 1024.0
+
+    def check(W, m):
+        W, m = W.view(-1), m.view(-1)
+        for a in range(0, E, step):
+            e = eps[a:a + step].double()
+            J0, J1 = e * lam[0] + q[0], e * lam[1] + q[1]
+            assert torch.equal(W[a:a + step], torch.minimum(J0, J1)), a
+            assert torch.equal(m[a:a + step] == 1, J1 < J0), a
+
+    with dro.Context(dev.index or 0) as c:
+        prob = dro.Problem.from_workload(w, dev)
+        S = dro.dro_cost_eval(c, prob, eps[:1].contiguous())["S"]
+        q = [float(v) / 5.0 for v in S.view(-1).cpu()]
+        r = dro.dro_cost_eval(c, prob, eps, want_S=False)
+        check(r["W"], r["m_star"])
+        del r
+        r = dro.dro_exact_table(c, prob, eps, want_argmin=False)
+        check(r["W"], r["m_star"])
+        del r
+        r = dro.dro_argmin_reservation(c, prob, eps, S)
+        check(r["W_star"], r["m_at_star"])
+        assert int(r["k_star"].abs().max()) == 0
+        del r
+    del eps
+    torch.cuda.empty_cache()
