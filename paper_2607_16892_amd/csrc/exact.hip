@@ -1514,7 +1514,7 @@ __global__ __launch_bounds__(256) void continuous_dual_kernel(
         r.rN = 1.0 / r.N;
         r.SX = (double)r.pre[kHistBins - 1].sum();
         const int Li = L_[c];
-        r.tmax = Li < kHistBins - 1 ? Li : kHistBins - 1;
+        r.tmax = min(max(Li, 0), kHistBins - 1);  // (L is not checked: stays inside the entries)
         const double eta = (double)eta_[k];
         r.L = (double)Li;
         r.cw = (double)c_w[c];

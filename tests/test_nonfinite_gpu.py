@@ -1,7 +1,8 @@
 """Hot calls do not check device data, so a radius, an S or a W that is infinite or
 NaN reaches the minima.  Where no value is below infinity the result is infinity
 at the last index searched (inside the table), and the rows beside it are what
-they are without it, bit for bit.
+they are without it, bit for bit.  A support bound outside [0, 2^15] leaves the
+other classes' rows as they are too (lookups stay inside the value counts).
 """
 import numpy as np
 import pytest
@@ -108,3 +109,23 @@ def test_sweeps_over_a_row_that_is_not_finite(ctx, dev):
         for c in (0, 2):
             assert int(got[c]) == int(Wh[c].argmin())
     assert float(st["W_star"][1]) == INF
+
+
+def test_support_bounds_outside_the_limits(ctx, dev):
+    import torch
+    import paper_2607_16892_amd as dro
+    w = random_workload(seed=10, C=4, N=(60, 9, 300, 77), L=500, K=33, M=11, E=2)
+    prob = dro.Problem.from_workload(w, dev)
+    eps = torch.from_numpy(w.eps.copy()).to(dev)
+
+    def run():
+        return dict(dual=dro.dro_continuous_dual(ctx, prob, eps)["W"],
+                    table=dro.dro_exact_table(ctx, prob, eps)["W"],
+                    dense=dro.dro_cost_eval(ctx, prob, eps)["W"])
+
+    ref = run()
+    prob.L = torch.tensor([500, -5, 500, 70_000], dtype=torch.int32, device=dev)
+    got = run()
+    torch.cuda.synchronize()
+    for k in ref:
+        assert torch.equal(got[k][:, [0, 2]], ref[k][:, [0, 2]]), k
