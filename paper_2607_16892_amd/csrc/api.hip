@@ -150,12 +150,8 @@ int ensure_ws(dro_ctx *ctx, size_t need, hipStream_t st)
     return DRO_OK;
 }
 
-struct Shape {
-    long long max_n = 0;  // largest class sample count
-};
-
 // Host-visible checks shared by every entry point.
-int check_problem(dro_ctx *ctx, const dro_problem *p, Shape *sh)
+int check_problem(dro_ctx *ctx, const dro_problem *p)
 {
     if (!ctx) return DRO_EINVAL;
     if (!p) return fail(ctx, DRO_EINVAL, "problem is NULL");
@@ -176,7 +172,6 @@ int check_problem(dro_ctx *ctx, const dro_problem *p, Shape *sh)
     if (o[0] != 0) return fail(ctx, DRO_EINVAL, "offsets[0] must be 0");
     for (int s = 0; s < p->S; ++s)
         if (o[s + 1] < o[s]) return fail(ctx, DRO_EINVAL, "offsets decrease at segment %d", s);
-    long long mx = 0;
     for (int c = 0; c < p->C; ++c) {
         const int s = p->seg_h ? p->seg_h[c] : c;
         if (s < 0 || s >= p->S)
@@ -185,9 +180,7 @@ int check_problem(dro_ctx *ctx, const dro_problem *p, Shape *sh)
         if (n <= 0) return fail(ctx, DRO_EINVAL, "class %d has an empty sample segment", c);
         if (n > (1LL << 26))
             return fail(ctx, DRO_ELIMIT, "class %d has %lld samples (> 2^26)", c, n);
-        mx = std::max(mx, n);
     }
-    sh->max_n = mx;
     return DRO_OK;
 }
 
@@ -652,8 +645,7 @@ const char *dro_last_error(const dro_ctx *ctx) { return ctx ? ctx->err : "no con
 int dro_validate(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
                  dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (E < 0 || (E > 0 && !eps)) return fail(ctx, DRO_EINVAL, "bad radius arguments");
     ENTER_DEVICE(ctx);
@@ -729,8 +721,7 @@ int dro_validate(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps
 int dro_cost_eval(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps, double *W,
                   int32_t *m_star, double *S, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (E <= 0 || !eps || !W) return fail(ctx, DRO_EINVAL, "E must be > 0 and eps, W non-NULL");
     if ((rc = check_rows(ctx, E, p->C))) return rc;
@@ -752,8 +743,7 @@ int dro_cost_eval(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *ep
 int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
                           double *W, int32_t *m_star, double *S, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (E <= 0 || !eps || !W || !S)
         return fail(ctx, DRO_EINVAL, "E must be > 0 and eps, W, S non-NULL");
@@ -787,8 +777,7 @@ int dro_argmin_reservation(dro_ctx *ctx, const dro_problem *p, int32_t E, const 
                            const double *S, const int32_t *k_max, int32_t *k_star, double *W_star,
                            int32_t *m_at_star, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (E <= 0 || !eps || !S || !k_star || !W_star)
         return fail(ctx, DRO_EINVAL, "E must be > 0 and eps, S, k_star, W_star non-NULL");
@@ -816,8 +805,7 @@ int dro_argmin_reservation(dro_ctx *ctx, const dro_problem *p, int32_t E, const 
 int class_quantile(dro_ctx *ctx, const dro_problem *p, int32_t *q_value, int64_t *q_rank,
                    dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (!q_value || !q_rank) return fail(ctx, DRO_EINVAL, "q_value and q_rank must be non-NULL");
     ENTER_DEVICE(ctx);
@@ -843,8 +831,7 @@ int dro_exact_table(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *
                     const int32_t *k_max, double *W, int32_t *m_star, int32_t *k_star,
                     double *W_star, int32_t *m_at_star, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (E <= 0 || !eps || !W || !m_star || (k_star && !W_star))
         return fail(ctx, DRO_EINVAL, "E must be > 0 and eps, W, m_star (and W_star with k_star) non-NULL");
@@ -870,8 +857,7 @@ int dro_exact_table(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *
 int dro_continuous_dual(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,
                         double *W, double *gamma, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (E <= 0 || !eps || !W || !gamma)
         return fail(ctx, DRO_EINVAL, "E must be > 0 and eps, W, gamma non-NULL");
@@ -896,8 +882,7 @@ int dro_continuous_dual(dro_ctx *ctx, const dro_problem *p, int32_t E, const flo
 int class_moments(dro_ctx *ctx, const dro_problem *p, int64_t *count, int64_t *sum,
                   int64_t *sumsq, int32_t *xmax, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (!count || !sum || !sumsq || !xmax)
         return fail(ctx, DRO_EINVAL, "count, sum, sumsq and xmax must be non-NULL");
@@ -919,8 +904,7 @@ int class_moments(dro_ctx *ctx, const dro_problem *p, int64_t *count, int64_t *s
 int dro_reservation_cost(dro_ctx *ctx, const dro_problem *p, int32_t R, const int32_t *eta_r,
                          double *cost, int64_t *cover, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (R <= 0 || !eta_r || !cost || !cover)
         return fail(ctx, DRO_EINVAL, "R must be > 0 and eta_r, cost, cover non-NULL");
@@ -972,8 +956,7 @@ int dro_baseline_reservations(dro_ctx *ctx, int32_t C, const int64_t *count, con
 
 int bcd_init_state(dro_ctx *ctx, const dro_problem *p, int32_t *k0, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (!k0) return fail(ctx, DRO_EINVAL, "k0 must be non-NULL");
     ENTER_DEVICE(ctx);
@@ -994,8 +977,7 @@ int bcd_init_state(dro_ctx *ctx, const dro_problem *p, int32_t *k0, dro_stream_t
 int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const dro_groups *grp,
                    const int32_t *k_prev, dro_step_out *out, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     if (!eps || !grp || !k_prev || !out || !out->k_next || !out->W_star || !out->q_value ||
         !out->usage || !out->feasible)
@@ -1168,8 +1150,7 @@ extern "C" {
 int bcd_service_times(dro_ctx *ctx, const dro_problem *p, const dro_service *svc, double *T,
                       double *ET2, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     rc = check_service(ctx, p->C, svc);
     if (rc) return rc;
@@ -1292,8 +1273,7 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
                   int32_t max_outer, int32_t max_inner, int32_t *z, int32_t *k, double *pi,
                   uint8_t *delta, double *objective, int32_t *info, dro_stream_t stream)
 {
-    Shape sh;
-    int rc = check_problem(ctx, p, &sh);
+    int rc = check_problem(ctx, p);
     if (rc) return rc;
     rc = check_service(ctx, p->C, svc);
     if (rc) return rc;

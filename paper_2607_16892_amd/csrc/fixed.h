@@ -21,16 +21,6 @@ __device__ __forceinline__ int64_t fix33(float v)
     return sh >= 0 ? (mant << sh) : (mant >> (-sh));
 }
 
-// floor(a / b) for b > 0 and |a| < 2^62: a double estimate corrected with
-// exact integer products, so the result does not depend on the estimate.
-__device__ __forceinline__ int64_t floor_div(int64_t a, int64_t b)
-{
-    int64_t q = (int64_t)floor((double)a / (double)b);
-    while (q * b > a) --q;
-    while ((q + 1) * b <= a) ++q;
-    return q;
-}
-
 // floor(a / b) clamped to [lo, hi] for b > 0 and -2^16 < lo <= hi < 2^16: the
 // quotient by the reciprocal instruction (about 2^-26 relative, so within one of
 // the floor after the clamp) corrected once with the exact remainder.
