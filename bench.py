@@ -49,12 +49,12 @@ PAPER_FLOPS_PER_EVAL = 7                 # 2 multiply-adds (4), a 3-way max (2),
 
 # Hardware-counter figures of the dense kernel on the 16 x 1e6 workload, from
 # profiles/dense_kernel_mixture-16x1M_counters.md.  They describe one version
-# of the dense kernel's code and launch plan (csrc/dense.hip, the constants of
-# csrc/dro_internal.h and plan_dense of csrc/api.hip, comments and layout
-# stripped, identified by the hash prefix) and are reported as null for any
-# other code or workload.
+# of the dense kernels' code and launch plan (csrc/dense.hip, the constants of
+# csrc/dro_internal.h, csrc/plan.h and the helpers of csrc/fixed.h and
+# csrc/wave.h, comments and layout stripped, identified by the hash prefix) and
+# are reported as null for any other code or workload.
 DENSE_COUNTERS = {
-    "dense_code_sha256_16": "a02407c483815aeb",
+    "dense_code_sha256_16": "3cee6ba81403211c",
     "workload": "mixture-16x1M",
     "valu_instr_per_eval": 0.50312,    # SQ_INSTS_VALU x 64 / evaluations
     "clock_ghz": 2.383,                # GRBM_GUI_ACTIVE / 8 XCDs / duration
@@ -63,32 +63,26 @@ DENSE_COUNTERS = {
 }
 
 
-def dense_code_hash() -> str:
-    """Hash of the dense kernel's code (the part of csrc/dense.hip before the
-    fill, epilogue and minimum kernels), of its constants (the dense section of
-    csrc/dro_internal.h) and of its launch plan (the plan constants and the
-    plan_dense function of csrc/api.hip, which set the slices and the grid),
-    comments and whitespace removed."""
+def dense_code_hash(csrc: str = os.path.join(ROOT, "paper_2607_16892_amd", "csrc")) -> str:
+    """Hash of the dense kernels' code (the part of csrc/dense.hip before the
+    fill, epilogue and minimum kernels, and the helpers it inlines from fixed.h
+    and wave.h), of their constants (the dense section of csrc/dro_internal.h)
+    and of their launch plan (csrc/plan.h, which picks the kernel, the tiles, the
+    slices and the grid), comments and whitespace removed."""
     import hashlib
     import re
 
     def code(name):
-        with open(os.path.join(ROOT, "paper_2607_16892_amd", "csrc", name)) as f:
+        with open(os.path.join(csrc, name)) as f:
             text = re.sub(r"/\*.*?\*/", " ", f.read(), flags=re.S)
         return re.sub(r"//[^\n]*", " ", text)
 
     hdr = code("dro_internal.h")
-    i = hdr.index("struct DensePlan")  # the dense section's constants come before its structs
+    i = hdr.index("struct DenseArgs")  # the dense section's constants come before its structs
     consts = [ln for ln in hdr[:i].splitlines() if "constexpr" in ln]
-    api = code("api.hip")
-    plan_consts = [ln for ln in api.splitlines()
-                   if any(f"constexpr long long {k} " in ln for k in ("kSlicesPerBlock", "kMaxSliceN",
-                                                                      "kBalanceSliceN", "kMinSliceN"))]
-    i = api.index("DensePlan plan_dense(")
-    plan = api[i:api.index("return pl;", i)]
     dense = code("dense.hip")
-    dense = dense[:dense.index("zero_u64_u32_kernel")]  # the dense kernel, its helpers and launch
-    text = dense + "\n" + "\n".join(consts + plan_consts) + "\n" + plan
+    dense = dense[:dense.index("zero_u64_u32_kernel")]  # the dense kernels, their helpers and launch
+    text = "\n".join([dense, *consts, code("plan.h"), code("fixed.h"), code("wave.h")])
     return hashlib.sha256(" ".join(text.split()).encode()).hexdigest()[:16]
 
 

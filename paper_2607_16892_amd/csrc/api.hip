@@ -11,9 +11,6 @@
 
 #include "dro_internal.h"
 
-// Sizes of the classes' segments and how many classes have each.
-using SizeCounts = std::vector<std::pair<long long, long long>>;
-
 struct dro_ctx {
     int device = 0;
     int num_cu = 256;
@@ -31,7 +28,7 @@ struct dro_ctx {
     std::vector<int64_t> staged_off;
     std::vector<int32_t> staged_seg;
     dro::RowPlan staged_rows{};  // parts of the staged segments; boff points into `stage`
-    SizeCounts staged_sizes;     // the staged classes' segment sizes
+    dro::SizeCounts staged_sizes;  // the staged classes' segment sizes
     // the dense plan last made for the staged problem, and its grid (K = 0: none)
     int plan_K = 0, plan_M = 0;
     dro::DensePlan plan{};
@@ -184,29 +181,6 @@ int check_problem(dro_ctx *ctx, const dro_problem *p)
     return DRO_OK;
 }
 
-// Large problems run the persistent grid that claims slices (see dense.hip):
-// tiles of kTM pairs per lane, each tile's samples split into P slices.  P
-// is the largest of three needs: slices of at most kMaxSliceN samples, so that
-// the last ones are short; about kSlicesPerBlock slices per resident block, so
-// that the issue priorities keep the blocks of a compute unit in step and the
-// blocks still finding work near the end keep every unit full (slices down to
-// kBalanceSliceN samples); and one slice for every resident block (slices down
-// to kMinSliceN samples).  Measured on 16 x 1e6 samples (K = 2048, M = 256,
-// 1024 resident blocks): P = 16 (62,500-sample slices) ran 0.3 % faster than
-// the launch of 20,480 short blocks it replaced, P = 31 0.2 % slower and
-// P = 8 2.5 % slower.
-// Others run one block per slice instead (dense_slices_kernel): a run's set-up
-// (its thresholds, claims, the search for work) is then not small beside its
-// work.  plan_slices picks its tile shape and slice length, plan_dense between
-// the two.
-// The kernels index with the host-validated offsets and segment map: both are
-// copied into the workspace at the start of every call, so device data that
-// disagrees with the host copies can never steer a kernel outside xi.
-constexpr long long kSlicesPerBlock = 16;
-constexpr long long kMaxSliceN = 65536;
-constexpr long long kBalanceSliceN = 512;
-constexpr long long kMinSliceN = 64;
-
 // The distinct sizes of the classes' segments and how many classes have each.
 SizeCounts class_sizes(const dro_problem *p)
 {
@@ -253,9 +227,10 @@ RowPlan plan_rows(dro_ctx *ctx, const dro_problem *p)
     return pl;
 }
 
-// The offsets (and segment map) every kernel indexes with: the host copies of
-// the call, uploaded to the device, with the row table of unequal segments
-// behind them.  Calls on the workspace keep them in the ctx's staging buffer
+// The offsets (and segment map) every kernel indexes with: the host-validated copies
+// of the call, uploaded to the device (so device data that disagrees with them can
+// never steer a kernel outside xi), with the row table of unequal segments behind
+// them.  Calls on the workspace keep them in the ctx's staging buffer
 // and skip the upload when the host arrays and the stream equal the last ones
 // staged.  `q` is the problem with the staged arrays, `rows` its row plan.
 int stage_problem(dro_ctx *ctx, const dro_problem *p, hipStream_t st, dro_problem *q, RowPlan *rows)
@@ -328,99 +303,6 @@ int stage_in_arena(dro_ctx *ctx, const dro_problem *p, Arena &ar, bool packed, h
     q->seg = seg;
     if (boff) rows->boff = boff;
     return DRO_OK;
-}
-
-// Tile shape and slice length of dense_slices_kernel by a model of its time in
-// cycles of a compute unit: w passes of the chip's resident blocks (one of 1,024
-// threads per compute unit), each as long as a slice's v_sad_u16 (4 waves a SIMD,
-// 4 cycles each; kLoop more per step of sixteen samples for its loads, claims and
-// branch) and a block's set-up, which grows with its pairs (the first samples,
-// thresholds, LDS sums, flush: 31 us for 8,192 pairs from slices of 12,500 and
-// 14,286 samples, 5 us for 512).  For every shape and w the shortest slices whose
-// blocks fit w passes; a sum split over slices also pays the zero fill of the
-// table.
-constexpr int kMaxDirectSlice = 65536;
-constexpr double kLoop = 8.0, kBlockCycles = 12000.0, kPairCycles = 7.0, kZeroCycles = 6000.0;
-
-double plan_slices(const SizeCounts &sizes, int K, int M, int num_cu, DensePlan *best)
-{
-    const long long KM = (long long)K * M;
-    double total = 0.0, best_cost = -1.0;
-    for (const auto &z : sizes) total += (double)z.first * z.second;
-    for (int sh = 0; sh < kSliceShapes; ++sh) {
-        const int TM = kSliceTM[sh], GL = kSliceGL[sh], NG = 1024 / GL;
-        const long long tiles = (KM + (long long)TM * GL - 1) / ((long long)TM * GL);
-        const double per_sample = (8 * TM + kLoop) / NG;
-        const double per_block = kBlockCycles + kPairCycles * TM * GL;
-        double least = 0.0;  // blocks of the longest slices
-        for (const auto &z : sizes)
-            least += (double)tiles * slices_of(z.first, kMaxDirectSlice) * z.second;
-        if (least > (1LL << 22)) continue;
-        const int w0 = std::max(1, (int)std::ceil(least / num_cu));
-        for (int i = 0; i < 12; ++i) {
-            const int w = i < 8 ? w0 + i : w0 + 7 + 4 * (i - 7);
-            const double room = (double)w * num_cu;
-            double len = std::max(16.0, std::ceil(total * tiles / room));
-            double blocks = 0.0, longest = 0.0;
-            bool one = true, fits = false;
-            for (int it = 0; it < 6 && !fits && len <= kMaxDirectSlice; ++it) {
-                blocks = longest = 0.0;
-                one = true;
-                for (const auto &z : sizes) {
-                    const double n = std::ceil((double)z.first / len);
-                    blocks += n * z.second;
-                    longest = std::max(longest, (double)z.first / n);
-                    one = one && n <= 1.0;
-                }
-                blocks *= tiles;
-                fits = blocks <= room;
-                if (!fits) len = std::ceil(len * std::max(1.02, blocks / room));
-            }
-            if (!fits) continue;
-            const double cost = w * (longest * per_sample + per_block) + (one ? 0.0 : kZeroCycles);
-            if (best_cost < 0.0 || cost < best_cost) {
-                best_cost = cost;
-                *best = DensePlan{};
-                best->tiles = (int)tiles;
-                best->direct = 1;
-                best->shape = sh;
-                best->len = (int)len;
-                best->stored = one;
-                best->blocks = (long long)blocks;
-            }
-        }
-    }
-    if (best_cost >= 0.0 && sizes.size() == 1) best->P = slices_of(sizes[0].first, best->len);
-    return best_cost;  // below 0: too many blocks
-}
-
-DensePlan plan_dense(const SizeCounts &sizes, int C, int K, int M, int num_cu, int bpc)
-{
-    const long long max_n = sizes.back().first;
-    DensePlan pl{};
-    pl.tiles = (int)(((long long)K * M + kThreads * kTM - 1) / (kThreads * kTM));
-    const long long T = (long long)C * pl.tiles;
-    const long long slots = (long long)num_cu * std::max(bpc, 1);
-    // The claimed slices run at 1.2 % above the v_sad_u16 rate of their padded
-    // tiles (16 x 1e6 samples: 108.6 ms), and lose 100 us where the last slices
-    // end and some 17 us per tile and compute unit in the runs' set-up (16 x 2e5 samples, K = 1000, M = 200:
-    // 8.72 ms, one block per slice 9.03; 8 x 4e5, K = 1024, M = 128: 5.75 and 5.53).
-    double total = 0.0;
-    for (const auto &z : sizes) total += (double)z.first * z.second;
-    const double claimed = total * pl.tiles * (kThreads * kTM) / (128.0 * num_cu) * 1.012 + 2.5e5 +
-                           4e4 * (double)T / num_cu;
-    DensePlan direct;
-    const double cost = plan_slices(sizes, K, M, num_cu, &direct);
-    if (cost >= 0.0 && cost <= claimed) return direct;
-    const long long by_size = (max_n + kMaxSliceN - 1) / kMaxSliceN;
-    const long long by_balance = std::min((kSlicesPerBlock * slots + T - 1) / T, max_n / kBalanceSliceN);
-    const long long by_fill = std::min((slots + T - 1) / T, max_n / kMinSliceN);
-    long long P = std::max({1LL, by_size, by_balance, by_fill});
-    P = std::min(P, std::max(1LL, 0x7fffffffLL / T));  // T P claims fit the 32-bit counters
-    pl.P = (int)P;
-    pl.direct = 0;
-    pl.blocks = std::min(slots, T * P);
-    return pl;
 }
 
 // The plan of the staged problem, kept until another grid or other segments come.

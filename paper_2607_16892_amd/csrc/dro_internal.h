@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "dro.h"
+#include "plan.h"
 
 namespace dro {
 
@@ -15,33 +16,10 @@ namespace dro {
 // into P slices.  A persistent grid of blocks claims slices
 // (its own tiles first, then other tiles' unclaimed slices) and keeps a
 // tile's sums in registers over consecutive slices of that tile.
-constexpr int kThreads = 256;
-constexpr int kTM = 32;
 constexpr int kTileN = 8192;          // 16-bit LDS words of the staging buffers and the thresholds
 constexpr int kHalfSadSteps = 32766;  // v_sad_u16 steps between carries: a sum kept below 2^31
                                       // takes 32766 more steps of at most 2 * 32770 below 2^32
 constexpr int kXcds = 8;              // accelerator complex dies of one MI355X (one L2 each)
-
-// tile shapes of the one-block-per-slice kernel: pairs per lane, lanes per group
-constexpr int kSliceShapes = 5;
-constexpr int kSliceTM[kSliceShapes] = {32, 32, 32, 16, 8};
-constexpr int kSliceGL[kSliceShapes] = {256, 128, 64, 64, 64};
-
-struct DensePlan {
-    int tiles;         // tiles of the K * M pairs of a class, in table order
-    int P;             // sample slices per tile (direct: 0 = by each class's size and len)
-    int direct;        // 1: one block per slice, no claims (smaller problems)
-    int shape;         // direct: the tile shape
-    int len;           // direct: samples per slice, at most
-    bool stored;       // direct: every class has one slice, so the sums are stored, not added
-    long long blocks;  // direct: a block per slice; else the persistent grid,
-                       // min(resident blocks, C * tiles * P)
-};
-// slices of n samples
-__host__ __device__ inline int slices_of(long long n, int len)
-{
-    return n <= len ? 1 : (int)((n + len - 1) / len);
-}
 
 struct DenseArgs {
     const int64_t *offsets;
