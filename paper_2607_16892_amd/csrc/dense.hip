@@ -382,8 +382,6 @@ __global__ __launch_bounds__(kThreads) void dense_kernel(DenseArgs a)
 // sads, 99.6 % issue, the rest before the first and after the last wave); six
 // segments from 1.2e5 to 7.9e3 samples, K = 333, M = 50: 289 -> 102 us; 1,000
 // samples, K = 64, M = 32: 21 -> 5.3 us.
-constexpr int kSliceThreads = 1024;
-
 template <int TM, int GL>
 __global__ __launch_bounds__(kSliceThreads) void dense_slices_kernel(DenseArgs a)
 {

@@ -1686,36 +1686,38 @@ __global__ __launch_bounds__(64 * kMomWaves) void class_moments_kernel(
     const int32_t *eta, int K, int32_t *k0)
 {
     const int lane = threadIdx.x & 63;
-    const int c = blockIdx.x * kMomWaves + (threadIdx.x >> 6);
-    if (c >= C) return;  // whole waves
-    const int s = seg_of_x(seg, c);
-    const long long row0 = boff ? boff[s] : (long long)s * B0;
-    const int B = boff ? (int)(boff[s + 1] - row0) : B0;
-    RowMoments m{0, 0, 0, 0};
-    for (int r = lane; r < B; r += 64) {
-        const RowMoments x = rows[row0 + r];
-        m.raw += x.raw;
-        m.sum += x.sum;
-        m.sq += x.sq;
-        m.mx = x.mx > m.mx ? x.mx : m.mx;
-    }
-    m = wave_moments(m);
-    if (lane != 0) return;
-    const long long N = offsets[s + 1] - offsets[s];
-    if (count) {
-        count[c] = N;
-        sum[c] = m.sum;
-        sumsq[c] = (int64_t)m.sq;
-        xmax[c] = (int32_t)m.mx;
-    }
-    if (eta) {
-        int lo = 0, hi = K - 1;  // eta ascending
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) / 2;
-            if ((long long)eta[mid] * N <= m.raw) lo = mid;
-            else hi = mid - 1;
+    // classes in a loop of whole waves (no block barrier)
+    for (long long c = (long long)blockIdx.x * kMomWaves + (threadIdx.x >> 6); c < C;
+         c += (long long)gridDim.x * kMomWaves) {
+        const int s = seg_of_x(seg, (int)c);
+        const long long row0 = boff ? boff[s] : (long long)s * B0;
+        const int B = boff ? (int)(boff[s + 1] - row0) : B0;
+        RowMoments m{0, 0, 0, 0};
+        for (int r = lane; r < B; r += 64) {
+            const RowMoments x = rows[row0 + r];
+            m.raw += x.raw;
+            m.sum += x.sum;
+            m.sq += x.sq;
+            m.mx = x.mx > m.mx ? x.mx : m.mx;
         }
-        k0[c] = lo;
+        m = wave_moments(m);
+        if (lane != 0) continue;
+        const long long N = offsets[s + 1] - offsets[s];
+        if (count) {
+            count[c] = N;
+            sum[c] = m.sum;
+            sumsq[c] = (int64_t)m.sq;
+            xmax[c] = (int32_t)m.mx;
+        }
+        if (eta) {
+            int lo = 0, hi = K - 1;  // eta ascending
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) / 2;
+                if ((long long)eta[mid] * N <= m.raw) lo = mid;
+                else hi = mid - 1;
+            }
+            k0[c] = lo;
+        }
     }
 }
 
@@ -1761,9 +1763,10 @@ hipError_t launch_moments(const int64_t *offsets, const int32_t *seg, const int3
     hipLaunchKernelGGL(row_moments_kernel, dim3((unsigned)std::min(pl.rows, kMaxGridBlocks)),
                        dim3(kMomThreads), 0, st, offsets, xi, S, pl.B, pl.boff, pl.rows, rows);
     HIPRET(hipGetLastError());
-    hipLaunchKernelGGL(class_moments_kernel, dim3((unsigned)((C + kMomWaves - 1) / kMomWaves)),
-                       dim3(64 * kMomWaves), 0, st, offsets, seg, (const RowMoments *)rows, pl.B,
-                       pl.boff, C, count, sum, sumsq, xmax, eta, K, k0);
+    const long long blocks = std::min(((long long)C + kMomWaves - 1) / kMomWaves, kMaxGridBlocks);
+    hipLaunchKernelGGL(class_moments_kernel, dim3((unsigned)blocks), dim3(64 * kMomWaves), 0, st,
+                       offsets, seg, (const RowMoments *)rows, pl.B, pl.boff, C, count, sum, sumsq,
+                       xmax, eta, K, k0);
     return hipGetLastError();
 }
 

@@ -67,6 +67,8 @@ constexpr long long kMinSliceN = 64;
 // 14,286 samples, 5 us for 512).  For every shape and w the shortest slices whose
 // blocks fit w passes; a sum split over slices also pays the zero fill of the
 // table.
+constexpr int kSliceThreads = 1024;
+constexpr long long kMaxDirectBlocks = (1LL << 32) / kSliceThreads - 1;  // below 2^32 work-items
 constexpr int kMaxDirectSlice = 65536;
 constexpr double kLoop = 8.0, kBlockCycles = 12000.0, kPairCycles = 7.0, kZeroCycles = 6000.0;
 
@@ -76,14 +78,14 @@ inline double plan_slices(const SizeCounts &sizes, int K, int M, int num_cu, Den
     double total = 0.0, best_cost = -1.0;
     for (const auto &z : sizes) total += (double)z.first * z.second;
     for (int sh = 0; sh < kSliceShapes; ++sh) {
-        const int TM = kSliceTM[sh], GL = kSliceGL[sh], NG = 1024 / GL;
+        const int TM = kSliceTM[sh], GL = kSliceGL[sh], NG = kSliceThreads / GL;
         const long long tiles = (KM + (long long)TM * GL - 1) / ((long long)TM * GL);
         const double per_sample = (8 * TM + kLoop) / NG;
         const double per_block = kBlockCycles + kPairCycles * TM * GL;
         double least = 0.0;  // blocks of the longest slices
         for (const auto &z : sizes)
             least += (double)tiles * slices_of(z.first, kMaxDirectSlice) * z.second;
-        if (least > (1LL << 22)) continue;
+        if (least > kMaxDirectBlocks) continue;
         const int w0 = std::max(1, (int)std::ceil(least / num_cu));
         for (int i = 0; i < 12; ++i) {
             const int w = i < 8 ? w0 + i : w0 + 7 + 4 * (i - 7);
@@ -104,7 +106,7 @@ inline double plan_slices(const SizeCounts &sizes, int K, int M, int num_cu, Den
                 fits = blocks <= room;
                 if (!fits) len = std::ceil(len * std::max(1.02, blocks / room));
             }
-            if (!fits) continue;
+            if (!fits || blocks > kMaxDirectBlocks) continue;
             const double cost = w * (longest * per_sample + per_block) + (one ? 0.0 : kZeroCycles);
             if (best_cost < 0.0 || cost < best_cost) {
                 best_cost = cost;

@@ -6,7 +6,8 @@ take each loop past one pass, against the oracle's exact definitions:
   multipliers: 4 rows per block, two passes) and E C = 2^20 + 6 radius rows
   (the argmin, one block per row, two passes), from an exact S table drawn
   with many ties (App. A Step 3, Prop. 4.2; ties to the lowest k, then m);
-- class_quantile on 2^20 + 5 classes (the select, one block per class);
+- class_quantile on 2^20 + 5 classes (the select, one block per class), and
+  class_moments and bcd_init_state on 2^22 + 9 (four per block);
 - dro_cost_eval on a C K M = 268,500,992-entry table, past the 2^28 items
   of one pass of the zero fill and the exact epilogue, checked at sampled
   entries that include the last ones (App. A Steps 4-5);
@@ -84,6 +85,28 @@ def test_quantile_classes_past_one_pass(ctx, dev):
     qv, qr = oracle.quantile(w)
     assert np.array_equal(q["q_rank"].cpu().numpy(), qr)
     assert np.array_equal(q["q_value"].cpu().numpy(), qv)
+
+
+def test_moments_of_classes_past_one_pass(ctx, dev):
+    import paper_2607_16892_amd as dro
+    rng = np.random.default_rng(35)
+    C, L = (1 << 22) + 9, 300
+    parts = [rng.integers(1, L + 1, n).astype(np.int32) for n in (50, 1, 77)]
+    offsets, xi = _csr(parts)
+    seg = (np.arange(C) % 3).astype(np.int32)
+    one = np.ones(C, np.float32)
+    print(f"[gpu] moments: C={C}", flush=True)
+    prob = dro.Problem.from_arrays(dev, offsets, xi, np.full(C, L, np.int32), eta_grid(5, L),
+                                   lam_grid(2), one, one, seg=seg)
+    m = dro.class_moments(ctx, prob)
+    k0 = dro.bcd_init_state(ctx, prob).cpu().numpy()
+    eta = eta_grid(5, L).astype(np.int64)
+    for s, x in enumerate(parts):
+        x = x.astype(np.int64)
+        at = seg == s
+        for k, v in (("count", len(x)), ("sum", x.sum()), ("sumsq", (x * x).sum()), ("xmax", x.max())):
+            assert (m[k].cpu().numpy()[at] == v).all(), k
+        assert (k0[at] == np.flatnonzero(eta * len(x) <= x.sum()).max()).all()
 
 
 def test_cost_eval_table_past_one_pass(ctx, dev):

@@ -1,0 +1,82 @@
+"""The dense evaluation's launch plan (csrc/plan.h, host arithmetic), compiled for
+the CPU: over sizes from one sample to millions of classes every plan keeps its
+grid below 2^32 work-items and covers all samples.
+"""
+import ctypes as ct
+import math
+import os
+import random
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2607_16892_amd", "csrc")
+SRC = r'''
+#include "plan.h"
+extern "C" void plan(int n, const long long *size, const long long *count, int C, int K, int M,
+                     long long *out)
+{
+    dro::SizeCounts z;
+    for (int i = 0; i < n; ++i) z.push_back({size[i], count[i]});
+    const dro::DensePlan p = dro::plan_dense(z, C, K, M, 256, 4);
+    const long long v[] = {p.tiles, p.P, p.direct, p.shape, p.len, p.stored, p.blocks};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
+'''
+SHAPES = [32 * 256, 32 * 128, 32 * 64, 16 * 64, 8 * 64]  # pairs of a tile
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SRC)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"),
+                    "-o", str(d / "plan.so")], check=True)
+    lib = ct.CDLL(str(d / "plan.so"))
+
+    def run(sizes, K, M):
+        """sizes: {segment size: classes}."""
+        z = sorted(sizes.items())
+        out = (ct.c_longlong * 7)()
+        lib.plan(len(z), (ct.c_longlong * len(z))(*[a for a, _ in z]),
+                 (ct.c_longlong * len(z))(*[b for _, b in z]), sum(b for _, b in z), K, M, out)
+        return dict(zip(("tiles", "P", "direct", "shape", "len", "stored", "blocks"), out))
+
+    return run
+
+
+def _check(p, sizes, K, M):
+    threads = 1024 if p["direct"] else 256
+    assert 0 < p["blocks"] and p["blocks"] * threads < 1 << 32
+    if p["direct"]:
+        assert p["tiles"] == -(-K * M // SHAPES[p["shape"]]) and 1 <= p["len"] <= 65536
+        slices = {n: -(-n // p["len"]) for n in sizes}
+        assert p["blocks"] == p["tiles"] * sum(slices[n] * c for n, c in sizes.items())
+        assert p["stored"] == all(s == 1 for s in slices.values())
+        if len(sizes) == 1:
+            assert p["P"] == slices[next(iter(sizes))]
+    else:
+        T = sum(sizes.values()) * p["tiles"]
+        assert p["tiles"] == -(-K * M // 8192) and p["P"] >= 1
+        assert p["blocks"] <= 1024 and (p["P"] == 1 or T * p["P"] < 1 << 31)
+
+
+@pytest.mark.parametrize("K,M", [(50, 10), (16, 16), (1, 1), (32, 16), (64, 32)])
+@pytest.mark.parametrize("C", [(1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 24) + 3, 1 << 21])
+def test_millions_of_classes(plan, C, K, M):
+    for sizes in ({100: C}, {100: C - 1, 70_000: 1}, {1: C // 2, 60_000: C - C // 2}):
+        _check(plan(sizes, K, M), sizes, K, M)
+
+
+def test_sizes_over_the_whole_range(plan):
+    rng = random.Random(5)
+
+    def log(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    for _ in range(300):
+        sizes = {log(1, 1 << 26): log(1, 1 << 12) for _ in range(rng.choice([1, 1, 2, 7, 60]))}
+        K, M = log(1, 32769), log(1, 65536)
+        if K * M < 1 << 31:
+            _check(plan(sizes, K, M), sizes, K, M)
