@@ -28,7 +28,6 @@ struct dro_ctx {
     std::vector<int64_t> staged_off;
     std::vector<int32_t> staged_seg;
     dro::RowPlan staged_rows{};  // parts of the staged segments; boff points into `stage`
-    dro::SizeCounts staged_sizes;  // the staged classes' segment sizes
     // the dense plan last made for the staged problem, and its grid (K = 0: none)
     int plan_K = 0, plan_M = 0;
     dro::DensePlan plan{};
@@ -181,22 +180,21 @@ int check_problem(dro_ctx *ctx, const dro_problem *p)
     return DRO_OK;
 }
 
-// The distinct sizes of the classes' segments and how many classes have each.
-SizeCounts class_sizes(const dro_problem *p)
+// The dense plan for the sizes of the classes' segments.
+DensePlan plan_problem(const dro_ctx *ctx, const dro_problem *p)
 {
-    SizeCounts v(p->S);
-    for (int s = 0; s < p->S; ++s) v[s] = {p->offsets_h[s + 1] - p->offsets_h[s], p->seg_h ? 0 : 1};
-    if (p->seg_h)
-        for (int c = 0; c < p->C; ++c) ++v[p->seg_h[c]].second;
-    std::sort(v.begin(), v.end());
-    size_t n = 0;
-    for (size_t i = 0; i < v.size(); ++i) {
-        if (!v[i].second) continue;
-        if (n && v[n - 1].first == v[i].first) v[n - 1].second += v[i].second;
-        else v[n++] = v[i];
+    std::vector<int32_t> uses;  // classes of each segment
+    if (p->seg_h) {
+        uses.assign(p->S, 0);
+        for (int c = 0; c < p->C; ++c) ++uses[p->seg_h[c]];
     }
-    v.resize(n);
-    return v;
+    auto each = [&](auto &&add) {
+        for (int s = 0; s < p->S; ++s) {
+            const long long classes = p->seg_h ? uses[s] : 1;
+            if (classes) add(p->offsets_h[s + 1] - p->offsets_h[s], classes);
+        }
+    };
+    return plan_dense(each, p->C, p->K, p->M, ctx->num_cu, ctx->dense_bpc);
 }
 
 size_t stage_bytes(const dro_problem *p)
@@ -271,7 +269,6 @@ int stage_problem(dro_ctx *ctx, const dro_problem *p, hipStream_t st, dro_proble
             pl.boff = boff;
         }
         ctx->staged_rows = pl;
-        ctx->staged_sizes = class_sizes(p);
         ctx->plan_K = 0;
         ctx->staged_off.assign(p->offsets_h, p->offsets_h + p->S + 1);
         if (p->seg_h) ctx->staged_seg.assign(p->seg_h, p->seg_h + p->C);
@@ -305,11 +302,12 @@ int stage_in_arena(dro_ctx *ctx, const dro_problem *p, Arena &ar, bool packed, h
     return DRO_OK;
 }
 
-// The plan of the staged problem, kept until another grid or other segments come.
+// The plan of the staged problem (made by the first dense call on it), kept until
+// another grid or other segments come.
 const DensePlan &staged_plan(dro_ctx *ctx, const dro_problem *p)
 {
     if (ctx->plan_K != p->K || ctx->plan_M != p->M) {
-        ctx->plan = plan_dense(ctx->staged_sizes, p->C, p->K, p->M, ctx->num_cu, ctx->dense_bpc);
+        ctx->plan = plan_problem(ctx, p);
         ctx->plan_K = p->K;
         ctx->plan_M = p->M;
     }
@@ -650,9 +648,7 @@ int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const f
                                      cost_eval_scratch_bytes(p, rows, true) <=
                                  (size_t)DRO_NOALLOC_SCRATCH_BYTES;
     if ((rc = stage_in_arena(ctx, p, ar, packed, (hipStream_t)stream, &q, &rows))) return rc;
-    const DensePlan pl =
-        plan_dense(class_sizes(p), p->C, p->K, p->M, ctx->num_cu, ctx->dense_bpc);
-    return run_cost_eval(ctx, &q, pl, rows, packed, E, eps, W, m_star, S, ar, (hipStream_t)stream);
+    return run_cost_eval(ctx, &q, plan_problem(ctx, p), rows, packed, E, eps, W, m_star, S, ar, (hipStream_t)stream);
 }
 
 int dro_argmin_reservation(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *eps,

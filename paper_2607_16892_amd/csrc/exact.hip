@@ -12,6 +12,7 @@
 // is J = RN(RN(lam eps) + RN(RN(S) / N)) with RN(S) the correctly rounded
 // double of the exact sum.
 #include <algorithm>
+#include <vector>
 
 #include "dro_internal.h"
 #include "fixed.h"
@@ -460,11 +461,17 @@ long long row_part_len(const int64_t *offsets_h, int S, int num_cu)
     // at most what 16-bit counts hold.
     const long long slots = (long long)num_cu * ((S + num_cu - 1) / num_cu);
     long long lo = 16384, hi = kQMaxPart;
+    // (only segments above the shortest part have more than one row: the search looks
+    // those through, not the many short ones of a large problem)
+    std::vector<long long> large;
+    for (int s = 0; s < S; ++s) {
+        const long long n = offsets_h[s + 1] - offsets_h[s];
+        if (n > lo) large.push_back(n);
+    }
     while (lo < hi) {
         const long long mid = (lo + hi) / 2;
-        long long rows = 0;
-        for (int s = 0; s < S && rows <= slots; ++s)
-            rows += row_parts(offsets_h[s + 1] - offsets_h[s], mid);
+        long long rows = S - (long long)large.size();
+        for (size_t i = 0; i < large.size() && rows <= slots; ++i) rows += row_parts(large[i], mid);
         if (rows <= slots) hi = mid;
         else lo = mid + 1;
     }

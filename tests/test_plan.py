@@ -17,9 +17,10 @@ SRC = r'''
 extern "C" void plan(int n, const long long *size, const long long *count, int C, int K, int M,
                      long long *out)
 {
-    dro::SizeCounts z;
-    for (int i = 0; i < n; ++i) z.push_back({size[i], count[i]});
-    const dro::DensePlan p = dro::plan_dense(z, C, K, M, 256, 4);
+    auto each = [&](auto &&add) {
+        for (int i = 0; i < n; ++i) add(size[i], count[i]);
+    };
+    const dro::DensePlan p = dro::plan_dense(each, C, K, M, 256, 4);
     const long long v[] = {p.tiles, p.P, p.direct, p.shape, p.len, p.stored, p.blocks};
     for (int i = 0; i < 7; ++i) out[i] = v[i];
 }
@@ -54,8 +55,8 @@ def _check(p, sizes, K, M):
         slices = {n: -(-n // p["len"]) for n in sizes}
         assert p["blocks"] == p["tiles"] * sum(slices[n] * c for n, c in sizes.items())
         assert p["stored"] == all(s == 1 for s in slices.values())
-        if len(sizes) == 1:
-            assert p["P"] == slices[next(iter(sizes))]
+        one = len(set(slices.values())) == 1 and (len(sizes) == 1 or p["stored"])
+        assert p["P"] == (next(iter(slices.values())) if one else 0)
     else:
         T = sum(sizes.values()) * p["tiles"]
         assert p["tiles"] == -(-K * M // 8192) and p["P"] >= 1
@@ -80,3 +81,22 @@ def test_sizes_over_the_whole_range(plan):
         K, M = log(1, 32769), log(1, 65536)
         if K * M < 1 << 31:
             _check(plan(sizes, K, M), sizes, K, M)
+
+
+@pytest.mark.parametrize("distinct", [63, 64, 65, 200, 5000])
+@pytest.mark.parametrize("K,M", [(7, 11), (64, 32), (1000, 200)])
+def test_more_sizes_than_the_plan_lists(plan, distinct, K, M):
+    rng = random.Random(distinct + K)
+    sizes = {}
+    while len(sizes) < distinct:
+        sizes[rng.choice([rng.randint(1, 40), rng.randint(1, 90_000), rng.randint(1, 300)])
+              if distinct < 300 else rng.randint(1, 90_000)] = rng.randint(1, 3)
+    _check(plan(sizes, K, M), sizes, K, M)
+
+
+def test_equal_sizes_give_the_plan_of_their_count(plan):
+    # bins hold their largest size, so sizes of one bin plan as if all had it
+    a = {1024 + i: 2 for i in range(100)}  # one bin, more sizes than are listed one by one
+    p, q = plan(a, 64, 32), plan({1123: 200}, 64, 32)
+    assert {k: p[k] for k in ("direct", "shape", "len")} == {k: q[k] for k in ("direct", "shape", "len")}
+    _check(p, a, 64, 32)
