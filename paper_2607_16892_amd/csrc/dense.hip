@@ -399,30 +399,41 @@ __global__ __launch_bounds__(kSliceThreads) void dense_slices_kernel(DenseArgs a
     const int nb = (int)gridDim.x, xcd = (int)(blockIdx.x % kXcds);
     const int b = xcd * (nb / kXcds) + min(xcd, nb % kXcds) + (int)(blockIdx.x / kXcds);
     // block b: class c, then slice p of its P, then tile
-    int c = 0, P = pl.P, u = b;
+    const int slice = b / pl.tiles, tile = b % pl.tiles;
+    int c, p = slice, P = pl.P;
     if (P) {
-        c = b / (P * pl.tiles);
-        u = b % (P * pl.tiles);
-    } else {
-        for (;; c += 64) {  // 64 classes at a time: the one whose blocks hold b
+        c = slice / P;
+        p = slice % P;
+    } else if (a.C <= kWalkClasses) {  // one or a few steps of 64 classes
+        for (c = 0;; c += 64) {
             int n = 0;
             if (c + lane < a.C) {
                 const int sg = seg_of(a.seg, c + lane);
-                n = pl.tiles * slices_of(a.offsets[sg + 1] - a.offsets[sg], pl.len);
+                n = slices_of(a.offsets[sg + 1] - a.offsets[sg], pl.len);
             }
             const int incl = (int)scan_wave((uint32_t)n);
-            const unsigned long long in = __ballot(u < incl);
+            const unsigned long long in = __ballot(p < incl);
             if (in || c + 64 >= a.C) {
                 const int l = in ? __ffsll(in) - 1 : 0;
                 c += l;
-                u -= __builtin_amdgcn_readlane(incl - n, l);
-                P = __builtin_amdgcn_readlane(n, l) / pl.tiles;
+                p -= __builtin_amdgcn_readlane(incl - n, l);
+                P = __builtin_amdgcn_readlane(n, l);
                 break;
             }
-            u -= __builtin_amdgcn_readlane(incl, 63);
+            p -= __builtin_amdgcn_readlane(incl, 63);
         }
+    } else {  // the last class that starts at or before the slice, 64 pieces at a time
+        const uint32_t *starts = a.claim;
+        int hi = a.C;
+        for (c = 0; hi - c > 1;) {
+            const int step = (hi - c + 63) >> 6, q = c + lane * step;
+            const int n = __popcll(__ballot(q < hi && (int)starts[min(q, hi - 1)] <= slice));
+            c += (n - 1) * step;  // (starts[c] <= slice, so n >= 1)
+            hi = min(c + step, hi);
+        }
+        p -= (int)starts[c];
+        P = (int)starts[c + 1] - (int)starts[c];
     }
-    const int p = u / pl.tiles, tile = u % pl.tiles;
     const int sg = seg_of(a.seg, c);
     // slice p of P nearly equal ones (N <= 2^26)
     const long long n_beg = a.offsets[sg];
@@ -535,6 +546,39 @@ __global__ __launch_bounds__(kSliceThreads) void dense_slices_kernel(DenseArgs a
     }
 }
 
+// starts[c] = the first slice of class c (slices of at most len samples, class after
+// class), starts[C] = all of them: one block, a run of classes per thread.  Blocks of
+// dense_slices_kernel find their class in it where walking the classes would be long.
+constexpr int kStartThreads = 1024;
+
+__global__ __launch_bounds__(kStartThreads) void slice_starts_kernel(const int64_t *offsets,
+                                                                     const int32_t *seg, int C,
+                                                                     int len, uint32_t *starts)
+{
+    __shared__ uint32_t wsum[kStartThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int per = (C + kStartThreads - 1) / kStartThreads;
+    const int c0 = min((long long)t * per, (long long)C), c1 = min(c0 + per, C);
+    auto slices = [&](int c) {
+        const int sg = seg_of(seg, c);
+        return (uint32_t)slices_of(offsets[sg + 1] - offsets[sg], len);
+    };
+    uint32_t n = 0;
+#pragma unroll 4
+    for (int c = c0; c < c1; ++c) n += slices(c);
+    const uint32_t incl = scan_wave(n);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - n;
+    for (int w = 0; w < wave; ++w) at += wsum[w];
+#pragma unroll 4
+    for (int c = c0; c < c1; ++c) {
+        starts[c] = at;
+        at += slices(c);
+    }
+    if (t == kStartThreads - 1) starts[C] = at;
+}
+
 int dense_blocks_per_cu()
 {
     int n = 0;
@@ -551,10 +595,13 @@ static const SlicesKernel kSlicesKernels[kSliceShapes] = {
 
 hipError_t launch_dense(const DenseArgs &a, hipStream_t st)
 {
-    if (a.plan.direct)
+    if (a.plan.direct) {
+        if (!a.plan.P && a.C > kWalkClasses)
+            hipLaunchKernelGGL(slice_starts_kernel, dim3(1), dim3(kStartThreads), 0, st, a.offsets,
+                               a.seg, a.C, a.plan.len, a.claim);
         hipLaunchKernelGGL(kSlicesKernels[a.plan.shape], dim3((unsigned)a.plan.blocks),
                            dim3(kSliceThreads), 0, st, a);
-    else
+    } else
         hipLaunchKernelGGL(dense_kernel, dim3((unsigned)a.plan.blocks), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }

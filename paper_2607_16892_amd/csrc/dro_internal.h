@@ -34,7 +34,8 @@ struct DenseArgs {
     DensePlan plan;
     unsigned long long *R;  // [C][K][M] sums of |x - t| over the class's samples, zeroed first
                             // unless plan.stored
-    uint32_t *claim;        // [C * tiles + 1] slice counters per tile, then the total; zeroed first
+    uint32_t *claim;        // dense_claim_words: slice counters per tile, then the total, zeroed
+                            // first; direct: the classes' first slices (slice_starts_kernel)
 };
 
 hipError_t launch_dense(const DenseArgs &a, hipStream_t st);

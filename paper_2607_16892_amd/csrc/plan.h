@@ -103,6 +103,12 @@ constexpr long long kMinSliceN = 64;
 // an upper bound).
 constexpr int kSliceThreads = 1024;
 constexpr long long kMaxDirectBlocks = (1LL << 32) / kSliceThreads - 1;  // below 2^32 work-items
+// A block of unequal classes, some of several slices, finds its class by walking them 64
+// at a time up to kWalkClasses, else in a table of their first slices that one more
+// launch writes: walk against launch and search, 2,048 pairs, 128 classes 28.9 and
+// 33.5 us, 512 classes 67.2 and 66.8, 1,000 classes 142 and 116 (512 pairs, 5,000
+// classes: 693 and 119).
+constexpr int kWalkClasses = 512;
 constexpr int kMaxDirectSlice = 65536;
 constexpr double kLoop = 8.0, kBlockCycles = 12000.0, kPairCycles = 7.0, kZeroCycles = 6000.0;
 

@@ -2,7 +2,7 @@
 for bit against the oracle: tables of one pair, of one pair less and more than a
 tile of each shape (512 to 8,192 pairs), class sizes around the staging buffer
 (16,384 samples) and the sixteens of a step, more unequal classes than one wave
-looks through at once (64), a class of one sample beside long ones, and sums of
+looks through at once (64) and than a block walks (512), a class of one sample beside long ones, and sums of
 one slice (stored) as well as of several (added).  The pass over the table's rows
 at its edges: rows longer than its stage (2,048 multipliers), more rows than a
 block takes, and more (radius, row) tasks than a block has lanes.  W, m_star and
@@ -72,6 +72,20 @@ def test_more_unequal_classes_than_a_wave_holds(ctx, dev):
     sizes[64] = 60_000
     _check(ctx, dev, sizes, 7, 11)
     _check(ctx, dev, sizes[60:70], 20, 30, seg=[c % 10 for c in range(70)])
+
+
+# (walked up to 512, by the table of first slices beyond; a thread of that table's launch
+# holds one class up to 1,024)
+@pytest.mark.parametrize("C", [512, 513, 1024, 1025, 1500, 2049])
+def test_unequal_classes_around_the_table(ctx, dev, C):
+    rng = np.random.default_rng(C)
+    sizes = [int(v) for v in rng.integers(1, 120, 50)]
+    sizes[7], sizes[49] = 70_000, 3000
+    _check(ctx, dev, sizes, 7, 11, seg=rng.permutation([c % 50 for c in range(C)]))
+    if C <= 1025:
+        sizes = [int(v) for v in rng.integers(1, 60, C)]
+        sizes[-1] = 66_000
+        _check(ctx, dev, sizes, 5, 3)
 
 
 @pytest.mark.parametrize("K,M,E", [(3, 2047, 2), (3, 2048, 9), (2, 2049, 9), (2, 5000, 300),
