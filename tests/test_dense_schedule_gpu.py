@@ -1,46 +1,34 @@
 """The dense sums do not depend on how the launch schedules its work.
 
-Problems large enough for the persistent grid that claims sample slices (at
-least 65,536 (tile, sample) terms per resident block, 1,024 resident blocks),
-each bit for bit against the oracle's exact definitions (App. A, Steps 3-5):
+Problems that the launch plan gives to the persistent grid that claims sample
+slices (checked on the plan's CPU build; 1,024 resident blocks), each bit for bit against the oracle's exact definitions (App. A, Steps 3-5):
 every S[c,k,m], W[e,c,k], m_star, the optimum and the quantiles; and two runs
 give the same bytes.
 
 - A: ragged segments (2e6 samples, one sample, 3e5 uniform samples), classes
   aliasing segments, costs on both sides of c_w = c_p (both kink
-  orientations), whole tiles (K = 512, M = 128), and more resident blocks
+  orientations), whole tiles (K = 512, M = 128: 8 of 8,192 pairs), and more resident blocks
   than tiles, so that most blocks start by taking slices of tiles they do not
   own and slices of the one-sample segment are empty.
-- B: partial tiles in both directions (K = 300 over tiles of 128 grid
-  points, M = 50 of a 64-multiplier tile), 9 tiles in all, one segment of
-  1.2e7 samples and one of 5, so nearly every slice of the short segment's
-  tiles is empty.
-- C: more tiles than resident blocks (1,152), so every block starts with more
-  than one tile of its own: 128 classes on 4 aliased segments of 1e5 samples,
-  K = 1025 (the last k-tile holds one grid point), M = 33 (half a tile),
-  cost ratios up to 2^17 either way.
+- B: a partial tile (K = 300, M = 50: 15,000 pairs, 1,384 short of two tiles),
+  6 tiles in all, one segment of 1.2e7 samples and one of 5, so nearly every
+  slice of the short segment's tiles is empty.
+- C: more tiles than resident blocks (1,152), so every block starts with one
+  tile of its own or two: 128 classes on 4 aliased segments of 1e5 samples,
+  K = 1023, M = 72 (73,656 pairs, 72 short of nine tiles), cost ratios up to
+  2^17 either way.
 """
 import numpy as np
 import pytest
 
 import oracle
+from plan_cpu import workload_plan
 from workloads.configs import Workload, _csr, _f32, eta_grid, lam_grid
 
 pytestmark = pytest.mark.gpu
 
 RESIDENT = 1024   # resident blocks of the dense launch (256 compute units x 4)
-DIRECT_TERMS = 65536
-
-
-def tiles_per_class(K, M, threads=256, tm=32):
-    """Tiles of one class as the dense launch forms them: lanes_m, a power of
-    two, covers M in groups of tm multipliers; the remaining lanes take grid
-    points."""
-    lanes_m = 1
-    while lanes_m < -(-M // tm) and lanes_m < threads:
-        lanes_m *= 2
-    lanes_k = threads // lanes_m
-    return -(-K // lanes_k) * -(-M // (tm * lanes_m))
+TILES = {"a": 5 * 8, "b": 3 * 2, "c": 128 * 9}
 
 
 def _case_a():
@@ -89,8 +77,8 @@ def _case_c():
     c_w = _f32([choices[i][1] for i in pick])
     eps = _f32(rng.uniform(0.0, 200.0, E * C))
     eps[:C] = 0.0
-    return Workload("schedule-c", C, offsets, seg, xi, np.full(C, L, np.int32), eta_grid(1025, L),
-                    lam_grid(33, 0.01, 100.0), c_p, c_w, E, eps)
+    return Workload("schedule-c", C, offsets, seg, xi, np.full(C, L, np.int32), eta_grid(1023, L),
+                    lam_grid(72, 0.01, 100.0), c_p, c_w, E, eps)
 
 
 CASES = {"a": _case_a, "b": _case_b, "c": _case_c}
@@ -112,11 +100,9 @@ def _run(ctx, dev, w):
 def test_claimed_slices_give_the_exact_table(dev, case):
     import paper_2607_16892_amd as dro
     w = CASES[case]()
-    T = w.C * tiles_per_class(w.K, w.M)
-    max_n = int(np.diff(w.offsets).max())
-    assert T * max_n >= DIRECT_TERMS * RESIDENT  # past the one-block-per-slice bound
-    if case == "c":
-        assert T > RESIDENT
+    plan = workload_plan(w)
+    T = w.C * plan["tiles"]
+    assert not plan["direct"] and T == TILES[case] and plan["blocks"] == RESIDENT
     print(f"[gpu] {w.name}: C={w.C} K={w.K} M={w.M} E={w.E} N={int(w.offsets[-1])} tiles={T}",
           flush=True)
     with dro.Context(dev.index or 0) as ctx:

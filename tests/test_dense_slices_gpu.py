@@ -1,9 +1,11 @@
 """The one-block-per-slice schedule of the dense evaluation at its edges, S bit
-for bit against the oracle: tables of one pair, of one pair less and more than a
-tile of each shape (512 to 8,192 pairs), class sizes around the staging buffer
-(16,384 samples) and the sixteens of a step, more unequal classes than one wave
-looks through at once (64) and than a block walks (512), a class of one sample beside long ones, and sums of
-one slice (stored) as well as of several (added).  The pass over the table's rows
+for bit against the oracle: for each of the five tile shapes (512 to 8,192 pairs)
+tables of one pair less, as many and one more than whole tiles, and slices around one
+and two staging buffers (16,384 samples), in problems for which the launch plan (read
+from its CPU build) takes that shape; tables of one pair and of a few; class sizes
+around the sixteens of a step; more unequal classes than one wave looks through at
+once (64) and than a block walks (512), a class of one sample beside long ones, and
+sums of one slice (stored) as well as of several (added).  The pass over the table's rows
 at its edges: rows longer than its stage (2,048 multipliers), more rows than a
 block takes, and more (radius, row) tasks than a block has lanes.  W, m_star and
 the optimum are checked with S.
@@ -12,6 +14,7 @@ import numpy as np
 import pytest
 
 import oracle
+from plan_cpu import PAIRS, dense_plan
 from workloads.configs import Workload, _csr, _f32, eta_grid, lam_grid
 
 pytestmark = pytest.mark.gpu
@@ -52,6 +55,39 @@ def _check(ctx, dev, sizes, K, M, L=32768, seg=None, E=1):
     k, ws = oracle.argmin(W)
     assert np.array_equal(a["k_star"].cpu().numpy(), k)
     assert np.array_equal(a["W_star"].cpu().numpy().view(np.uint64), ws.view(np.uint64))
+
+
+# classes of 300 samples each, and the table: one pair less, as many, one more than tiles
+@pytest.mark.parametrize("shape,C,K,M", [
+    (0, 64, 983, 25), (0, 64, 768, 32), (0, 32, 10923, 3),
+    (1, 32, 20479, 1), (1, 32, 640, 32), (1, 8, 10923, 3),
+    (2, 32, 3413, 3), (2, 32, 320, 32), (2, 8, 565, 29),
+    (3, 32, 5119, 1), (3, 32, 160, 32), (3, 4, 1229, 5),
+    (4, 1, 73, 7), (4, 1, 16, 32), (4, 1, 27, 19)])
+def test_every_shape_around_its_tiles(ctx, dev, shape, C, K, M):
+    p = dense_plan({300: C}, K, M)
+    assert p["direct"] and p["shape"] == shape and (K * M + 1) % PAIRS[shape] <= 2
+    _check(ctx, dev, (300, 300), K, M, seg=[c % 2 for c in range(C)])
+
+
+# one block per class and tile: a slice is the class's n samples
+@pytest.mark.parametrize("n", [16_383, 16_384, 16_385, 32_769])
+@pytest.mark.parametrize("shape,C,K,M", [(0, 256, 8191, 1), (1, 256, 819, 5), (2, 256, 89, 23),
+                                         (3, 256, 341, 3), (4, 256, 73, 7)])
+def test_every_shape_around_its_buffers(ctx, dev, shape, C, K, M, n):
+    p = dense_plan({n: C}, K, M)
+    assert p["direct"] and p["shape"] == shape and p["P"] == 1
+    _check(ctx, dev, (n, n), K, M, seg=[c % 2 for c in range(C)])
+
+
+# a long slice's sums added to another's
+@pytest.mark.parametrize("shape,C,K,M", [(0, 128, 8191, 1), (1, 128, 819, 5), (2, 64, 89, 23),
+                                         (3, 64, 27, 19), (4, 64, 73, 7)])
+def test_every_shape_with_several_long_slices(ctx, dev, shape, C, K, M):
+    n = 65_537
+    p = dense_plan({n: C}, K, M)
+    assert p["direct"] and p["shape"] == shape and p["P"] > 1 and n // p["P"] >= 16_384
+    _check(ctx, dev, (n, n), K, M, seg=[c % 2 for c in range(C)])
 
 
 @pytest.mark.parametrize("K,M", [(1, 1), (1, 511), (64, 8), (27, 19), (32, 32), (25, 41),

@@ -2,15 +2,18 @@
 with at most 2^20 blocks (so a grid stays below 2^32 work-items).  These tests
 take each loop past one pass, against the oracle's exact definitions:
 
-- dro_argmin_reservation on C K = 4.7e6 rows (the minimum over the
-  multipliers: 4 rows per block, two passes) and E C = 2^20 + 6 radius rows
-  (the argmin, one block per row, two passes), from an exact S table drawn
-  with many ties (App. A Step 3, Prop. 4.2; ties to the lowest k, then m);
+- dro_cost_eval and dro_argmin_reservation on C K = 67,143,681 rows of one
+  multiplier (the pass over the rows, in both its forms: 64 rows per block,
+  two passes; App. A Steps 3-5);
+- dro_argmin_reservation on E C = 2^20 + 6 radius rows (the argmin, one
+  block per row, two passes), from an exact S table drawn with many ties
+  (Prop. 4.2; ties to the lowest k, then m);
 - class_quantile on 2^20 + 5 classes (the select, one block per class), and
   class_moments and bcd_init_state on 2^22 + 9 (four per block);
-- dro_cost_eval on a C K M = 268,500,992-entry table, past the 2^28 items
-  of one pass of the zero fill and the exact epilogue, checked at sampled
-  entries that include the last ones (App. A Steps 4-5);
+- dro_cost_eval on a C K M = 276,891,648-entry table whose last class is
+  long enough to be split, so that its sums are added to zeros past the
+  2^28 items of one pass of the zero fill, checked at sampled entries that
+  include the last ones (App. A Steps 4-5);
 - 2^31 - 1 radius rows, the limit, of which the last step of a 32-bit loop
   index would pass its range.
 """
@@ -18,6 +21,7 @@ import numpy as np
 import pytest
 
 import oracle
+from plan_cpu import workload_plan
 from workloads.configs import Workload, _csr, _f32, eta_grid, lam_grid
 
 pytestmark = pytest.mark.gpu
@@ -37,6 +41,43 @@ def _costs(rng, C):
     return _f32([choice[i][0] for i in pick]), _f32([choice[i][1] for i in pick])
 
 
+def test_table_rows_past_one_pass(ctx, dev):
+    import torch
+    import paper_2607_16892_amd as dro
+    rng = np.random.default_rng(30)
+    C, K, M, L = 2049, 32769, 1, 32768
+    assert C * K > 64 << 20
+    parts = [rng.integers(0, L + 1, n).astype(np.int32) for n in (3, 5)]
+    offsets, xi = _csr(parts)
+    seg = (np.arange(C) % 2).astype(np.int32)
+    c_p, c_w = _costs(rng, C)
+    eps = _f32(rng.uniform(0.0, 50.0, C))
+    w = Workload("rows", C, offsets, seg, xi, np.full(C, L, np.int32), eta_grid(K, L),
+                 lam_grid(2, 0.5, 8.0)[:1], c_p, c_w, 1, eps)
+    print(f"[gpu] table rows: C={C} K={K}", flush=True)
+    prob = dro.Problem.from_workload(w, dev)
+    e = torch.from_numpy(eps).to(dev)
+    r = dro.dro_cost_eval(ctx, prob, e)
+    a = dro.dro_argmin_reservation(ctx, prob, e, r["S"])
+    torch.cuda.synchronize()
+    S = r["S"].view(C, K)
+    # entries of the last classes (past the first pass) and of all
+    cs = np.concatenate([np.full(3000, C - 1), rng.integers(0, C, 3000)])
+    ks = rng.integers(0, K, cs.size)
+    ref = oracle.S_exact_at(w, cs, ks, np.zeros_like(cs)).to_double()
+    got = S[torch.from_numpy(cs).to(dev), torch.from_numpy(ks).to(dev)].cpu().numpy()
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+    # with one multiplier W = RN(RN(lam eps) + RN(S / N)) at every row
+    N = torch.tensor([3.0, 5.0], dtype=torch.float64, device=dev)[torch.from_numpy(seg).to(dev).long()]
+    W = (float(w.lam[0]) * e.double())[:, None] + S / N[:, None]
+    assert torch.equal(r["W"][0], W) and int(r["m_star"].abs().max()) == 0
+    Wh = W.cpu().numpy()
+    k = Wh.argmin(1)
+    assert np.array_equal(a["k_star"][0].cpu().numpy(), k)
+    assert np.array_equal(a["W_star"][0].cpu().numpy(), Wh[np.arange(C), k])
+    assert int(a["m_at_star"].abs().max()) == 0
+
+
 def test_argmin_rows_past_one_pass(ctx, dev):
     import torch
     import paper_2607_16892_amd as dro
@@ -50,7 +91,7 @@ def test_argmin_rows_past_one_pass(ctx, dev):
     eps[:C] = 0.0
     w = Workload("rows", C, offsets, seg, xi, np.full(C, L, np.int32), eta_grid(K, L),
                  lam_grid(M, 0.5, 8.0), c_p, c_w, E, eps)
-    assert C * K > 4 << 20 and E * C > 1 << 20
+    assert E * C > 1 << 20
     # an exact S table (units of 2^-33) with ties: values from a small set
     lo = (rng.integers(0, 64, (C, K, M)).astype(np.uint64) << np.uint64(36))
     S = oracle.ExactS(np.zeros((C, K, M), np.int64), lo)
@@ -113,21 +154,24 @@ def test_cost_eval_table_past_one_pass(ctx, dev):
     import torch
     import paper_2607_16892_amd as dro
     rng = np.random.default_rng(33)
-    C, K, M, E, L = 32, 4097, 2048, 1, 4096
+    C, K, M, E, L = 33, 4097, 2048, 1, 4096
     offsets, xi = _csr([rng.integers(0, L + 1, 3).astype(np.int32),
-                        np.array([0, L, 17], np.int32)])
+                        np.array([0, L, 17], np.int32),
+                        rng.integers(0, L + 1, 70_000).astype(np.int32)])
     seg = (np.arange(C) % 2).astype(np.int32)
+    seg[C - 1] = 2
     c_p, c_w = _costs(rng, C)
     eps = _f32(rng.uniform(0.0, 30.0, E * C))
     w = Workload("table", C, offsets, seg, xi, np.full(C, L, np.int32), eta_grid(K, L),
                  lam_grid(M, 2.0 ** -10, 2.0 ** 7), c_p, c_w, E, eps)
     n = C * K * M
-    assert n > (1 << 20) * 256
+    assert (C - 1) * K * M >= (1 << 20) * 256 and not workload_plan(w)["stored"]
     print(f"[gpu] cost eval table: C={C} K={K} M={M} ({n} entries)", flush=True)
     prob = dro.Problem.from_workload(w, dev)
-    r = dro.dro_cost_eval(ctx, prob, torch.from_numpy(eps).to(dev))
+    S = torch.full((C, K, M), float("nan"), dtype=torch.float64, device=dev)
+    r = dro.dro_cost_eval(ctx, prob, torch.from_numpy(eps).to(dev), S=S)
     torch.cuda.synchronize()
-    Sg = r["S"].view(-1)
+    Sg = S.view(-1)
     # sampled entries, the last 4096 of the table among them
     idx = np.unique(np.concatenate([rng.integers(0, n, 3000), np.arange(n - 4096, n)]))
     cs, ks, ms = idx // (K * M), (idx // M) % K, idx % M

@@ -2,56 +2,19 @@
 the CPU: over sizes from one sample to millions of classes every plan keeps its
 grid below 2^32 work-items and covers all samples.
 """
-import ctypes as ct
 import math
-import os
 import random
-import subprocess
 
 import pytest
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
-                    "paper_2607_16892_amd", "csrc")
-SRC = r'''
-#include "plan.h"
-extern "C" void plan(int n, const long long *size, const long long *count, int C, int K, int M,
-                     long long *out)
-{
-    auto each = [&](auto &&add) {
-        for (int i = 0; i < n; ++i) add(size[i], count[i]);
-    };
-    const dro::DensePlan p = dro::plan_dense(each, C, K, M, 256, 4);
-    const long long v[] = {p.tiles, p.P, p.direct, p.shape, p.len, p.stored, p.blocks};
-    for (int i = 0; i < 7; ++i) out[i] = v[i];
-}
-'''
-SHAPES = [32 * 256, 32 * 128, 32 * 64, 16 * 64, 8 * 64]  # pairs of a tile
-
-
-@pytest.fixture(scope="module")
-def plan(tmp_path_factory):
-    d = tmp_path_factory.mktemp("plan")
-    (d / "plan.cpp").write_text(SRC)
-    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"),
-                    "-o", str(d / "plan.so")], check=True)
-    lib = ct.CDLL(str(d / "plan.so"))
-
-    def run(sizes, K, M):
-        """sizes: {segment size: classes}."""
-        z = sorted(sizes.items())
-        out = (ct.c_longlong * 7)()
-        lib.plan(len(z), (ct.c_longlong * len(z))(*[a for a, _ in z]),
-                 (ct.c_longlong * len(z))(*[b for _, b in z]), sum(b for _, b in z), K, M, out)
-        return dict(zip(("tiles", "P", "direct", "shape", "len", "stored", "blocks"), out))
-
-    return run
+from plan_cpu import PAIRS, dense_plan
 
 
 def _check(p, sizes, K, M):
     threads = 1024 if p["direct"] else 256
     assert 0 < p["blocks"] and p["blocks"] * threads < 1 << 32
     if p["direct"]:
-        assert p["tiles"] == -(-K * M // SHAPES[p["shape"]]) and 1 <= p["len"] <= 65536
+        assert p["tiles"] == -(-K * M // PAIRS[p["shape"]]) and 1 <= p["len"] <= 65536
         slices = {n: -(-n // p["len"]) for n in sizes}
         assert p["blocks"] == p["tiles"] * sum(slices[n] * c for n, c in sizes.items())
         assert p["stored"] == all(s == 1 for s in slices.values())
@@ -65,12 +28,12 @@ def _check(p, sizes, K, M):
 
 @pytest.mark.parametrize("K,M", [(50, 10), (16, 16), (1, 1), (32, 16), (64, 32)])
 @pytest.mark.parametrize("C", [(1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 24) + 3, 1 << 21])
-def test_millions_of_classes(plan, C, K, M):
+def test_millions_of_classes(C, K, M):
     for sizes in ({100: C}, {100: C - 1, 70_000: 1}, {1: C // 2, 60_000: C - C // 2}):
-        _check(plan(sizes, K, M), sizes, K, M)
+        _check(dense_plan(sizes, K, M), sizes, K, M)
 
 
-def test_sizes_over_the_whole_range(plan):
+def test_sizes_over_the_whole_range():
     rng = random.Random(5)
 
     def log(lo, hi):
@@ -80,23 +43,23 @@ def test_sizes_over_the_whole_range(plan):
         sizes = {log(1, 1 << 26): log(1, 1 << 12) for _ in range(rng.choice([1, 1, 2, 7, 60]))}
         K, M = log(1, 32769), log(1, 65536)
         if K * M < 1 << 31:
-            _check(plan(sizes, K, M), sizes, K, M)
+            _check(dense_plan(sizes, K, M), sizes, K, M)
 
 
 @pytest.mark.parametrize("distinct", [63, 64, 65, 200, 5000])
 @pytest.mark.parametrize("K,M", [(7, 11), (64, 32), (1000, 200)])
-def test_more_sizes_than_the_plan_lists(plan, distinct, K, M):
+def test_more_sizes_than_the_plan_lists(distinct, K, M):
     rng = random.Random(distinct + K)
     sizes = {}
     while len(sizes) < distinct:
         sizes[rng.choice([rng.randint(1, 40), rng.randint(1, 90_000), rng.randint(1, 300)])
               if distinct < 300 else rng.randint(1, 90_000)] = rng.randint(1, 3)
-    _check(plan(sizes, K, M), sizes, K, M)
+    _check(dense_plan(sizes, K, M), sizes, K, M)
 
 
-def test_equal_sizes_give_the_plan_of_their_count(plan):
+def test_equal_sizes_give_the_plan_of_their_count():
     # bins hold their largest size, so sizes of one bin plan as if all had it
     a = {1024 + i: 2 for i in range(100)}  # one bin, more sizes than are listed one by one
-    p, q = plan(a, 64, 32), plan({1123: 200}, 64, 32)
+    p, q = dense_plan(a, 64, 32), dense_plan({1123: 200}, 64, 32)
     assert {k: p[k] for k in ("direct", "shape", "len")} == {k: q[k] for k in ("direct", "shape", "len")}
     _check(p, a, 64, 32)

@@ -1,6 +1,6 @@
 """The exact table's search over the multipliers where its shortcuts end, against
 the oracle's scan over every multiplier (W by bits, the lowest m, the optimum):
-one and two multipliers, grids past the block's staged ones (2048), radii at
+one and two multipliers, grids past the block's staged ones (1,024), radii at
 which J is flat or nearly flat in the multiplier (every sample at the radius, so
 that the slope is zero over many multipliers; radius 0; radii a rounding away),
 and multipliers above and below both costs.  A multiplier grid that is not
