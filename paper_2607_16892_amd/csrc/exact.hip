@@ -12,6 +12,7 @@
 // is J = RN(RN(lam eps) + RN(RN(S) / N)) with RN(S) the correctly rounded
 // double of the exact sum.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "dro_internal.h"
@@ -310,11 +311,33 @@ __global__ __launch_bounds__(kQThreads) void qhist_kernel(const int64_t *offsets
     }
 }
 
+// The sum of f(p[r stride]) over the rows r = g, g + kStep, ... below B.
+template <int kStep, class F>
+__device__ __forceinline__ uint32_t sum_rows(const uint32_t *p, int stride, int g, int B, F &&f)
+{
+    uint32_t a = 0;
+    auto take = [&](auto n) {  // n rows, every load in flight
+        constexpr int kN = decltype(n)::value;
+        for (; g + (kN - 1) * kStep < B; g += kN * kStep) {
+            uint32_t x[kN];
+#pragma unroll
+            for (int i = 0; i < kN; ++i) x[i] = p[(long long)(g + i * kStep) * stride];
+#pragma unroll
+            for (int i = 0; i < kN; ++i) a += f(x[i]);
+        }
+    };
+    take(std::integral_constant<int, 16>{});
+    take(std::integral_constant<int, 4>{});
+    take(std::integral_constant<int, 1>{});
+    return a;
+}
+
 // Class c (segment s, its B rows at s B0 or boff[s]; classes in a
 // block-uniform loop): the coarse counts of the rows summed per bucket, the
 // bucket holding the exact rank j, then the counts of its values summed over
-// the rows, and the value where the cumulative count reaches j.  Every thread
-// issues its share of the rows' loads together.
+// the rows, and the value where the cumulative count reaches j.  A thread has 16
+// rows' loads in flight, as a class of many rows (763 of 5e7 samples) is a chain of
+// round trips else.
 __device__ void qselect_class(const int64_t *offsets, const int32_t *seg, const float *c_p,
                               const float *c_w, const uint32_t *fine, const uint32_t *coarse, int B0,
                               const int64_t *boff, int c, int32_t *q_value, int64_t *q_rank)
@@ -343,17 +366,7 @@ __device__ void qselect_class(const int64_t *offsets, const int32_t *seg, const 
     const uint32_t *fs = fine + row0 * kQStride;
     {
         const int q = t % kQBuckets, g = t / kQBuckets;
-        uint32_t a = 0;
-        int bb = g;
-        for (; bb + 3 * kG < B; bb += 4 * kG) {
-            const uint32_t x0 = cs[(long long)bb * kQBuckets + q];
-            const uint32_t x1 = cs[(long long)(bb + kG) * kQBuckets + q];
-            const uint32_t x2 = cs[(long long)(bb + 2 * kG) * kQBuckets + q];
-            const uint32_t x3 = cs[(long long)(bb + 3 * kG) * kQBuckets + q];
-            a += (x0 + x1) + (x2 + x3);
-        }
-        for (; bb < B; bb += kG) a += cs[(long long)bb * kQBuckets + q];
-        part[g][q] = a;
+        part[g][q] = sum_rows<kG>(cs + q, kQBuckets, g, B, [](uint32_t x) { return x; });
     }
     if (t == 0) sel = -1;
     if (t < 2) s_off[t] = r_off;         // offsets[s], offsets[s + 1]
@@ -392,20 +405,12 @@ __device__ void qselect_class(const int64_t *offsets, const int32_t *seg, const 
         const int v = v0 + o;
         const int w = v & (kQTop / 2 - 1), sh = (v >> 10) & 16;
         const bool top = bk == kQBuckets - 1 && o == 0;
-        uint32_t a = 0, a_top = 0;
-        int bb = g;
-        for (; bb + 3 * kFG < B; bb += 4 * kFG) {
-            const uint32_t x0 = fs[(long long)bb * kQStride + w];
-            const uint32_t x1 = fs[(long long)(bb + kFG) * kQStride + w];
-            const uint32_t x2 = fs[(long long)(bb + 2 * kFG) * kQStride + w];
-            const uint32_t x3 = fs[(long long)(bb + 3 * kFG) * kQStride + w];
-            a += ((x0 >> sh) & 0xffffu) + ((x1 >> sh) & 0xffffu) + ((x2 >> sh) & 0xffffu) +
-                 ((x3 >> sh) & 0xffffu);
-        }
-        for (; bb < B; bb += kFG) a += (fs[(long long)bb * kQStride + w] >> sh) & 0xffffu;
+        fpart[g][o] = sum_rows<kFG>(fs + w, kQStride, g, B,
+                                    [&](uint32_t x) { return (x >> sh) & 0xffffu; });
+        uint32_t a_top = 0;
         if (top)
-            for (int r = g; r < B; r += kFG) a_top += fs[(long long)r * kQStride + kQTop / 2] & 0xffffu;
-        fpart[g][o] = a;
+            a_top = sum_rows<kFG>(fs + kQTop / 2, kQStride, g, B,
+                                  [](uint32_t x) { return x & 0xffffu; });
         if (o == 0) fpart[g][128] = a_top;
     }
     __syncthreads();
