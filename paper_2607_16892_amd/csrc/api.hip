@@ -211,7 +211,8 @@ RowPlan plan_rows(dro_ctx *ctx, const dro_problem *p)
     RowPlan pl{};
     bool uniform = true;
     for (int s = 0; s < p->S; ++s) {
-        const long long b = row_parts(o[s + 1] - o[s], len);
+        const long long n = o[s + 1] - o[s], b = row_parts(n, len);
+        pl.longest = std::max(pl.longest, (n + b - 1) / b);
         if (s == 0) pl.B = (int)b;
         else if (b != pl.B) uniform = false;
         pl.rows += b;

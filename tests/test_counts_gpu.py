@@ -64,6 +64,29 @@ def test_every_prefix_entry(ctx, dev, sizes):
         assert int(k0[c]) == np.flatnonzero(w.eta.astype(np.int64) * n <= x64.sum()).max()
 
 
+# one wave a row up to 4,096 samples in the longest, else four
+@pytest.mark.parametrize("sizes", [(4096, 1, 777), (4097, 1, 65), (63, 64, 65), (16_384, 255),
+                                   (256, 257) * 400])
+def test_moments_at_either_block_size(ctx, dev, sizes):
+    import paper_2607_16892_amd as dro
+    rng = np.random.default_rng(sum(sizes))
+    parts = [rng.integers(0, 32769, n).astype(np.int32) for n in sizes]
+    C = len(parts)
+    off, xi = _csr(parts)
+    w = Workload("moments", C, off, None, xi, np.full(C, 32768, np.int32), eta_grid(129, 32768),
+                 lam_grid(2), _f32([1] * C), _f32([1] * C), 1, np.zeros(C, np.float32))
+    prob = dro.Problem.from_workload(w, dev)
+    print(f"[gpu] moments of {C} segments", flush=True)
+    m = {k: v.cpu().numpy() for k, v in dro.class_moments(ctx, prob).items()}
+    k0 = dro.bcd_init_state(ctx, prob).cpu().numpy()
+    eta = w.eta.astype(np.int64)
+    for c, x in enumerate(parts):
+        x = x.astype(np.int64)
+        assert [int(m[k][c]) for k in ("count", "sum", "sumsq", "xmax")] == \
+            [len(x), x.sum(), (x * x).sum(), x.max()]
+        assert k0[c] == np.flatnonzero(eta * len(x) <= x.sum()).max()
+
+
 def test_merged_histogram_where_the_rows_do_not_fit(dev):
     import torch
     import paper_2607_16892_amd as dro
