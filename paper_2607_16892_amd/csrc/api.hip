@@ -213,6 +213,7 @@ RowPlan plan_rows(dro_ctx *ctx, const dro_problem *p)
     for (int s = 0; s < p->S; ++s) {
         const long long n = o[s + 1] - o[s], b = row_parts(n, len);
         pl.longest = std::max(pl.longest, (n + b - 1) / b);
+        pl.most = std::max(pl.most, b);
         if (s == 0) pl.B = (int)b;
         else if (b != pl.B) uniform = false;
         pl.rows += b;
@@ -377,14 +378,26 @@ long long max_segment(const dro_problem *p)
     return max_seg;
 }
 
-// Prefix entries of every segment: counted in packed rows while their scratch
-// stays within kMaxCountRows rows (270 MB), else through a merged histogram,
-// whose scratch does not grow with the samples (rows hold at most 65,535 each,
-// so it takes over beyond 2.7e8 samples, and where the no-allocation array
-// cannot hold the rows).
+// Prefix entries of every segment: counted in packed rows, or through a merged histogram
+// where there are many rows and the histogram's blocks are about equally long: each row
+// stores its 64 KB of counts and the prefix pass reads a segment's rows in 32 blocks, while
+// a merged block holds any number of samples but adds its counts with atomics, after a zero
+// fill, and every segment gets as many blocks.  Packed against merged
+// (dro_reservation_cost, us): 1 segment of 2e6 (122 rows) 42 and 48, of 4e6 (245) 53 and
+// 52, of 5e7 (763) 116 and 76; 8 of 4e6 (62 each) 59 and 65, of 1e7 (153 each) 118 and 101;
+// 16 of 4e6 (62 each) 95 and 83; 40 of 1e6 (16 each) 74 and 78, of 2e6 (31 each) 126 and
+// 110; 1,000 of 3e4 (2 each) 339 and 323.  A segment of 2e7 beside one of 100: 70 and 60,
+// beside 100 of 1,000: 81 and 574.  The rows' scratch ends at kMaxCountRows (270 MB), where
+// the no-allocation array cannot hold the rows either.
 constexpr long long kMaxCountRows = 4096;
 
-bool packed_rows(const RowPlan &pl) { return pl.rows <= kMaxCountRows; }
+bool packed_rows(const RowPlan &pl, const dro_problem *p, int num_cu)
+{
+    if (pl.rows > kMaxCountRows) return false;
+    if (pl.most <= 200 && (pl.rows <= 3LL * num_cu || pl.rows < 8LL * p->S)) return true;
+    const long long max_seg = max_segment(p);
+    return max_seg > 8 * kQMaxPart * hist_parts(p->S, max_seg, num_cu);
+}
 
 size_t prefix_bytes(const dro_problem *p)
 {
@@ -613,7 +626,7 @@ int dro_cost_eval(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *ep
     dro_problem q;
     RowPlan rows;
     if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
-    const bool packed = packed_rows(rows);
+    const bool packed = packed_rows(rows, p, ctx->num_cu);
     rc = ensure_ws(ctx, (S ? 0 : rup(ckm * 8)) + cost_eval_scratch_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
@@ -645,7 +658,7 @@ int dro_cost_eval_noalloc(dro_ctx *ctx, const dro_problem *p, int32_t E, const f
     dro_problem q;
     RowPlan rows = plan_rows(ctx, p);
     const bool packed =
-        packed_rows(rows) && stage_bytes(p) + rup(((size_t)p->S + 1) * 8) +
+        packed_rows(rows, p, ctx->num_cu) && stage_bytes(p) + rup(((size_t)p->S + 1) * 8) +
                                      cost_eval_scratch_bytes(p, rows, true) <=
                                  (size_t)DRO_NOALLOC_SCRATCH_BYTES;
     if ((rc = stage_in_arena(ctx, p, ar, packed, (hipStream_t)stream, &q, &rows))) return rc;
@@ -720,7 +733,7 @@ int dro_exact_table(dro_ctx *ctx, const dro_problem *p, int32_t E, const float *
     dro_problem q;
     RowPlan rows;
     if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
-    const bool packed = packed_rows(rows);
+    const bool packed = packed_rows(rows, p, ctx->num_cu);
     rc = ensure_ws(ctx, counts_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
@@ -746,7 +759,7 @@ int dro_continuous_dual(dro_ctx *ctx, const dro_problem *p, int32_t E, const flo
     dro_problem q;
     RowPlan rows;
     if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
-    const bool packed = packed_rows(rows);
+    const bool packed = packed_rows(rows, p, ctx->num_cu);
     rc = ensure_ws(ctx, counts_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
@@ -794,7 +807,7 @@ int dro_reservation_cost(dro_ctx *ctx, const dro_problem *p, int32_t R, const in
     dro_problem q;
     RowPlan rows;
     if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
-    const bool packed = packed_rows(rows);
+    const bool packed = packed_rows(rows, p, ctx->num_cu);
     rc = ensure_ws(ctx, counts_bytes(p, rows, packed), st);
     if (rc) return rc;
     Arena ar{(char *)ctx->ws, 0};
@@ -871,7 +884,7 @@ int bcd_block_step(dro_ctx *ctx, const dro_problem *p, const float *eps, const d
     dro_problem q;
     RowPlan rows;
     if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
-    const bool packed = packed_rows(rows);
+    const bool packed = packed_rows(rows, p, ctx->num_cu);
     const size_t need = rup(ckm * 8) + cost_eval_scratch_bytes(p, rows, packed) +
                         rup((size_t)C * p->K * 8) + rup((size_t)C * p->K * 4) + rup((size_t)C * 4);
     rc = ensure_ws(ctx, need, st);
@@ -1169,7 +1182,7 @@ int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dr
     dro_problem q;
     RowPlan rows;
     if ((rc = stage_problem(ctx, p, st, &q, &rows))) return rc;
-    const bool packed = packed_rows(rows);
+    const bool packed = packed_rows(rows, p, ctx->num_cu);
     const size_t need = counts_bytes(p, rows, packed) + rup((size_t)rows.rows * sizeof(RowMoments)) +
                         rup((size_t)C * K * 8) + rup((size_t)C * K * 4) +
                         4 * rup((size_t)C * 8) + rup(lp1_work_doubles(C, G) * 8) +

@@ -100,6 +100,7 @@ struct RowPlan {
     int B;
     const int64_t *boff;
     long long longest;  // samples of the longest row, at most
+    long long most;     // rows of the segment with the most
 };
 // samples per part: about one part per compute unit over all segments (host offsets)
 long long row_part_len(const int64_t *offsets_h, int S, int num_cu);

@@ -2,7 +2,8 @@
 that build them: one row of counts per segment and more rows than the pass has
 waves (16), values on both sides of its runs (512 values), of the packed halves
 (2^14) and 2^15 itself, segments with unequal row counts, and the merged
-histogram that takes over where the scratch cannot hold the rows.
+histogram that takes over beyond 200 rows of a segment, beyond 768 rows of
+segments of 8 or more, and where the scratch cannot hold the rows.
 
 dro_reservation_cost at every integer reservation reads every entry: cover is
 the count and the cost follows from the sum, so both are compared exactly with
@@ -28,8 +29,11 @@ def ctx(dev):
     c.close()
 
 
+# (the last three through the merged histogram: 214 rows of one segment, 254 of one beside
+# two short ones, 806 of 13)
 @pytest.mark.parametrize("sizes", [(1,), (15,), (16_385,), (20, 300_001, 1, 40_000),
-                                   (600_000,) * 3, (1_100_000,)])
+                                   (600_000,) * 3, (1_100_000,), (3_250_000,),
+                                   (3_500_000,), (3, 5_000_000, 40), (4_000_000,) * 13])
 def test_every_prefix_entry(ctx, dev, sizes):
     import torch
     import paper_2607_16892_amd as dro
