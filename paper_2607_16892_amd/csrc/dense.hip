@@ -802,11 +802,81 @@ __global__ __launch_bounds__(kRowThreads) void row_min_kernel(RowMinArgs a, int 
     }
 }
 
+// The minimum over the multipliers from an S that is there, one wave per row: the wave
+// stages q_m = S / N and lambda_m of a chunk of multipliers, its lanes split over up to 64
+// radii, and nothing waits for another wave.  Bound by reading S where the rows are many
+// and long.
+constexpr int kWaveRows = 4;     // waves (rows) per block
+constexpr int kWaveChunk = 256;  // multipliers staged per wave at a time
+constexpr int kWaveRadii = 32;   // radii at most
+
+__global__ __launch_bounds__(64 * kWaveRows) void row_min_wave_kernel(RowMinArgs a)
+{
+    __shared__ double2 st[kWaveRows][kWaveChunk];  // (q_m, lambda_m)
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, M = a.M;
+    int lg = 0;  // log2 of the radii's groups of lanes
+    while ((1 << lg) < a.E) ++lg;
+    const int lp = 64 >> lg, part = lane & (lp - 1), e = lane / lp;
+    double2 *q = st[w];
+    // rows in a loop of whole waves (no block barrier)
+    for (long long ck = (long long)blockIdx.x * kWaveRows + w; ck < (long long)a.C * a.K;
+         ck += (long long)gridDim.x * kWaveRows) {
+        const int c = (int)(ck / a.K), k = (int)(ck % a.K);
+        const int s = seg_of(a.seg, c);
+        const double N = (double)(a.offsets[s + 1] - a.offsets[s]);
+        const double *row = a.S + ck * M;
+        const double ev = e < a.E ? (double)a.eps[(long long)e * a.C + c] : 0.0;
+        double best = __builtin_inf();
+        int bm = M;  // no multiplier yet: loses every comparison below
+        for (int m0 = 0; m0 < M; m0 += kWaveChunk) {
+            const int mc = min(kWaveChunk, M - m0);
+            __builtin_amdgcn_wave_barrier();  // the last chunk's reads come first
+            for (int i = lane; i < mc; i += 64)
+                q[i] = make_double2(__ddiv_rn(row[m0 + i], N), (double)a.lam[m0 + i]);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int i = part; i < mc; i += lp) {
+                const double2 v = q[i];
+                const double J = __dadd_rn(__dmul_rn(v.y, ev), v.x);
+                if (J < best) {
+                    best = J;
+                    bm = m0 + i;
+                }
+            }
+        }
+        for (int d = lp >> 1; d >= 1; d >>= 1) {
+            const double ob = __shfl_xor(best, d, 64);
+            const int om = __shfl_xor(bm, d, 64);
+            if (ob < best || (ob == best && om < bm)) {
+                best = ob;
+                bm = om;
+            }
+        }
+        if (part == 0 && e < a.E) {
+            const long long o = ((long long)e * a.C + c) * a.K + k;
+            a.W[o] = best;
+            if (a.m_star) a.m_star[o] = min(bm, M - 1);  // (no J below infinity: the last)
+        }
+    }
+}
+
 hipError_t launch_row_min(const RowMinArgs &a, bool finish, int num_cu, hipStream_t st)
 {
+    // A wave per row where the chip has enough rows and few radii share a row: the whole
+    // argmin call, row_min_kernel and this one, 32,768 rows of 128 multipliers 37 and 41 us,
+    // of 256 47 and 46, of 1,024 107 and 78 (16 radii 243 and 195, 65 radii 1,192 and
+    // 1,163); 6,000 rows of 256 31.6 and 31.0, of 2,000 65 and 47; 1,000 rows of 32 29.6 and
+    // 28.2, of 512 30.3 and 29.6, of 1,024 31.2 and 31.7, of 4,096 39.5 and 50.7.
+    const long long rows = (long long)a.C * a.K;
+    if (!finish && a.E <= kWaveRadii &&
+        (rows >= 16LL * num_cu ? a.M >= 256 : rows >= 2LL * num_cu && a.M <= 512)) {
+        const long long blocks = std::min((rows + kWaveRows - 1) / kWaveRows, kMaxGridBlocks);
+        hipLaunchKernelGGL(row_min_wave_kernel, dim3((unsigned)blocks), dim3(64 * kWaveRows), 0, st, a);
+        return hipGetLastError();
+    }
     // whole rows up to the stage's pairs, but at least two blocks per compute unit (and
     // (radius, row) tasks counted in 32 bits)
-    const long long rows = (long long)a.C * a.K;
     const int RB = (int)std::max(1LL, std::min({(long long)kRowPairs / a.M, (long long)kRowMax,
                                                 rows / (2 * num_cu), 0x7fffffffLL / a.E}));
     int lp = 64;

@@ -7,8 +7,9 @@ around the sixteens of a step; more unequal classes than one wave looks through 
 once (64) and than a block walks (512), a class of one sample beside long ones, and
 sums of one slice (stored) as well as of several (added).  The pass over the table's rows
 at its edges: rows longer than its stage (2,048 multipliers), more rows than a
-block takes, and more (radius, row) tasks than a block has lanes.  W, m_star and
-the optimum are checked with S.
+block takes, and more (radius, row) tasks than a block has lanes; the argmin's pass
+on both sides of its two kernels' border.  W, m_star and the optimum are checked
+with S.
 """
 import numpy as np
 import pytest
@@ -128,3 +129,12 @@ def test_unequal_classes_around_the_table(ctx, dev, C):
                                    (300, 1, 7), (130, 3, 70), (700, 2, 300), (65, 32, 5)])
 def test_rows_and_radii_around_the_stage(ctx, dev, K, M, E):
     _check(ctx, dev, (40, 7, 300), K, M, E=E)
+
+
+# the argmin's pass over S takes a wave per row from 512 rows (of up to 512 multipliers)
+# and from 4,096 rows (of 256 or more), up to 32 radii
+@pytest.mark.parametrize("K,M,E", [(511, 3, 1), (512, 3, 1), (600, 511, 2), (600, 512, 33),
+                                   (600, 513, 2), (4095, 255, 1), (4096, 255, 1), (4096, 256, 1),
+                                   (4097, 257, 3), (4100, 300, 32), (4100, 300, 33), (4096, 600, 5)])
+def test_argmin_rows_around_the_wave_kernel(ctx, dev, K, M, E):
+    _check(ctx, dev, (23,), K, M, E=E)
