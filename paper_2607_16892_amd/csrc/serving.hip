@@ -479,47 +479,84 @@ __device__ ConfigPre config_view(const ConfigBufs &b, int C, int G)
     return q;
 }
 
-// One block.
+// One block of kBlockThreads; lds: kStateLds doubles.  G <= 32, so the five sums of every
+// configuration have a thread each.
 __device__ void config_prep_block(const SvcArgs &s, const double *T, const double *ET2,
                                   const double *pi, const int32_t *eta_c, const uint8_t *delta,
-                                  const ConfigPre &q)
+                                  const ConfigPre &q, double *lds)
 {
-    const int t = threadIdx.x, nt = blockDim.x, C = s.C, G = s.G;
-    auto kept = [&](int j) { return pi[j] != 0.0 || !(fabs(T[j]) < INFINITY); };
+    constexpr int nt = kBlockThreads;
+    static_assert(5 * nt + kLpMaxG <= kStateLds && 5 * kLpMaxG <= nt, "a tile; a thread per sum");
+    const int t = threadIdx.x, C = s.C, G = s.G;
+    // calls f(g, pi, T) for the configurations of class c, in order
+    auto routing = [&](int c, auto &&f) {
+        for (int g0 = 0; g0 < G; g0 += 8) {
+            double p[8], w[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int j = c * G + min(g0 + i, G - 1);
+                p[i] = pi[j];
+                w[i] = T[j];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (g0 + i < G) f(g0 + i, p[i], w[i]);
+        }
+    };
+    auto kept = [](double p, double w) { return p != 0.0 || !(fabs(w) < INFINITY); };
     for (int c = t; c < C; c += nt) {
         double a = 0.0, gpu = 0.0;
         int n = 0;
-        for (int g = 0; g < G; ++g) {
-            const double p = pi[c * G + g];
+        routing(c, [&](int g, double p, double w) {
             a = a + p;
-            gpu = gpu + p * (s.c_gpu * (double)(s.tau[g] * s.pp[g]) * T[c * G + g]);
-            n += kept(c * G + g) ? 1 : 0;
-        }
+            gpu = gpu + p * (s.c_gpu * (double)(s.tau[g] * s.pp[g]) * w);
+            n += kept(p, w) ? 1 : 0;
+        });
         q.a[c] = a;
         q.gpu[c] = gpu;
         q.start[c + 1] = n;
     }
-    for (int g = nt - 1 - t; g < G; g += nt) {  // (the last threads: the first hold the classes)
-        double used = 0.0, pre = 0.0, load = 0.0, X = 0.0, m2 = 0.0;
-        int route = 0;
-        for (int c = 0; c < C; ++c) {
-            const int j = c * G + g;
-            const int dl = delta[j] ? s.Lpre[c] : 0;
-            used = used + (double)s.lam[c] * T[j] * pi[j] * (double)(s.Lin[c] + eta_c[c] - dl);
-            pre = pre + (double)dl;
-            const double wgt = (double)s.lam[c] * pi[j];
-            load = load + wgt * T[j];
-            X = X + wgt;
-            m2 = m2 + wgt * ET2[j];
-            route |= pi[j] > 0.0;
+    // a tile of classes at a time: a thread per (class, configuration) forms its five terms,
+    // then a thread per (sum, configuration) adds them up in class order (one thread per
+    // configuration, each class a round trip, took 52 us for 200 classes and 12
+    // configurations, this takes 16; 88 and 45 for 250 and 32)
+    const int tile = nt / G, sum = t / G, g1 = t % G;
+    int *any = reinterpret_cast<int *>(lds + 5 * nt);  // [G] some pi_cg > 0
+    if (t < G) any[t] = 0;
+    double acc = 0.0;
+    bool route = false;
+    for (int c0 = 0; c0 < C; c0 += tile) {
+        const int n = min(tile, C - c0);
+        if (sum < n) {  // (t = class of the tile, configuration)
+            const int c = c0 + sum, j = c * G + g1;
+            const double p = pi[j], w = T[j], w2 = ET2[j], lam = (double)s.lam[c];
+            const int pre = s.Lpre[c], res = s.Lin[c] + eta_c[c], dl = delta[j] ? pre : 0;
+            const double wgt = lam * p;
+            lds[t] = lam * w * p * (double)(res - dl);
+            lds[nt + t] = (double)dl;
+            lds[2 * nt + t] = wgt * w;
+            lds[3 * nt + t] = wgt;
+            lds[4 * nt + t] = wgt * w2;
+            route = route || p > 0.0;
         }
-        q.used[g] = used;
-        q.pre[g] = pre;
-        q.load[g] = load;
-        q.X[g] = X;
-        q.m2[g] = m2;
-        q.route[g] = route;
+        __syncthreads();
+        if (route) any[g1] = 1;
+        if (sum < 5) {
+            const double *v = lds + sum * nt + g1;
+            int i = 0;
+            for (; i + 8 <= n; i += 8) {
+                double x[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) x[k] = v[(i + k) * G];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) acc = acc + x[k];
+            }
+            for (; i < n; ++i) acc = acc + v[i * G];
+        }
+        __syncthreads();
     }
+    if (sum < 5) (sum == 0 ? q.used : (sum == 1 ? q.pre : (sum == 2 ? q.load : (sum == 3 ? q.X : q.m2))))[g1] = acc;
+    if (t < G) q.route[t] = any[t];
     __syncthreads();
     if (t < 64) {  // the classes' entry counts to starts, by one wave
         int base = 0;
@@ -535,14 +572,13 @@ __device__ void config_prep_block(const SvcArgs &s, const double *T, const doubl
     __syncthreads();
     for (int c = t; c < C; c += nt) {
         int o = q.start[c];
-        for (int g = 0; g < G; ++g) {
-            const int j = c * G + g;
-            if (!kept(j)) continue;
+        routing(c, [&](int g, double p, double w) {
+            if (!kept(p, w)) return;
             q.g[o] = g;
-            q.pi[o] = pi[j];
-            q.T[o] = T[j];
+            q.pi[o] = p;
+            q.T[o] = w;
             ++o;
-        }
+        });
     }
 }
 
@@ -606,8 +642,9 @@ __global__ __launch_bounds__(kBlockThreads) void config_prep_kernel(
     SvcArgs s, const double *T, const double *ET2, const double *pi, const int32_t *eta_c,
     const uint8_t *delta, ConfigBufs b)
 {
+    __shared__ double lds[kStateLds];
     const ConfigPre q = config_view(b, s.C, s.G);
-    config_prep_block(s, T, ET2, pi, eta_c, delta, q);
+    config_prep_block(s, T, ET2, pi, eta_c, delta, q, lds);
     __syncthreads();
     config_wait_table(s, q, b.gpus, b.wt);
 }
@@ -670,11 +707,11 @@ __device__ __forceinline__ int unrank(long long r, int G, int J, const int32_t *
 // z_g alone), the classes' sums run over the routing's non-zero entries, and a z
 // whose waits are all those of the one before (only counts of configurations
 // without traffic differ) has its objective.  The tables and the classes' data are
-// staged in LDS where they fit; a thread keeps its waits and counts of groups there
-// ([G][threads]).  747,788 configurations of 15 classes:
+// staged in LDS where they fit; a thread keeps its counts of groups there ([G][threads])
+// and, kWaits, its waits.  747,788 configurations of 15 classes:
 // 40 us, 101 before (one rank a thread, its waits recomputed with five
 // divisions each, its counts read from memory, all 180 entries of the routing).
-template <bool kLds>
+template <bool kLds, bool kWaits>
 __global__ __launch_bounds__(kSvcThreads) void config_search_kernel(SvcArgs s, long long nz,
                                                                     int each, const double *Wc,
                                                                     ConfigBufs b)
@@ -686,10 +723,11 @@ __global__ __launch_bounds__(kSvcThreads) void config_search_kernel(SvcArgs s, l
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, G = s.G, J = s.J;
     if (t < G) gpus[t] = b.gpus[t];
     const ConfigPre q = config_view(b, s.C, G);
-    double *wl = dyn;                                        // [G][threads]
-    int32_t *zl = reinterpret_cast<int32_t *>(wl + G * kSvcThreads);  // [G][threads]
+    // a thread's waits (kWaits) and counts (J <= 4,096): [G][threads] each
+    double *wl = dyn;
+    uint16_t *zl = reinterpret_cast<uint16_t *>(wl + (kWaits ? G * kSvcThreads : 0));
     // when kLds: the tables and the classes' data behind them
-    long long *lw = reinterpret_cast<long long *>(wl + G * kSvcThreads + G * kSvcThreads / 2);
+    long long *lw = reinterpret_cast<long long *>(zl + G * kSvcThreads);
     double *lt = reinterpret_cast<double *>(lw + (G + 1) * (J + 1)), *ld = lt + G * (J + 1);
     int32_t *li = reinterpret_cast<int32_t *>(ld + 5 * s.C + 2 * s.C * G);
     if (kLds) {
@@ -722,10 +760,17 @@ __global__ __launch_bounds__(kSvcThreads) void config_search_kernel(SvcArgs s, l
     const long long r0 = ((long long)blockIdx.x * kSvcThreads + t) * each;
     if (r0 < nz) {
         int bad = 0;  // configurations that z does not allow
+        auto wait = [&](int g) {
+            const int o = g * kSvcThreads + t;
+            return kWaits ? wl[o] : wt[g * (J + 1) + zl[o]];
+        };
+        auto set = [&](int g, int v, double w) {
+            zl[g * kSvcThreads + t] = (uint16_t)v;
+            if (kWaits) wl[g * kSvcThreads + t] = w;
+        };
         int left = unrank(r0, G, J, gpus, ways, [&](int g, int v) {
             const double w = wt[g * (J + 1) + v];
-            zl[g * kSvcThreads + t] = v;
-            wl[g * kSvcThreads + t] = w;
+            set(g, v, w);
             bad += is_no_wait(w) ? 1 : 0;
         });
         const long long r1 = min(nz, r0 + each);
@@ -735,9 +780,7 @@ __global__ __launch_bounds__(kSvcThreads) void config_search_kernel(SvcArgs s, l
             if (!bad) {
                 if (!same) {
                     obj = 0.0;
-                    for (int c = 0; c < C; ++c)
-                        obj = obj + class_cost<kLds>(s, cc, c,
-                                                     [&](int g) { return wl[g * kSvcThreads + t]; });
+                    for (int c = 0; c < C; ++c) obj = obj + class_cost<kLds>(s, cc, c, wait);
                 }
                 same = true;
                 feas += obj < INFINITY ? 1 : 0;
@@ -749,14 +792,13 @@ __global__ __launch_bounds__(kSvcThreads) void config_search_kernel(SvcArgs s, l
             if (++r >= r1) break;
             // the next z: one more of the last configuration that the budget allows
             for (int g = G - 1; g >= 0; --g) {
-                const int n = gpus[g], o = g * kSvcThreads + t;
-                const int v = left >= n ? zl[o] + 1 : 0;
-                const double w0 = wl[o], w = wt[g * (J + 1) + v];
+                const int n = gpus[g], z0 = zl[g * kSvcThreads + t];
+                const int v = left >= n ? z0 + 1 : 0;
+                const double w0 = wait(g), w = wt[g * (J + 1) + v];
                 bad += (is_no_wait(w) ? 1 : 0) - (is_no_wait(w0) ? 1 : 0);
                 same = same && __double_as_longlong(w0) == __double_as_longlong(w);
-                left += v ? -n : zl[o] * n;
-                zl[o] = v;
-                wl[o] = w;
+                left += v ? -n : z0 * n;
+                set(g, v, w);
                 if (v) break;
             }
         }
@@ -958,7 +1000,7 @@ __global__ __launch_bounds__(kBlockThreads) void block1_kernel(SvcArgs s, Block1
     for (int i = t; i < CG; i += nt) a.d_new[i] = a.conc[i] > 1.0 ? 1 : 0;
     __syncthreads();
     const ConfigPre q = config_view(a.b, C, G);
-    config_prep_block(s, a.T, a.ET2, a.pi, a.eta_c, a.d_new, q);
+    config_prep_block(s, a.T, a.ET2, a.pi, a.eta_c, a.d_new, q, dyn);
     __syncthreads();
     config_wait_table(s, q, a.b.gpus, a.b.wt);
     if (t == 0) {
@@ -974,9 +1016,9 @@ __global__ __launch_bounds__(kBlockThreads) void state_objective_kernel(
     SvcArgs s, const double *T, const double *ET2, const double *pi, const int32_t *z,
     const int32_t *eta_c, const uint8_t *delta, const double *Wc, ConfigBufs b, double *out)
 {
-    __shared__ double w[kMaxG];
+    __shared__ double w[kMaxG], lds[kStateLds];
     const ConfigPre q = config_view(b, s.C, s.G);
-    config_prep_block(s, T, ET2, pi, eta_c, delta, q);
+    config_prep_block(s, T, ET2, pi, eta_c, delta, q, lds);
     __syncthreads();
     if (threadIdx.x < 64) {
         const double o = config_objective(s, q, Wc, z, w);
@@ -1016,8 +1058,10 @@ hipError_t lp1_prepare()
     const void *k[] = {reinterpret_cast<const void *>(lp1_kernel<true>),
                        reinterpret_cast<const void *>(block1_kernel<true>),
                        reinterpret_cast<const void *>(block1_kernel<false>),
-                       reinterpret_cast<const void *>(config_search_kernel<false>),
-                       reinterpret_cast<const void *>(config_search_kernel<true>)};
+                       reinterpret_cast<const void *>(config_search_kernel<false, false>),
+                       reinterpret_cast<const void *>(config_search_kernel<false, true>),
+                       reinterpret_cast<const void *>(config_search_kernel<true, false>),
+                       reinterpret_cast<const void *>(config_search_kernel<true, true>)};
     for (const void *f : k) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)kLp1LdsBytes);
@@ -1090,13 +1134,22 @@ hipError_t launch_config_search(const SvcArgs &s, long long nz, const double *Wc
                                 uint8_t *delta, double *best_obj, long long *best_rank,
                                 long long *n_feasible, int32_t *flag, hipStream_t st)
 {
-    const size_t own = (size_t)s.G * kSvcThreads * 12;  // a thread's waits and counts
+    // Tables staged and waits kept where two blocks fit a compute unit, else the tables
+    // staged and the waits looked up in them where three do, else the tables in memory and
+    // the waits kept where two do.  Staged without waits against kept without tables: 30
+    // classes, 32 configurations, 24 GPUs 473 and 1,317 us (one block a unit), 24
+    // configurations 31 and 58; 200 classes, 12 configurations, 48 GPUs (two blocks) 31 and
+    // 22.  Neither: 200 classes, 32 configurations, 20 GPUs 91 us, 278 with the waits kept.
+    const size_t counts = (size_t)s.G * kSvcThreads * 2, waits = (size_t)s.G * kSvcThreads * 8;
     const size_t tables = (size_t)(2 * s.G + 1) * (s.J + 1) * 8 + (size_t)s.C * (40 + 20 * s.G) +
                           (size_t)(s.C + 2) * 4;
-    const bool lds = own + tables <= kLp1LdsBytes / 2;  // (two blocks a compute unit)
-    hipLaunchKernelGGL(lds ? config_search_kernel<true> : config_search_kernel<false>,
-                       dim3((unsigned)config_parts(nz)), dim3(kSvcThreads),
-                       own + (lds ? tables : 0), st, s, nz, config_each(nz), Wc, b);
+    const bool both = counts + waits + tables <= kLp1LdsBytes / 2;
+    const bool lds = both || counts + tables <= kLp1LdsBytes / 3;
+    const bool keep = both || (!lds && counts + waits <= kLp1LdsBytes / 2);
+    const auto kernel = lds ? (keep ? config_search_kernel<true, true> : config_search_kernel<true, false>)
+                            : (keep ? config_search_kernel<false, true> : config_search_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)config_parts(nz)), dim3(kSvcThreads),
+                       counts + (keep ? waits : 0) + (lds ? tables : 0), st, s, nz, config_each(nz), Wc, b);
     hipLaunchKernelGGL(config_final_kernel, dim3(1), dim3(kBlockThreads), 0, st, s, config_parts(nz),
                        Wc, b, z, delta_new, delta, best_obj, best_rank, n_feasible, flag);
     return hipGetLastError();

@@ -1,9 +1,10 @@
 """Alg. 1 at the sizes where its kernels change how they work: the sweep with and
 without its operands in LDS, the routing LP and the fused Blocks 1-2 with the
 tableau in LDS and in memory, the configuration search with its tables in LDS and
-in memory, with one and with several configurations per thread.  Bars as in
-test_serving_gpu: everything but the LP in the same fixed-order arithmetic, bit
-for bit; the LP's objective to 1e-9 relative and its routing to 1e-7."""
+in memory, its waits kept and looked up, with one and with several configurations
+per thread.  Bars as in test_serving_gpu: everything but the LP in the same
+fixed-order arithmetic, bit for bit; the LP's objective to 1e-9 relative and its
+routing to 1e-7."""
 import numpy as np
 import pytest
 
@@ -97,16 +98,19 @@ def test_alg1_tableau_in_lds_and_in_memory(ctx, dev, C, seed):
     assert (g["info"]["outer"], g["info"]["inner"]) == (ref["outer"], ref["inner"])
 
 
-# two z, a part of a block, many blocks (the tables in LDS, one z per thread), and
-# 811,801 z: four per thread, the tables beyond LDS
-@pytest.mark.parametrize("J,configs", [(1, [(1, 1)]), (37, [(1, 1), (2, 1), (4, 2)]),
-                                       (170, [(1, 1), (2, 1), (4, 1)]),
-                                       (1800, [(1, 1), (2, 1)])])
+# two z, a part of a block, many blocks (the tables in LDS, one z per thread), 811,801 z
+# (four per thread, the tables beyond LDS); 32 configurations, whose waits are looked up:
+# tables in LDS, and beyond it; classes in more than one tile of the sums (1,024 entries)
+@pytest.mark.parametrize("C,J,configs", [(5, 1, [(1, 1)]), (5, 37, [(1, 1), (2, 1), (4, 2)]),
+                                         (5, 170, [(1, 1), (2, 1), (4, 1)]),
+                                         (5, 1800, [(1, 1), (2, 1)]),
+                                         (5, 40, [(4, 2), (8, 2), (4, 4), (8, 4)] * 8),
+                                         (33, 40, [(4, 2), (8, 2), (4, 4), (8, 4)] * 8),
+                                         (171, 10, None), (86, 10, None), (85, 10, None)])
 @pytest.mark.parametrize("routed", ["all", "none of the last", "nothing"])
-def test_config_search_paths(ctx, dev, J, configs, routed):
+def test_config_search_paths(ctx, dev, C, J, configs, routed):
     import torch
     from paper_2607_16892_amd import serving as gs
-    C = 5
     w, svc = serving_workload(C=C, N=500, J=J, K=65, M=8, configs=configs, seed=J)
     s = gs.Service.from_model(svc, dev)
     print(f"[gpu] config search J={J} G={svc.G} routed={routed}", flush=True)
