@@ -383,8 +383,8 @@ long long max_segment(const dro_problem *p)
 // stores its 64 KB of counts and the prefix pass reads a segment's rows in 32 blocks, while
 // a merged block holds any number of samples but adds its counts with atomics, after a zero
 // fill, and every segment gets as many blocks.  Packed against merged
-// (dro_reservation_cost, us): 1 segment of 2e6 (122 rows) 42 and 48, of 4e6 (245) 53 and
-// 52, of 5e7 (763) 116 and 76; 8 of 4e6 (62 each) 59 and 65, of 1e7 (153 each) 118 and 101;
+// (dro_reservation_cost, us): 1 segment of 2e6 (122 rows) 42 and 48, of 1.2e7 (184) 51 and
+// 55, of 5e7 (763) 116 and 76; 8 of 4e6 (62 each) 59 and 65, of 1e7 (153 each) 118 and 101;
 // 16 of 4e6 (62 each) 95 and 83; 40 of 1e6 (16 each) 74 and 78, of 2e6 (31 each) 126 and
 // 110; 1,000 of 3e4 (2 each) 339 and 323.  A segment of 2e7 beside one of 100: 70 and 60,
 // beside 100 of 1,000: 81 and 574.  The rows' scratch ends at kMaxCountRows (270 MB), where

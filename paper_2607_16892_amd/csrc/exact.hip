@@ -462,10 +462,15 @@ long long row_part_len(const int64_t *offsets_h, int S, int num_cu)
     // The shortest parts whose rows still fit one resident block per compute
     // unit (their LDS counts allow one; a few more rows than units would take a
     // second pass over the chip), at least 16,384 samples, below which a row's
-    // fixed cost (clearing and storing its counts) passes its reading time, and
-    // at most what 16-bit counts hold.
+    // fixed cost (clearing and storing its counts) passes its reading time, at
+    // least a 128th of the longest segment, whose rows the select and the prefix
+    // pass read one after the other (5e6 samples beside two short segments: the
+    // quantile 42 us with 254 rows, 38 with 128, the counts 54 and 45), and at most
+    // what 16-bit counts hold.
     const long long slots = (long long)num_cu * ((S + num_cu - 1) / num_cu);
-    long long lo = 16384, hi = kQMaxPart;
+    long long max_n = 0;
+    for (int s = 0; s < S; ++s) max_n = std::max(max_n, (long long)(offsets_h[s + 1] - offsets_h[s]));
+    long long lo = std::min(kQMaxPart, std::max(16384LL, (max_n + 127) / 128)), hi = kQMaxPart;
     // (only segments above the shortest part have more than one row: the search looks
     // those through, not the many short ones of a large problem)
     std::vector<long long> large;

@@ -29,11 +29,12 @@ def ctx(dev):
     c.close()
 
 
-# (the last three through the merged histogram: 214 rows of one segment, 254 of one beside
+# (the last three through the merged histogram: 202 rows of one segment, 214 of one beside
 # two short ones, 806 of 13)
 @pytest.mark.parametrize("sizes", [(1,), (15,), (16_385,), (20, 300_001, 1, 40_000),
-                                   (600_000,) * 3, (1_100_000,), (3_250_000,),
-                                   (3_500_000,), (3, 5_000_000, 40), (4_000_000,) * 13])
+                                   (600_000,) * 3, (1_100_000,), (12_900_000,),
+                                   (3, 5_000_000, 40), (13_200_000,), (3, 14_000_000, 40),
+                                   (4_000_000,) * 13])
 def test_every_prefix_entry(ctx, dev, sizes):
     import torch
     import paper_2607_16892_amd as dro

@@ -161,12 +161,12 @@ def test_segments_with_unequal_part_counts(ctx, dev, n_small, n_big):
     _check(ctx, dev, w)
 
 
-# rows of 16,384 samples: on both sides of the loads the select has in flight (16 rows by
-# 4 groups of the coarse counts, by 8 of the values)
-@pytest.mark.parametrize("rows", [1, 4, 5, 16, 17, 63, 64, 65, 127, 128, 129, 200])
+# on both sides of the loads the select has in flight (16 rows by 4 groups of the coarse
+# counts, by 8 of the values): rows of 16,384 samples up to 128, of 65,535 beyond
+@pytest.mark.parametrize("rows", [1, 4, 5, 16, 17, 63, 64, 65, 127, 128, 129, 190])
 def test_row_counts_around_the_loads_in_flight(ctx, dev, rows):
     rng = np.random.default_rng(rows)
-    n = (rows - 1) * 16384 + 1
+    n = (rows - 1) * (16384 if rows <= 128 else 65535) + 1
     x = rng.integers(0, 32769, n).astype(np.int32)
     x[rng.integers(n, size=n // 50 + 1)] = 32768
     c_p = [1.0, 3.0, 2.0 ** 7, 2.0 ** -10, 127.0, 0.01]
