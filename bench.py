@@ -513,7 +513,7 @@ def main():
                                      "FETCH_SIZE + WRITE_SIZE of the committed counter profile: "
                                      "the samples are fetched about once, and a block adds a "
                                      "tile's exact sums to the table with one 64-bit atomic per "
-                                     "pair each time it leaves that tile (about 2.3 times per "
+                                     "pair each time it leaves that tile (about 2.4 times per "
                                      "pair), about 8 bytes of write traffic each",
                      "launch_ms": dense_ms, "launch_ms_median": float(np.median(launch_times)),
                      "launch_ms_min": float(np.min(launch_times)), "evals_per_launch": evals,

@@ -225,7 +225,8 @@ int dro_continuous_dual(dro_ctx *ctx, const dro_problem *p, int32_t E, const flo
  *   count[c] = N_c,  sum[c] = sum of x,  sumsq[c] = sum of x^2,
  *   xmax[c]  = the largest sample of class c.
  * All outputs are device arrays of length C.  Uses C, S, offsets, seg, xi, L of
- * `p` (the value histogram assumes validated samples, 0 <= x <= L <= 2^15). */
+ * `p` (samples are clamped to 0 .. 2^15, so the sums are those of validated
+ * samples, 0 <= x <= L <= 2^15). */
 int class_moments(dro_ctx *ctx, const dro_problem *p, int64_t *count, int64_t *sum,
                   int64_t *sumsq, int32_t *xmax, dro_stream_t stream);
 
@@ -375,8 +376,8 @@ int bcd_reservation_sweep(dro_ctx *ctx, int32_t C, int32_t K, const double *W,
 int bcd_prefix_cache(dro_ctx *ctx, int32_t C, int32_t G, const double *conc, uint8_t *delta,
                      dro_stream_t stream);
 
-/* Block 3: every z in Z = {z >= 0 : sum_g z_g tau_g pp_g <= J}, one thread
- * per z in lexicographic order of (z_0, .., z_{G-1}), evaluated with pi, the
+/* Block 3: every z in Z = {z >= 0 : sum_g z_g tau_g pp_g <= J} in lexicographic
+ * order of (z_0, .., z_{G-1}), consecutive z per thread, evaluated with pi, the
  * reservations and delta fixed; the first minimiser of the objective over the
  * feasible z replaces z (device int32 [G], in/out) unless the incoming z
  * attains the minimum (no feasible z: z is kept).  best_objective (double),
@@ -400,7 +401,7 @@ int bcd_config_search(dro_ctx *ctx, int32_t C, const dro_service *svc, const dou
  * rounds, simplex pivots, status bits: 1 pivot limit, 2 infeasible LP start,
  * 4 unbounded LP, 8 a class without a feasible reservation, 16 Block 1 hit
  * max_inner, 32 the loop hit max_outer}.  Synchronises the stream once per
- * Block 1 round (the loop's decisions are read on the host).  Uses every
+ * outer iteration (the change of z and delta is read on the host).  Uses every
  * field of `p`. */
 int dro_bcd_solve(dro_ctx *ctx, const dro_problem *p, const float *eps, const dro_service *svc,
                   int32_t max_outer, int32_t max_inner, int32_t *z, int32_t *k, double *pi,
