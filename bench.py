@@ -54,11 +54,11 @@ PAPER_FLOPS_PER_EVAL = 7                 # 2 multiply-adds (4), a 3-way max (2),
 # csrc/wave.h, comments and layout stripped, identified by the hash prefix) and
 # are reported as null for any other code or workload.
 DENSE_COUNTERS = {
-    "dense_code_sha256_16": "a2d4bca4338abecf",
+    "dense_code_sha256_16": "98a33ff23c635ab1",
     "workload": "mixture-16x1M",
     "valu_instr_per_eval": 0.50313,    # SQ_INSTS_VALU x 64 / evaluations
-    "clock_ghz": 2.376,                # GRBM_GUI_ACTIVE / 8 XCDs / duration
-    "hbm_bytes_per_launch": 226903680,  # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated)
+    "clock_ghz": 2.373,                # GRBM_GUI_ACTIVE / 8 XCDs / duration
+    "hbm_bytes_per_launch": 224913984,  # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated)
     "source": "profiles/dense_kernel_mixture-16x1M_counters.md",
 }
 

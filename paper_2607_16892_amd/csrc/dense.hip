@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kRowThreads) void row_min_kernel(RowMinArgs a, int 
 }
 
 // The minimum over the multipliers from an S that is there, one wave per row: the wave
-// stages q_m = S / N and lambda_m of a chunk of multipliers, its lanes split over up to 64
+// stages q_m = S / N and lambda_m of a chunk of multipliers, its lanes split over up to 32
 // radii, and nothing waits for another wave.  Bound by reading S where the rows are many
 // and long.
 constexpr int kWaveRows = 4;     // waves (rows) per block

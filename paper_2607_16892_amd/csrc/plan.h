@@ -57,7 +57,8 @@ constexpr int kSliceGL[kSliceShapes] = {256, 128, 64, 64, 64};
 
 struct DensePlan {
     int tiles;         // tiles of the K * M pairs of a class, in table order
-    int P;             // sample slices per tile (direct: 0 = slices_of each class's size and len)
+    int P;             // sample slices per tile (direct: 0 = they differ, slices_of each class's
+                       // size and len)
     int direct;        // 1: one block per slice, no claims (smaller problems)
     int shape;         // direct: the tile shape
     int len;           // direct: samples per slice, at most
@@ -99,8 +100,8 @@ constexpr long long kMinSliceN = 64;
 // thresholds, LDS sums, flush: 31 us for 8,192 pairs from slices of 12,500 and
 // 14,286 samples, 5 us for 512).  For every shape and w the shortest slices whose
 // blocks fit w passes; a sum split over slices also pays the zero fill of the
-// table.  Where the sizes are bins, their largest sizes stand for all (blocks is then
-// an upper bound).
+// table.  Where the sizes are bins, their largest sizes stand for all; plan_dense
+// counts the slices of the true ones.
 constexpr int kSliceThreads = 1024;
 constexpr long long kMaxDirectBlocks = (1LL << 32) / kSliceThreads - 1;  // below 2^32 work-items
 // A block of unequal classes, some of several slices, finds its class by walking them 64
@@ -158,9 +159,7 @@ inline double plan_slices(const SizeCounts &sizes, int K, int M, int num_cu, Den
                 best->direct = 1;
                 best->shape = sh;
                 best->len = (int)len;
-                best->P = one ? 1 : (sizes.size() == 1 ? slices_of(sizes[0].first, (int)len) : 0);
                 best->stored = one;
-                best->blocks = (long long)blocks;
             }
         }
     }
@@ -188,8 +187,14 @@ DensePlan plan_dense(Each &&each, int C, int K, int M, int num_cu, int bpc)
     DensePlan direct;
     const double cost = plan_slices(sizes, K, M, num_cu, &direct);
     if (cost >= 0.0 && cost <= claimed) {
-        long long slices = 0;
-        each([&](long long n, long long classes) { slices += slices_of(n, direct.len) * classes; });
+        long long slices = 0, min_n = max_n;
+        each([&](long long n, long long classes) {
+            slices += slices_of(n, direct.len) * classes;
+            min_n = std::min(min_n, n);
+        });
+        // (the sizes of one bin can differ in it too)
+        direct.P = slices_of(min_n, direct.len) == slices_of(max_n, direct.len)
+                       ? slices_of(max_n, direct.len) : 0;
         direct.blocks = slices * direct.tiles;
         return direct;
     }

@@ -111,6 +111,16 @@ def test_more_unequal_classes_than_a_wave_holds(ctx, dev):
     _check(ctx, dev, sizes[60:70], 20, 30, seg=[c % 10 for c in range(70)])
 
 
+# more sizes than the plan lists one by one, all in one of its bins, with slice counts that
+# differ by one
+@pytest.mark.parametrize("lo,step,C,K,M", [(8192, 15, 65, 7, 11), (40_960, 40, 100, 64, 32)])
+def test_unequal_classes_of_one_bin(ctx, dev, lo, step, C, K, M):
+    sizes = [lo + i * step for i in range(C)]
+    p = dense_plan({n: 1 for n in sizes}, K, M)
+    assert p["direct"] and len({-(-n // p["len"]) for n in sizes}) == 2
+    _check(ctx, dev, sizes, K, M)
+
+
 # (walked up to 512, by the table of first slices beyond; a thread of that table's launch
 # holds one class up to 1,024)
 @pytest.mark.parametrize("C", [512, 513, 1024, 1025, 1500, 2049])

@@ -18,8 +18,8 @@ def _check(p, sizes, K, M):
         slices = {n: -(-n // p["len"]) for n in sizes}
         assert p["blocks"] == p["tiles"] * sum(slices[n] * c for n, c in sizes.items())
         assert p["stored"] == all(s == 1 for s in slices.values())
-        one = len(set(slices.values())) == 1 and (len(sizes) == 1 or p["stored"])
-        assert p["P"] == (next(iter(slices.values())) if one else 0)
+        same = len(set(slices.values())) == 1
+        assert p["P"] == (next(iter(slices.values())) if same else 0)
     else:
         T = sum(sizes.values()) * p["tiles"]
         assert p["tiles"] == -(-K * M // 8192) and p["P"] >= 1
@@ -55,6 +55,17 @@ def test_more_sizes_than_the_plan_lists(distinct, K, M):
         sizes[rng.choice([rng.randint(1, 40), rng.randint(1, 90_000), rng.randint(1, 300)])
               if distinct < 300 else rng.randint(1, 90_000)] = rng.randint(1, 3)
     _check(dense_plan(sizes, K, M), sizes, K, M)
+
+
+@pytest.mark.parametrize("lo,width", [(1 << 10, 128), (1 << 13, 1024), (40_960, 4096), (1 << 16, 8192),
+                                      (1 << 20, 131_072)])
+@pytest.mark.parametrize("distinct", [65, 100, 128])
+@pytest.mark.parametrize("K,M", [(7, 11), (64, 32), (200, 100)])
+def test_sizes_of_one_bin(lo, width, distinct, K, M):
+    # unequal sizes in one eighth of an octave: their slice counts differ
+    for step in (1, width // distinct):
+        sizes = {lo + i * step: 1 for i in range(distinct)}
+        _check(dense_plan(sizes, K, M), sizes, K, M)
 
 
 def test_equal_sizes_give_the_plan_of_their_count():
